@@ -29,6 +29,7 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));  // at any float's address
 
 constexpr float kNegInf = -INFINITY;
 
@@ -1837,20 +1838,96 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
 }
 
-// fp32 LM head for small validation shapes: one thread per vocab row.
+// fp32 LM head on the fp32 matrix cores: C^T[16 vocab x 16 rows] += W[16 x 4]
+// X^T[4 x 16] (v_mfma_f32_16x16x4_f32). Bound: the W stream, and at small
+// shapes one memory round trip. A block of 4 waves owns VT 16-row vocab tiles
+// for up to 16 NT rows of x; the waves split the hidden dimension in interleaved
+// 32-wide units (whole 128-byte lines of each W row), so even a one-tile block
+// keeps 4 x U units in flight, and add their sums through LDS in wave order.
+// Lane (col, quad) loads elements 32u + 8 quad .. + 7 of its W and x rows as two
+// 16-byte loads; product e of a unit contracts element e of every quad. A row's
+// sum of squares comes from the same x operands. VT = 2 halves the x reads per
+// W byte where V fills the GPU anyway.
+// 5 rows x 1000 x 256: 4.9 us (166 us with one thread per vocab row).
+template <int NT, int VT>
 __global__ __launch_bounds__(256) void k_lmhead_f32(LmArgs a) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= a.V) return;
-  const float* W = (const float*)a.w + (size_t)v * a.K;
-  for (int m = 0; m < a.M; ++m) {
-    const float* x = (const float*)a.x + (size_t)m * a.K;
-    float ss = 0.f, dot = 0.f;
-    for (int k = 0; k < a.K; ++k) {
-      ss += x[k] * x[k];
-      dot += x[k] * W[k];
+  constexpr int U = 4;  // units in flight per wave
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int col = lane & 15, quad = lane >> 4;
+  const int K = a.K, KU = (K + 31) / 32;  // (K is a multiple of 4)
+  const int v0 = 16 * VT * blockIdx.x;
+  const float* wrow[VT];
+#pragma unroll
+  for (int vt = 0; vt < VT; ++vt) wrow[vt] = (const float*)a.w + (size_t)min(v0 + 16 * vt + col, a.V - 1) * K;
+  __shared__ f32x4 red[4][VT][NT][64];
+  __shared__ float red_ss[4][NT][16];
+  for (int m0 = 0; m0 < a.M; m0 += 16 * NT) {
+    const float* xrow[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) xrow[nt] = (const float*)a.x + (size_t)min(m0 + 16 * nt + col, a.M - 1) * K;
+    f32x4 acc[VT][NT];
+    float ss[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      ss[nt] = 0.f;
+#pragma unroll
+      for (int vt = 0; vt < VT; ++vt) acc[vt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    const float rho = a.rms ? 1.0f / sqrtf(ss / (float)a.K + 1e-5f) : 1.0f;
-    a.logits[(size_t)m * a.V + v] = dot * rho;
+    // elements past K read as zero (both operands: 0 x inf is NaN)
+    auto ld = [&](const float* row, int k) __attribute__((always_inline)) {
+      f32x4 v = *(const f32x4_a4*)(row + min(k, K - 4));
+      if (k >= K) v = f32x4{0.f, 0.f, 0.f, 0.f};
+      return v;
+    };
+    for (int u0 = wave; u0 < KU; u0 += 4 * U) {
+      f32x4 wv[U][VT][2], xv[U][NT][2];
+#pragma unroll
+      for (int i = 0; i < U; ++i) {
+        const int k = 32 * (u0 + 4 * i) + 8 * quad;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+          for (int vt = 0; vt < VT; ++vt) wv[i][vt][h] = ld(wrow[vt], k + 4 * h);
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) xv[i][nt][h] = ld(xrow[nt], k + 4 * h);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < U; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+              ss[nt] = fmaf(xv[i][nt][h][e], xv[i][nt][h][e], ss[nt]);
+#pragma unroll
+              for (int vt = 0; vt < VT; ++vt)
+                acc[vt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[i][vt][h][e], xv[i][nt][h][e], acc[vt][nt], 0,
+                                                                   0, 0);
+            }
+    }
+    if (m0 > 0) __syncthreads();  // the previous row group's sums have been read
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      float t = ss[nt] + __shfl_xor(ss[nt], 16);
+      t += __shfl_xor(t, 32);
+      if (quad == 0) red_ss[wave][nt][col] = t;
+#pragma unroll
+      for (int vt = 0; vt < VT; ++vt) red[wave][vt][nt][lane] = acc[vt][nt];
+    }
+    __syncthreads();
+    for (int i = wave; i < VT * NT; i += 4) {  // whole waves
+      const int vt = i / NT, nt = i % NT, m = m0 + 16 * nt + col, v = v0 + 16 * vt + 4 * quad;
+      const f32x4 c = (red[0][vt][nt][lane] + red[1][vt][nt][lane]) + (red[2][vt][nt][lane] + red[3][vt][nt][lane]);
+      const float t = (red_ss[0][nt][col] + red_ss[1][nt][col]) + (red_ss[2][nt][col] + red_ss[3][nt][col]);
+      const float rho = a.rms ? 1.0f / sqrtf(t / (float)K + 1e-5f) : 1.0f;
+      if (m >= a.M) continue;
+      float* out = a.logits + (size_t)m * a.V + v;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (v + r < a.V) out[r] = c[r] * rho;
+    }
   }
 }
 
@@ -2957,7 +3034,16 @@ hipError_t launch_lmhead(const LmArgs& a0, bool bf16, hipStream_t st, const Timi
     return fused ? go(k_lmhead_bf16<VT, NT, true, true>, dim3(blocks), dim3(256), 0, st, t0(tm), t1(tm), b)
                  : go(k_lmhead_bf16<VT, NT, false, true>, dim3(blocks), dim3(256), 0, st, t0(tm), t1(tm), b);
   }
-  return go(k_lmhead_f32, dim3((a.V + 255) / 256), dim3(256), 0, st, t0(tm), t1(tm), a);
+  // two vocab tiles per block once one-tile blocks would come to several per compute unit
+  const bool two = a.V >= 16384;
+  const dim3 g((a.V + (two ? 31 : 15)) / (two ? 32 : 16));
+#define PCED_F32(NT)                                                                          \
+  return two ? go(k_lmhead_f32<NT, 2>, g, dim3(256), 0, st, t0(tm), t1(tm), a)                \
+             : go(k_lmhead_f32<NT, 1>, g, dim3(256), 0, st, t0(tm), t1(tm), a);
+  if (a.M <= 16) PCED_F32(1)
+  if (a.M <= 32) PCED_F32(2)
+  PCED_F32(3)
+#undef PCED_F32
 }
 
 hipError_t launch_beta(const BetaArgs& a, int n_seqs, int n_exp, hipStream_t st, const Timing* tm) {
