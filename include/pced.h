@@ -169,9 +169,10 @@ const char* pced_last_error(void);
  *                   Device sources are copied by a kernel on `stream` and must
  *                   stay valid until the stream has executed this call. Host
  *                   sources cross to the device during the call: the library
- *                   re-lays each host sequence into the pool's page layout in
- *                   host memory and copies it with hipMemcpyAsync on `stream`,
- *                   waiting for those copies before it returns (the one
+ *                   copies each host sequence with hipMemcpyAsync on `stream`
+ *                   into the workspace (in pieces of at most 64 MiB), from
+ *                   where a kernel moves it into the pool's page layout, and
+ *                   waits for the stream before it returns (the one
  *                   synchronisation in the library), so host buffers may be
  *                   freed as soon as the call returns
  *   k_pool, v_pool  device, pced_pool_bytes(cfg) each, caller-owned; this call

@@ -75,13 +75,15 @@ bool cfg_valid(const pced_config* c, std::string* why) {
   return true;
 }
 
+constexpr size_t kLoadStage = (size_t)64 << 20;  // staging of host-memory caches, at most
+
 struct Layout {
   size_t len0, page_table, seq_query, query_seq0, query_exp0, exp_seq, exp_query, prior, logw, beta_fixed,
       load_items, src_k, src_v, meta_end;
   size_t chunk_info, seg, nparts, work_pages, prev_tok, beta, part_acc, part_ml, x, logits,
       rho, x_packed, fuse_part, lse_part, jsd_part, agg_lse, syn_q, syn_k, syn_v, dec_h, dec_a, dec_act, dec_ss, dec_rho, dec_part,
       rope, pf_len0, pf_pt, pf_tok, pf_glen0, pf_gpt, pf_nparts, pf_rho, pf_h, pf_a, pf_act, pf_ss, pf_q, pf_x, pf_part_acc, pf_part_ml, pf_proj,
-      total;
+      load_stage, stage_bytes, total;
   int pf_rows;          // rows of one prefill chunk (sequences x suffix tokens)
   size_t pf_proj_cols;  // slices x columns per row of the prefill projection partials
   int rows_pad, nblk_fuse, nblk_agg, nchunk, max_work;
@@ -188,6 +190,11 @@ Layout make_layout(const pced_config& c) {
   L.pf_part_acc = take(PR * c.n_kv_heads * kPrefillParts * G * c.head_dim * 4);
   L.pf_part_ml = take(PR * c.n_kv_heads * kPrefillParts * G * 2 * 4);
   L.pf_proj = take(std::max(PR * max_cols, (size_t)kLmRowsPad * L.part_cols) * 4);
+  // staging of caches loaded from host memory: the longest sequence's K and V, at
+  // most kLoadStage (longer ones go in pieces), at least one page of one layer
+  const size_t page_bytes = (size_t)kPage * c.n_kv_heads * c.head_dim * es;
+  L.stage_bytes = align_up(2 * std::max(page_bytes, std::min(kLoadStage / 2, page_bytes * c.max_pages_per_seq * c.n_layers)));
+  L.load_stage = take(L.stage_bytes);
   L.total = o;
   return L;
 }
@@ -362,66 +369,44 @@ bool is_device_memory(const void* p) {
   return attr.type == hipMemoryTypeDevice || attr.type == hipMemoryTypeManaged || attr.isManaged;
 }
 
-// Host path of pced_load_caches: sequence s's cache, held in host memory as
-// [L][len][Hkv][D], re-laid on the host into the pool's tiles of each of its
-// pages (slots past len zero) and copied into the pool with one hipMemcpyAsync
-// per run of consecutive physical pages. The staging image is reused once the
-// copies out of it have completed (hence the stream synchronisations).
-struct HostLoader {
-  const pced_config& cfg;
-  hipStream_t st;
-  size_t es, tile_elems, page_bytes;  // page_bytes: all kv-heads of one page and layer
-  std::vector<char> img;
-  size_t used = 0;
-  HostLoader(const pced_config& c, hipStream_t s)
-      : cfg(c), st(s), es(c.dtype == PCED_BF16 ? 2 : 4), tile_elems((size_t)kPage * c.head_dim),
-        page_bytes((size_t)c.n_kv_heads * kPage * c.head_dim * (c.dtype == PCED_BF16 ? 2 : 4)) {}
-
-  pced_status flush() {
-    if (used) HIP_OK(hipStreamSynchronize(st));
-    used = 0;
+// Host path of pced_load_caches: a sequence's cache, held in host memory as
+// [L][len][Hkv][D], is copied as it is into the workspace's staging region and
+// moved from there into the pool's tiles by the load kernel. A piece is as many
+// whole layers as the region holds (K in its first half, V in its second), or,
+// where one layer does not fit, as many of its pages. Copies and kernels follow
+// each other on the stream, so the region is free again for the next piece.
+pced_status load_from_host(pced_ctx* c, LoadArgs a, int s, int len, const char* src_k, const char* src_v,
+                           hipStream_t st) {
+  const size_t row = (size_t)c->cfg.n_kv_heads * c->cfg.head_dim * esize_of(c->cfg);
+  const size_t half = c->lay.stage_bytes / 2;
+  char* stage = c->at<char>(c->lay.load_stage);
+  a.items = nullptr;
+  a.one_s = s;
+  a.one_k = stage;
+  a.one_v = stage + half;
+  // layers [l0, l0 + nl), tokens [t0, t0 + n) of each (all of them when nl > 1)
+  auto piece = [&](int l0, int nl, int t0, int n) -> pced_status {
+    const size_t off = ((size_t)l0 * len + t0) * row, bytes = (size_t)nl * n * row;
+    HIP_OK(hipMemcpyAsync(stage, src_k + off, bytes, hipMemcpyHostToDevice, st));
+    HIP_OK(hipMemcpyAsync(stage + half, src_v + off, bytes, hipMemcpyHostToDevice, st));
+    a.layer0 = l0;
+    a.n_layers = nl;
+    a.page0 = t0 / kPage;
+    a.one_len = n;
+    HIP_OK(launch_load(a, ceil_div(n, kPage), c->bf16, st));
     return PCED_OK;
+  };
+  const int L = c->cfg.n_layers, fit = (int)std::min<size_t>(L, half / (len * row));
+  pced_status r = PCED_OK;
+  if (fit >= 1) {
+    for (int l0 = 0; l0 < L && r == PCED_OK; l0 += fit) r = piece(l0, std::min(fit, L - l0), 0, len);
+    return r;
   }
-
-  // one (sequence, layer, K or V) image and its copies
-  pced_status put(const void* src, int len, int layer, const int32_t* pt, bool is_v, void* pool) {
-    const int D = cfg.head_dim, Hkv = cfg.n_kv_heads, np = ceil_div(len, kPage);
-    const size_t bytes = (size_t)np * page_bytes;
-    if (used + bytes > img.size()) {
-      pced_status r = flush();
-      if (r != PCED_OK) return r;
-      if (bytes > img.size()) img.resize(std::max(bytes, (size_t)64 << 20));
-    }
-    char* dst = img.data() + used;
-    const bool bf16 = cfg.dtype == PCED_BF16;
-    for (int p = 0; p < np; ++p)
-      for (int g = 0; g < Hkv; ++g) {
-        char* tile = dst + ((size_t)p * Hkv + g) * tile_elems * es;
-        for (int t = 0; t < kPage; ++t) {
-          const int tok = p * kPage + t;
-          const size_t row = (((size_t)layer * len + tok) * Hkv + g) * D;
-          for (int d = 0; d < D; ++d) {
-            if (bf16) {
-              const uint16_t v = tok < len ? ((const uint16_t*)src)[row + d] : 0;
-              ((uint16_t*)tile)[is_v ? vswz(t, d) : kswz(t, d)] = v;
-            } else {
-              ((float*)tile)[(size_t)t * D + d] = tok < len ? ((const float*)src)[row + d] : 0.f;
-            }
-          }
-        }
-      }
-    const size_t layer_off = (size_t)layer * cfg.max_pages * page_bytes;
-    for (int p0 = 0; p0 < np;) {
-      int p1 = p0 + 1;
-      while (p1 < np && pt[p1] == pt[p1 - 1] + 1) ++p1;
-      HIP_OK(hipMemcpyAsync((char*)pool + layer_off + (size_t)pt[p0] * page_bytes, dst + (size_t)p0 * page_bytes,
-                            (size_t)(p1 - p0) * page_bytes, hipMemcpyHostToDevice, st));
-      p0 = p1;
-    }
-    used += bytes;
-    return PCED_OK;
-  }
-};
+  const int step = (int)(half / (row * kPage)) * kPage;  // >= one page
+  for (int l = 0; l < L; ++l)
+    for (int t0 = 0; t0 < len && r == PCED_OK; t0 += step) r = piece(l, 1, t0, std::min(step, len - t0));
+  return r;
+}
 
 pced_status check_ctx(const pced_ctx* c, bool need_loaded) {
   if (!c) return fail(PCED_ERR_INVALID_ARG, "ctx is NULL");
@@ -1422,19 +1407,14 @@ pced_status pced_load_caches(pced_ctx* c, int32_t n_queries, const int32_t* n_ex
   la.max_pages = cfg.max_pages;
   la.maxpps = P;
   if (!items.empty()) HIP_OK(launch_load(la, (int)(items.size() / 2), c->bf16, st));
-  {
-    HostLoader hl(cfg, st);
-    for (long s = 0; s < S; ++s) {
-      if (!on_host[s]) continue;
-      for (int l = 0; l < cfg.n_layers; ++l) {
-        r = hl.put(src_k[s], cache_len[s], l, &pt[s * P], false, k_pool);
-        if (r == PCED_OK) r = hl.put(src_v[s], cache_len[s], l, &pt[s * P], true, v_pool);
-        if (r != PCED_OK) return r;
-      }
-    }
-    r = hl.flush();
+  bool any_host = false;
+  for (long s = 0; s < S; ++s) {
+    if (!on_host[s]) continue;
+    any_host = true;
+    r = load_from_host(c, la, (int)s, cache_len[s], (const char*)src_k[s], (const char*)src_v[s], st);
     if (r != PCED_OK) return r;
   }
+  if (any_host) HIP_OK(hipStreamSynchronize(st));  // the host buffers have been read
 
   c->kpool = k_pool;
   c->vpool = v_pool;

@@ -106,6 +106,13 @@ struct LoadArgs {
   void* kpool;
   void* vpool;
   int n_layers, n_kv_heads, head_dim, max_pages, maxpps;
+  // items null: n_items consecutive pages of sequence one_s from page0 on, into
+  // layers layer0 .. layer0 + n_layers - 1, from rows [n_layers][one_len][Hkv][D]
+  // at one_k / one_v that start at token 16 page0
+  int n_items;              // (set by launch_load)
+  int layer0, one_s, page0, one_len;
+  const void* one_k;
+  const void* one_v;
 };
 
 struct LmArgs {

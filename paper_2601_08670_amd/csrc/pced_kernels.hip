@@ -77,37 +77,132 @@ __global__ void k_zero_u32(uint32_t* p, size_t n) {
 
 // ------------------------------------------------------------- cache loading
 
-// One block per (sequence, logical page) item and layer: copies the page's
-// tokens of every kv-head from the contiguous [L][len][Hkv][D] source into the
-// pool tiles, zero-filling slots past the sequence's length.
+// 16 bytes at any element's address (a cache handed in or out may start anywhere)
+typedef unsigned u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
+
+// A page's tiles in 16-byte units: a V tile is D/4 "runs" of 8 units. Run r
+// holds tokens 4q .. 4q + 3 of dims d0 .. d0 + 7 and d0 + 16 .. d0 + 23, with
+// q = (r >> 1) & 3 and d0 = 32 (r >> 3) + 8 (r & 1); its unit i holds dims d0 + i
+// (first 8 bytes: the four tokens) and d0 + 16 + i. A K tile's unit n is dims
+// 32 (n >> 6) + 8 ((n >> 4) & 3) .. + 7 of token n & 15.
+//
+// A wave moves 64 runs of a page (8 KiB of K and of V) between the pool and
+// contiguous [token][Hkv][D] rows, all in 16-byte accesses: the pool side as
+// contiguous 1 KiB wave accesses, the row side as 16-byte pieces whose
+// neighbours the same wave touches next (lines are shared inside the wave only).
+// K units are whole on both sides. A V run is 4 x 2 row pieces, transposed in
+// registers, and reaches (or leaves) the pool-side order through the wave's own
+// 8 KiB of LDS, units XOR-swizzled against bank conflicts.
+struct RunPos {
+  int g, q, d0;
+};
+__device__ __forceinline__ RunPos run_pos(int run, int D) {
+  const int rpt = D / 4, r = run % rpt;
+  return RunPos{run / rpt, (r >> 1) & 3, 32 * (r >> 3) + 8 * (r & 1)};
+}
+struct UnitPos {
+  int g, t, d;
+};
+__device__ __forceinline__ UnitPos kunit_pos(int n, int D) {
+  const int upt = 2 * D, u = n % upt;
+  return UnitPos{n / upt, u & 15, 32 * (u >> 6) + 8 * ((u >> 4) & 3)};
+}
+// element e (of 8) of a 16-byte row piece
+__device__ __forceinline__ uint32_t el16(const u32x4& v, int e) { return (v[e >> 1] >> (16 * (e & 1))) & 0xFFFFu; }
+
+// This wave's LDS accesses so far are complete and ordered before the next ones
+// (other lanes' data is read next).
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Loading: one wave per (item, layer, 64 runs), items being (sequence, logical
+// page) pairs, or with a.items null consecutive pages of sequence a.one_s from
+// page a.page0 on, whose rows (all layers, a.one_len tokens per layer, from token
+// 16 page0) sit at a.one_k / a.one_v. Slots past the sequence's length are
+// zero-filled. Bound: HBM, every byte read and written once. 33 caches x 32
+// layers (5.4 GB in, 5.4 GB out): 2.06 ms, 5.2 TB/s (one thread per element, 2-byte
+// accesses: 4.1 ms).
 template <bool BF16>
 __global__ __launch_bounds__(256) void k_load(LoadArgs a) {
-  const int item = blockIdx.x, l = blockIdx.y;
-  const int s = a.items[2 * item], p = a.items[2 * item + 1];
+  __shared__ uint4 lds[BF16 ? 4 : 1][512];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int Hkv = a.n_kv_heads, D = a.head_dim;
+  const int units = Hkv * D * (BF16 ? 2 : 4);  // 16-byte units of a page
+  const int nb = (units + 511) / 512;
+  const int task = blockIdx.x * 4 + wave;
+  const int item = task / nb, batch = task - item * nb, l = blockIdx.y;
+  if (item >= a.n_items) return;
+  const int s = a.items ? a.items[2 * item] : a.one_s, p = a.items ? a.items[2 * item + 1] : a.page0 + item;
   const int len = a.len0[s];
   const int phys = a.page_table[(size_t)s * a.maxpps + p];
-  const int Hkv = a.n_kv_heads, D = a.head_dim;
-  const size_t tile = (size_t)kPage * D;
-  const size_t tile0 = ((size_t)l * a.max_pages + phys) * Hkv;
-  const int n = Hkv * kPage * D;
-  for (int idx = threadIdx.x; idx < n; idx += blockDim.x) {
-    const int g = idx / (kPage * D), rem = idx % (kPage * D);
-    const int t = rem / D, d = rem % D;
-    const int tok = p * kPage + t;
-    const size_t src = (((size_t)l * len + tok) * Hkv + g) * D + d;
-    const size_t base = (tile0 + g) * tile;
-    if (BF16) {
-      const uint16_t* sk = (const uint16_t*)a.src_k[s];
-      const uint16_t* sv = (const uint16_t*)a.src_v[s];
-      const uint16_t kv = tok < len ? sk[src] : 0, vv = tok < len ? sv[src] : 0;
-      ((uint16_t*)a.kpool)[base + kswz(t, d)] = kv;
-      ((uint16_t*)a.vpool)[base + vswz(t, d)] = vv;
-    } else {
-      const float* sk = (const float*)a.src_k[s];
-      const float* sv = (const float*)a.src_v[s];
-      ((float*)a.kpool)[base + (size_t)t * D + d] = tok < len ? sk[src] : 0.f;
-      ((float*)a.vpool)[base + (size_t)t * D + d] = tok < len ? sv[src] : 0.f;
+  const char* sk = a.items ? (const char*)a.src_k[s] : (const char*)a.one_k;
+  const char* sv = a.items ? (const char*)a.src_v[s] : (const char*)a.one_v;
+  // rows per layer of the source, and the page's first row there
+  const int ld = a.items ? len : a.one_len, row0 = kPage * (a.items ? p : item);
+  const int last = min(len - kPage * p, kPage) - 1;  // last token of the page
+  const size_t src0 = ((size_t)l * ld + row0) * Hkv * D;
+  const size_t dst0 = ((size_t)(a.layer0 + l) * a.max_pages + phys) * units + batch * 512 + lane;
+  uint4* dk = (uint4*)a.kpool + dst0;
+  uint4* dv = (uint4*)a.vpool + dst0;
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+  if constexpr (BF16) {
+    const uint16_t* k16 = (const uint16_t*)sk + src0;
+    const uint16_t* v16 = (const uint16_t*)sv + src0;
+    const int run = batch * 64 + lane;
+    const RunPos rp = run_pos(min(run, units / 8 - 1), D);
+    u32x4 kv[8], vv[4][2];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const uint16_t* row = v16 + ((size_t)min(4 * rp.q + t, last) * Hkv + rp.g) * D + rp.d0;
+      vv[t][0] = *(const u32x4_a2*)row;
+      vv[t][1] = *(const u32x4_a2*)(row + 16);
     }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const UnitPos u = kunit_pos(min(batch * 512 + 64 * i + lane, units - 1), D);
+      kv[i] = *(const u32x4_a2*)(k16 + ((size_t)min(u.t, last) * Hkv + u.g) * D + u.d);
+      if (u.t > last) kv[i] = zero;
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      if (4 * rp.q + t > last) vv[t][0] = vv[t][1] = zero;
+    uint4* mine = lds[wave];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      mine[lane * 8 + (i ^ (lane & 7))] =
+          make_uint4(el16(vv[0][0], i) | (el16(vv[1][0], i) << 16), el16(vv[2][0], i) | (el16(vv[3][0], i) << 16),
+                     el16(vv[0][1], i) | (el16(vv[1][1], i) << 16), el16(vv[2][1], i) | (el16(vv[3][1], i) << 16));
+    wave_lds_sync();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int n = 64 * i + lane;
+      if (batch * 512 + n < units) {
+        dk[64 * i] = __builtin_bit_cast(uint4, kv[i]);
+        dv[64 * i] = mine[(n >> 3) * 8 + ((n & 7) ^ ((n >> 3) & 7))];
+      }
+    }
+  } else {
+    // row-major tiles: 16-byte unit n of the page is kv-head n / (4 D), then the tile's units in order
+    const float* k32 = (const float*)sk + src0;
+    const float* v32 = (const float*)sv + src0;
+    u32x4 kv[8], vv[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int n = min(batch * 512 + 64 * i + lane, units - 1), u = n % (4 * D), t = u / (D / 4);
+      const size_t o = ((size_t)min(t, last) * Hkv + n / (4 * D)) * D + 4 * (u % (D / 4));
+      kv[i] = *(const u32x4_a2*)(k32 + o);
+      vv[i] = *(const u32x4_a2*)(v32 + o);
+      if (t > last) kv[i] = vv[i] = zero;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (batch * 512 + 64 * i + lane < units) {
+        dk[64 * i] = __builtin_bit_cast(uint4, kv[i]);
+        dv[64 * i] = __builtin_bit_cast(uint4, vv[i]);
+      }
   }
 }
 
@@ -2696,22 +2791,80 @@ __global__ __launch_bounds__(64) void k_prefill_meta(PrefillMetaArgs a) {
 }
 
 // Tokens [start, start + count) of one sequence and layer out of the paged pool
-// into contiguous [count][Hkv][D] rows: one block per (token, kv-head), one
-// thread per dimension.
-__global__ __launch_bounds__(128) void k_read_cache(ReadCacheArgs a) {
-  const int i = blockIdx.x, g = blockIdx.y, d = threadIdx.x;
-  if (d >= a.head_dim) return;
-  const int tok = a.start + i, D = a.head_dim;
-  const int phys = a.page_table[(size_t)a.seq * a.maxpps + tok / kPage];
-  const int t = tok % kPage;
-  const size_t base = (((size_t)a.layer * a.max_pages + phys) * a.n_kv_heads + g) * kPage * D;
-  const size_t o = ((size_t)i * a.n_kv_heads + g) * D + d;
-  if (a.bf16) {
-    ((uint16_t*)a.k_out)[o] = ((const uint16_t*)a.kpool)[base + kswz(t, d)];
-    ((uint16_t*)a.v_out)[o] = ((const uint16_t*)a.vpool)[base + vswz(t, d)];
+// into contiguous [count][Hkv][D] rows: k_load's movement the other way, one
+// wave per (page, 64 runs). 500 tokens of 8 kv-heads x 128 dims: 4.8 us (one
+// thread per element, 2-byte accesses: 5.3 us).
+template <bool BF16>
+__global__ __launch_bounds__(256) void k_read_cache(ReadCacheArgs a) {
+  __shared__ uint4 lds[BF16 ? 4 : 1][512];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int Hkv = a.n_kv_heads, D = a.head_dim;
+  const int units = Hkv * D * (BF16 ? 2 : 4);
+  const int nb = (units + 511) / 512;
+  const int task = blockIdx.x * 4 + wave;
+  const int p = a.start / kPage + task / nb, batch = task % nb;
+  if (kPage * p >= a.start + a.count) return;
+  const int phys = a.page_table[(size_t)a.seq * a.maxpps + p];
+  const size_t src0 = ((size_t)a.layer * a.max_pages + phys) * units;
+  const uint4* k16 = (const uint4*)a.kpool + src0;
+  const uint4* v16 = (const uint4*)a.vpool + src0;
+  // output row of page token t, or -1 outside the range
+  auto out_row = [&](int t) { const int i = kPage * p + t - a.start; return i >= 0 && i < a.count ? i : -1; };
+  if constexpr (BF16) {
+    uint4 kv[8], vv[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int n = min(batch * 512 + 64 * i + lane, units - 1);
+      vv[i] = v16[n];
+      kv[i] = k16[n];
+    }
+    uint4* mine = lds[wave];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int n = 64 * i + lane;
+      mine[(n >> 3) * 8 + ((n & 7) ^ ((n >> 3) & 7))] = vv[i];
+    }
+    wave_lds_sync();
+    const int run = batch * 64 + lane;
+    if (run < units / 8) {
+      const RunPos rp = run_pos(run, D);
+      u32x4 w[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) w[i] = __builtin_bit_cast(u32x4, mine[lane * 8 + (i ^ (lane & 7))]);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int r = out_row(4 * rp.q + t);
+        if (r < 0) continue;
+        uint16_t* o = (uint16_t*)a.v_out + ((size_t)r * Hkv + rp.g) * D + rp.d0;
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {  // dims d0 .. + 7, then d0 + 16 .. + 23
+          u32x4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            v[e] = el16(w[2 * e], 4 * hf + t) | (el16(w[2 * e + 1], 4 * hf + t) << 16);
+          *(u32x4_a2*)(o + 16 * hf) = v;
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int n = batch * 512 + 64 * i + lane;
+      const UnitPos u = kunit_pos(n, D);
+      const int r = out_row(u.t);
+      if (n < units && r >= 0)
+        *(u32x4_a2*)((uint16_t*)a.k_out + ((size_t)r * Hkv + u.g) * D + u.d) = __builtin_bit_cast(u32x4, kv[i]);
+    }
   } else {
-    ((float*)a.k_out)[o] = ((const float*)a.kpool)[base + (size_t)t * D + d];
-    ((float*)a.v_out)[o] = ((const float*)a.vpool)[base + (size_t)t * D + d];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int n = batch * 512 + 64 * i + lane, u = n % (4 * D);
+      const int r = out_row(u / (D / 4));
+      if (n < units && r >= 0) {
+        const size_t o = ((size_t)r * Hkv + n / (4 * D)) * D + 4 * (u % (D / 4));
+        *(u32x4_a2*)((float*)a.k_out + o) = __builtin_bit_cast(u32x4, k16[n]);
+        *(u32x4_a2*)((float*)a.v_out + o) = __builtin_bit_cast(u32x4, v16[n]);
+      }
+    }
   }
 }
 
@@ -2799,9 +2952,17 @@ hipError_t launch_zero_bytes(void* p, size_t nbytes, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_load(const LoadArgs& a, int n_items, bool bf16, hipStream_t st, const Timing* tm) {
+// blocks of 4 waves, one wave per 512 16-byte units (8 KiB) of each page's K and V
+static unsigned page_wave_blocks(int pages, int n_kv_heads, int head_dim, bool bf16) {
+  const int units = n_kv_heads * head_dim * (bf16 ? 2 : 4);
+  return (unsigned)(((size_t)pages * ((units + 511) / 512) + 3) / 4);
+}
+
+hipError_t launch_load(const LoadArgs& a0, int n_items, bool bf16, hipStream_t st, const Timing* tm) {
   if (n_items == 0) return hipSuccess;
-  dim3 grid(n_items, a.n_layers);
+  LoadArgs a = a0;
+  a.n_items = n_items;
+  const dim3 grid(page_wave_blocks(n_items, a.n_kv_heads, a.head_dim, bf16), a.n_layers);
   if (bf16) return go(k_load<true>, grid, dim3(256), 0, st, t0(tm), t1(tm), a);
   return go(k_load<false>, grid, dim3(256), 0, st, t0(tm), t1(tm), a);
 }
@@ -2959,7 +3120,10 @@ hipError_t launch_prefill_meta(const PrefillMetaArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_read_cache(const ReadCacheArgs& a, hipStream_t st) {
-  return go(k_read_cache, dim3(a.count, a.n_kv_heads), dim3(128), 0, st, nullptr, nullptr, a);
+  const int pages = (a.start + a.count - 1) / kPage - a.start / kPage + 1;
+  const dim3 grid(page_wave_blocks(pages, a.n_kv_heads, a.head_dim, a.bf16));
+  return a.bf16 ? go(k_read_cache<true>, grid, dim3(256), 0, st, nullptr, nullptr, a)
+                : go(k_read_cache<false>, grid, dim3(256), 0, st, nullptr, nullptr, a);
 }
 
 hipError_t launch_rho(const float* ss, int parts, int ld, int M, float inv_dim, float eps, float* rho,

@@ -89,3 +89,48 @@ def test_read_cache_and_load_errors():
     with pytest.raises(PcedError, match="both be device or both host"):
         load_workload(sess, wl, src=(bad_k, hv))
     assert sess.lengths() == before
+
+
+@pytest.mark.parametrize("dtype,hkv,d,layers,lens", [
+    ("bf16", 1, 64, 2, [1, 15, 16, 17]),        # less than one wave's share of a page
+    ("bf16", 5, 128, 3, [33, 47, 128]),         # 2.5 shares
+    ("bf16", 12, 64, 1, [16, 300]),
+    ("f32", 3, 4, 2, [5, 31, 32]),              # a page smaller than one share
+    ("f32", 5, 80, 2, [63, 100]),               # 3.1 shares, rows of 20 units
+    ("bf16", 40, 128, 1, [16, 3400]),           # host: one layer exceeds the staging region
+    ("bf16", 8, 128, 3, [16, 7700]),            # host: two layers fit, the third goes alone
+])
+def test_load_and_read_any_rows(dtype, hkv, d, layers, lens):
+    """Sources and outputs that start at any element, pages in shuffled order,
+    ranges that start and end inside a page; device and host sources alike."""
+    from paper_2601_08670_amd.session import PcedSession
+    need = [-(-n // 16) for n in lens]
+    td, el = (torch.int16, 2) if dtype == "bf16" else (torch.int32, 4)
+    g = torch.Generator().manual_seed(7 * hkv + d)
+
+    def source(n, host):
+        flat = torch.randint(-2 ** (8 * el - 1), 2 ** (8 * el - 1), (1 + layers * n * hkv * d,), dtype=td, generator=g)
+        flat = flat if host else flat.to(DEV)
+        return flat[1:].view(layers, n, hkv, d)  # one element off the allocation's start
+
+    order = np.random.RandomState(3).permutation(sum(need) + 2).astype(np.int32)
+    table, at = np.full((len(lens), max(need)), -1, np.int32), 0
+    for s, n in enumerate(need):
+        table[s, :n] = order[at:at + n]
+        at += n
+    kw = dict(n_layers=layers, n_q_heads=hkv * (1 if dtype == "f32" or hkv * d % 256 == 0 else 256 // d), n_kv_heads=hkv,
+              head_dim=d, vocab=64, dtype=dtype, max_queries=1, max_seqs=len(lens), max_pages=sum(need) + 2,
+              max_pages_per_seq=max(need), device=DEV, poison=True)
+    for host in (False, True):
+        sess = PcedSession(**kw)
+        k, v = [source(n, host) for n in lens], [source(n, host) for n in lens]
+        sess.load([len(lens) - 1], lens, k, v, [0.5] * (len(lens) - 1), page_table=table)
+        for s, n in enumerate(lens):
+            for start, count in ((0, n), (n // 3, n - n // 3), (n - 1, 1)):
+                for l in range(layers):
+                    out = torch.zeros((2, 2 + count * hkv * d), dtype=td, device=DEV)
+                    ko, vo = out[0, 1:-1], out[1, 1:-1]
+                    sess.ctx.pced_read_cache(s, l, start, count, ko.view(count, hkv, d), vo.view(count, hkv, d))
+                    assert torch.equal(ko.cpu(), k[s][l, start:].cpu().flatten()[:count * hkv * d]), (s, l, start, host)
+                    assert torch.equal(vo.cpu(), v[s][l, start:].cpu().flatten()[:count * hkv * d]), (s, l, start, host)
+                    assert not bool(out[:, 0].any()) and not bool(out[:, -1].any())
