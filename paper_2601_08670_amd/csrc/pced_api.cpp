@@ -84,6 +84,7 @@ struct Layout {
       rho, x_packed, fuse_part, lse_part, jsd_part, agg_lse, syn_q, syn_k, syn_v, dec_h, dec_a, dec_act, dec_ss, dec_rho, dec_part,
       rope, pf_len0, pf_pt, pf_tok, pf_glen0, pf_gpt, pf_nparts, pf_rho, pf_h, pf_a, pf_act, pf_ss, pf_q, pf_x, pf_part_acc, pf_part_ml, pf_proj,
       load_stage, stage_bytes, total;
+  int packed_rows;      // rows x_packed holds
   int pf_rows;          // rows of one prefill chunk (sequences x suffix tokens)
   size_t pf_proj_cols;  // slices x columns per row of the prefill projection partials
   int rows_pad, nblk_fuse, nblk_agg, nchunk, max_work;
@@ -139,7 +140,9 @@ Layout make_layout(const pced_config& c) {
   L.rho = take((size_t)L.rows_pad * 4);
   // the many-row LM head's operand-ordered copy of x (bf16, more than 48 rows)
   const bool wide = c.dtype == PCED_BF16 && c.max_seqs > kLmRowsPad;
-  L.x_packed = take(wide ? (size_t)kLmWideMaxRows * c.hidden * 2 : 0);
+  // (row groups of at most 288 rows; one group to spare for groups of whole queries)
+  L.packed_rows = !wide ? 0 : (ceil_div(c.max_seqs, kLmWideMaxRows) + (c.max_seqs > kLmWideMaxRows ? 1 : 0)) * kLmWideMaxRows;
+  L.x_packed = take((size_t)L.packed_rows * c.hidden * 2);
   // per-slice candidates: k_fuse uses 256-column slices, the fused LM-head epilogue 128-column ones
   L.fuse_part = take(B * (size_t)ceil_div(c.vocab, 128) * 5 * 4);
   L.lse_part = take(S * L.nchunk * 2 * 4);
@@ -218,6 +221,7 @@ struct pced_ctx {
   int B = 0, S = 0, NE = 0;
   std::vector<int32_t> n_experts, seq_off, exp_off, len, page_table;
   bool dynamic_beta = false, beta_frozen = false;
+  LmWidePlan head_groups;  // the fused LM head's row groups for more than 288 rows
   int t = 0;
   void* kpool = nullptr;
   void* vpool = nullptr;
@@ -539,6 +543,7 @@ pced_status run_lmhead(pced_ctx* c, const void* x, int M, const void* w, float* 
     a.prior = c->at<float>(c->lay.prior);
     a.exp_seq = c->at<int32_t>(c->lay.exp_seq);
     a.fuse_part = c->at<float>(c->lay.fuse_part);
+    a.wide_plan = &c->head_groups;
     a.n_queries = c->B;
     a.fuse_nblk = fuse_nblk;
   }
@@ -560,7 +565,7 @@ pced_status run_head(pced_ctx* c, const void* x, const float* rho_in, const void
   const pced_config& cfg = c->cfg;
   const bool refresh = c->dynamic_beta && !c->beta_frozen;
   const int fused_nblk = (c->bf16 && !refresh && !(extra && extra->logits) && cfg.aggregation == PCED_AGG_MAX)
-                             ? lmhead_fused_nblk(c->S, cfg.vocab) : 0;
+                             ? lmhead_fused_nblk(c->S, cfg.vocab, c->head_groups.groups > 0) : 0;
   pced_status r;
   if (fused_nblk > 0) {
     r = run_lmhead(c, x, c->S, w, nullptr, st, fused_nblk, rho_in);
@@ -1328,6 +1333,9 @@ pced_status pced_load_caches(pced_ctx* c, int32_t n_queries, const int32_t* n_ex
   }
   c->len.assign(cache_len, cache_len + S);
   c->page_table = pt;
+  c->head_groups = c->bf16 ? lmhead_wide_plan_queries(c->seq_off.data(), n_queries, cfg.vocab, cfg.hidden,
+                                                      c->lay.packed_rows)
+                           : LmWidePlan{};
 
   // metadata image, uploaded with one copy
   const Layout& L = c->lay;
@@ -1607,7 +1615,8 @@ pced_status pced_lmhead_noalloc(const pced_config* cfg, const void* x, int32_t n
   if (!x || !lm_head || !logits) return fail(PCED_ERR_INVALID_ARG, "NULL argument");
   if (n_rows < 1) return fail(PCED_ERR_INVALID_ARG, "n_rows %d < 1", n_rows);
   const size_t row_bytes = (size_t)cfg->hidden * esize_of(*cfg);
-  const int wide = cfg->dtype == PCED_BF16 ? lmhead_wide_tiles(n_rows, cfg->vocab, cfg->hidden) : 0;
+  LmWidePlan wide;
+  if (cfg->dtype == PCED_BF16) wide = lmhead_wide_plan(n_rows, cfg->vocab, cfg->hidden);
   LmArgs a{};
   a.w = lm_head;
   a.logits = logits;
@@ -1615,10 +1624,11 @@ pced_status pced_lmhead_noalloc(const pced_config* cfg, const void* x, int32_t n
   a.V = cfg->vocab;
   a.K = cfg->hidden;
   a.rms = cfg->norm == PCED_NORM_RMS;
-  if (wide) {
+  const size_t packed = lmhead_packed_rows(wide) * row_bytes;
+  // (several row groups whose packed x exceeds the scratch: the 48-row kernel below)
+  if (wide.groups == 1 || (wide.groups > 1 && packed + (size_t)n_rows * 4 <= kNoAllocScratchBytes)) {
     // the many-row kernel reads only rows < n_rows of x (through its packed
     // copy, which holds the padding): scratch = packed x, then the row scales
-    const size_t packed = (size_t)wide * 32 * row_bytes;
     if (packed + (size_t)n_rows * 4 > kNoAllocScratchBytes)
       return fail(PCED_ERR_CAPACITY, "%d rows need %zu bytes of scratch > the %zu available", n_rows,
                   packed + (size_t)n_rows * 4, kNoAllocScratchBytes);

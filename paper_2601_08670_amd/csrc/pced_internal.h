@@ -30,12 +30,11 @@ constexpr bool kProjKMajor = true;
 // Element offsets inside a bf16 KV tile (16 tokens x head_dim; see pced.h, pool
 // layout): every matrix-core operand of the attention is one contiguous 16-byte
 // load per lane. K token t, dim d: the A operand of the 16x16x32 q.k product;
-// V: the A operand of the 16x16x16 V^T.P^T product. Used by the kernels and by
-// the host-side loading of caches held in host memory.
-__host__ __device__ inline int kswz(int t, int d) {
+// V: the A operand of the 16x16x16 V^T.P^T product.
+__device__ inline int kswz(int t, int d) {
   return ((d >> 5) * 64 + t + 16 * ((d & 31) >> 3)) * 8 + (d & 7);
 }
-__host__ __device__ inline int vswz(int t, int d) {
+__device__ inline int vswz(int t, int d) {
   const int j = d >> 4;
   return (((j >> 1) * 64 + (d & 15) + 16 * (t >> 2)) * 2 + (j & 1)) * 4 + (t & 3);
 }
@@ -115,13 +114,28 @@ struct LoadArgs {
   const void* one_v;
 };
 
+constexpr int kLmWideMaxRows = 288;  // rows of the largest many-row tile count
+constexpr int kLmMaxGroups = 16;     // row groups of the fused many-row LM head
+
+// Row groups of the many-row LM head: every block takes the rows of one group
+// (at most 32 mth) against 256 vocabulary rows. groups 0: another kernel runs.
+struct LmWidePlan {
+  int groups = 0, rows = 0, mth = 0;
+  // with the fused epilogue and several groups: the groups' first rows and queries
+  int row0[kLmMaxGroups + 1] = {}, q0[kLmMaxGroups + 1] = {};
+};
+
 struct LmArgs {
   const void* x;            // [rows_pad][K] storage type, rows >= M zero
   const void* w;            // packed bf16 tiles (see pced_pack_lm_head) or f32 [V][K]
   float* logits;            // [M][V]
   int M, V, K, rms;
-  int row_groups;           // >= 1: work-groups per vocab chunk, each taking every R-th 48-row group
-  // Fused Eq. 2 epilogue (fuse_part != nullptr, M <= 288, one row group): the
+  int row_groups;           // >= 1: work-groups per vocab chunk: each takes every R-th 48-row group, or
+                            // (many-row kernel) one group of the plan
+  int grp_rows;             // rows of an unfused many-row group; the fused ones' first rows and queries:
+  int grp_row0[kLmMaxGroups + 1], grp_q0[kLmMaxGroups + 1];
+  const LmWidePlan* wide_plan;  // host: the fused launch's row groups when M > 288
+  // Fused Eq. 2 epilogue (fuse_part != nullptr; M <= 288 or wide_plan): the
   // logits are not written; every block writes its best two tokens per query
   // (over its vocabulary slice) to fuse_part [B][fuse_nblk][5] for k_fuse_final.
   const int32_t* query_seq0;// [B+1]
@@ -133,8 +147,8 @@ struct LmArgs {
   int n_queries, fuse_nblk;
   const float* rho_in;      // optional [M] row scales used instead of rms (bf16 kernels)
   float* rho_buf;           // optional [M] scratch: the many-row kernel computes the row scales there first
-  void* x_packed;           // optional scratch of ceil(M/16)*16*K bf16 (rounded up to the kernel's tile
-                            // count): the many-row kernel's operand-ordered copy of x
+  void* x_packed;           // optional scratch of lmhead_packed_rows(plan) rows of K bf16: the many-row
+                            // kernel's operand-ordered copy of x
   size_t w_vb, w_ks;        // packed W: 16-byte units from one vocab block / 64-wide k step to the next
                             // (set by launch_lmhead from kLmKMajor)
 };
@@ -302,12 +316,16 @@ hipError_t launch_beta_mean(const BetaArgs& a, int n_queries, hipStream_t st);
 hipError_t launch_agg(const AggArgs& a, int n_exp, int n_queries, hipStream_t st, const Timing* tm = nullptr);
 // the final per-query merge alone (after an LM head with the fused epilogue)
 hipError_t launch_fuse_final(const FuseArgs& a, int n_queries, hipStream_t st, const Timing* tm = nullptr);
-// vocabulary slices (blocks) of the fused LM-head epilogue for M rows, or 0 if M rows cannot be fused
-int lmhead_fused_nblk(int M, int V);
-// 32-row tiles of the many-row LM head for M rows of a bf16 LM head (its packed
-// x then holds that many tiles, zero past M), or 0 if another kernel runs
-int lmhead_wide_tiles(int M, int V, int K);
-constexpr int kLmWideMaxRows = 288;  // rows of the largest many-row tile count
+// vocabulary slices (blocks) of the fused LM-head epilogue for M rows, or 0 if M
+// rows cannot be fused (groups: a plan of query-aligned row groups is given)
+int lmhead_fused_nblk(int M, int V, bool groups = false);
+// Row groups of the many-row LM head for M rows of a bf16 LM head, or none if
+// another kernel runs; for the fused epilogue of more than 288 rows, groups of
+// whole queries (seq_off [n_queries + 1]: the queries' first rows) whose packed x
+// takes at most max_packed_rows rows, or none
+LmWidePlan lmhead_wide_plan(int M, int V, int K);
+LmWidePlan lmhead_wide_plan_queries(const int32_t* seq_off, int n_queries, int V, int K, int max_packed_rows);
+size_t lmhead_packed_rows(const LmWidePlan& p);  // rows of the plan's packed x (padded tiles included)
 hipError_t launch_synth(const SynthArgs& a, int n_seqs, hipStream_t st, const Timing* tm = nullptr);
 hipError_t launch_copy_rows(const void* src, void* dst, size_t nbytes, hipStream_t st);
 hipError_t launch_stream_read(const void* src, size_t nbytes, uint32_t* xor_out, int num_cus, hipStream_t st);

@@ -1589,27 +1589,39 @@ __device__ __forceinline__ void wait_vmcnt() {
 typedef __attribute__((address_space(3))) void lds_void;
 
 
-// The many-row LM head's B operands, laid out in advance: x [M][K] bf16
-// (row-major) into xp [K/64][MTP][2][64] 16-byte units, unit (ks, t, h, lane)
-// holding x[16t + lane%16][64ks + 16(lane/16) + 8h .. +7], so that each
-// (64-wide k step, 16-row tile, half) operand is one contiguous 1 KiB; rows
-// M .. 16 MTP - 1 are zero. Also rho[m] = 1/sqrt(mean(x[m]^2) + 1e-5) (or 1
-// without RMS) from the same reads. One wave per row, 16-byte loads.
-__global__ __launch_bounds__(256) void k_pack_x(const uint16_t* __restrict__ x, int M, int K, int MTP, int rms,
-                                                uint4* __restrict__ xp, float* __restrict__ rho) {
-  const int m = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (m >= 16 * MTP) return;
-  const int t = m >> 4, col = m & 15;
+// The rows of row group rg of the many-row LM head: [row0, row1).
+__device__ __forceinline__ int2 lm_group_rows(const LmArgs& a, int rg) {
+  if (a.fuse_part && a.row_groups > 1) return make_int2(a.grp_row0[rg], a.grp_row0[rg + 1]);
+  return make_int2(rg * a.grp_rows, min(rg * a.grp_rows + a.grp_rows, a.M));
+}
+
+// The many-row LM head's B operands, laid out in advance: the x rows of each row
+// group (x [M][K] bf16, row-major) into xp [group][K/64][MTP][2][64] 16-byte
+// units, unit (ks, t, h, lane) holding row 16t + lane%16 of the group, elements
+// 64ks + 16(lane/16) + 8h .. +7, so that each (64-wide k step, 16-row tile, half)
+// operand is one contiguous 1 KiB; rows past the group's last are zero. Also
+// rho[m] = 1/sqrt(mean(x[m]^2) + 1e-5) (or 1 without RMS) from the same reads.
+// One wave per row, 16-byte loads.
+__global__ __launch_bounds__(256) void k_pack_x(LmArgs a, int MTP) {
+  const int pm = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int rg = pm / (16 * MTP), lm = pm - rg * 16 * MTP;
+  if (rg >= a.row_groups) return;
+  const int2 rows = lm_group_rows(a, rg);
+  const int m = rows.x + lm, K = a.K;
+  const bool valid = m < rows.y;
+  const uint16_t* x = (const uint16_t*)a.x + (size_t)m * K;
+  uint4* xp = (uint4*)a.x_packed + (size_t)rg * (K / 64) * MTP * 128;
+  const int t = lm >> 4, col = lm & 15;
   float ss = 0.f;
   for (int k = 8 * lane; k < K; k += 512) {
-    const uint4 v = m < M ? *(const uint4*)(x + (size_t)m * K + k) : make_uint4(0u, 0u, 0u, 0u);
+    const uint4 v = valid ? *(const uint4*)(x + k) : make_uint4(0u, 0u, 0u, 0u);
     ss += sumsq8(as_bf16x8(v));
     const int ks = k >> 6, kk = k & 63, quad = kk >> 4, h = (kk >> 3) & 1;
     xp[(((size_t)ks * MTP + t) * 2 + h) * 64 + col + 16 * quad] = v;
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) ss += __shfl_xor(ss, o);
-  if (lane == 0 && m < M) rho[m] = rms ? 1.0f / sqrtf(ss / (float)K + 1e-5f) : 1.0f;
+  if (lane == 0 && valid) a.rho_buf[m] = a.rms ? 1.0f / sqrtf(ss / (float)K + 1e-5f) : 1.0f;
 }
 
 // Compile-time loop: f(integral_constant<int, i>) for i = 0 .. N-1, in order.
@@ -1643,7 +1655,7 @@ static_assert(lmhead_wide_wait(7, 3, 5, 2) == 20 && lmhead_wide_wait(3, 3, 5, 4)
                   lmhead_wide_wait(15, 7, 2, 2) == 38,
               "wait counts");
 
-// LM head for 49..288 rows with W read once: logits[m][v] = rho_m sum_k x[m][k] W[v][k]
+// LM head for 49 rows and more: logits[m][v] = rho_m sum_k x[m][k] W[v][k]
 // (x packed by k_pack_x, rho precomputed) on the matrix cores,
 // C^T[16 vocab x 16 rows] += W[16 x 32] X^T[32 x 16] (v_mfma_f32_16x16x32_bf16).
 // A block of 8 waves (two per SIMD) owns 256 vocabulary rows; wave w computes
@@ -1670,7 +1682,14 @@ static_assert(lmhead_wide_wait(7, 3, 5, 2) == 20 && lmhead_wide_wait(3, 3, 5, 4)
 // the slice argmax in the epilogue, in four passes of 64 columns through the
 // (then free) LDS stages, with the row scales, beta and prior by row and the
 // queries' first rows staged in LDS at the start.
-template <int MTH, int NS, bool FUSED>
+// GROUPS: more rows than one block holds (288) go in a.row_groups groups of
+// rows, of whole queries with the fused epilogue. Work-groups are dealt to the 8
+// XCDs round-robin, and the groups of one vocabulary chunk are consecutive
+// work-groups of the same XCD, so they stream the same W together and all but
+// the first take it from that XCD's L2 (plain loads). 364 rows x 128256 x 4096:
+// 410 us (0.93 PFLOP/s), with the token choice fused 436 us; in 48-row groups of
+// the few-row kernel 1046 us, and 45 us for the token choice after it.
+template <int MTH, int NS, bool FUSED, bool GROUPS>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_lmhead_wide_bf16(LmArgs a) {
   static_assert(NS == 4 || NS == 8, "x stages");
   constexpr int MTP = 2 * MTH;           // 16-row tiles of the packed x
@@ -1698,9 +1717,23 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15, quad = lane >> 4;
   const int K = a.K, KS = K / 64, H = 2 * KS;
-  const int M = a.M;
   const int nvb = (a.V + 15) / 16;
-  const int vb0 = blockIdx.x * 16 + 2 * wave;  // this wave's first 16-row vocab block (of 2)
+  int chunk = blockIdx.x, rg = 0, row0 = 0, M = a.M;  // the block's 256 vocabulary rows, its rows of x
+  int q0 = 0, nq = a.n_queries;                       // (fused) its queries
+  if constexpr (GROUPS) {
+    const int xcd = blockIdx.x % 8, i = blockIdx.x / 8;
+    chunk = xcd + 8 * (i / a.row_groups);
+    rg = i % a.row_groups;
+    if (16 * chunk >= nvb) return;  // (the grid is rounded up to whole XCD rounds)
+    const int2 rows = lm_group_rows(a, rg);
+    row0 = rows.x;
+    M = rows.y - rows.x;
+    if constexpr (FUSED) {
+      q0 = a.grp_q0[rg];
+      nq = a.grp_q0[rg + 1] - q0;
+    }
+  }
+  const int vb0 = chunk * 16 + 2 * wave;  // this wave's first 16-row vocab block (of 2)
   // buffer loads: a uniform descriptor per operand, one 32-bit vector offset per
   // lane, the step's advance in a scalar offset
   const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, 0x7FFFFFFF, 0x00020000);
@@ -1709,11 +1742,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   for (int vt = 0; vt < 2; ++vt) w_t[vt] = (uint32_t)min(vb0 + vt, nvb - 1) * (uint32_t)a.w_vb * 16u;
   const uint32_t w_ks = (uint32_t)a.w_ks * 16u;
   const uint32_t lane16 = 16u * lane;
-  const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void*)a.x, 0, 0x7FFFFFFF, 0x00020000);
   constexpr uint32_t x_ks = XU * 1024u;  // bytes of one 64-wide step of the packed x
-  // W is read once per launch: its loads carry the non-temporal hint (cache
-  // policy bit 1, "nt" on gfx950) so they stream through the caches
-  constexpr int kNt = 2;
+  const char* xg = (const char*)a.x_packed + (size_t)rg * KS * x_ks;
+  const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void*)xg, 0, 0x7FFFFFFF, 0x00020000);
+  // with one row group W is read once per launch: its loads carry the
+  // non-temporal hint (cache policy bit 1, "nt" on gfx950) so they stream
+  // through the caches
+  constexpr int kNt = GROUPS ? 0 : 2;
   u32x4 wr[WR][2];
   auto load_w = [&](auto slot_c, int h) __attribute__((always_inline)) {
     constexpr int SL = decltype(slot_c)::value;
@@ -1774,13 +1809,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   float e_rho = 0.f, e_beta = 0.f, e_prior = 0.f;
   int e_qs = 0, e_row = -1;
   if constexpr (FUSED) {
-    if (tid < M) e_rho = a.rho_in[tid];
-    if (tid < M - a.n_queries) {  // experts: every query has one amateur row
-      e_row = a.exp_seq[tid];
-      e_beta = a.beta[tid];
-      e_prior = a.prior[tid];
+    if (tid < M) e_rho = a.rho_in[row0 + tid];
+    if (tid < M - nq) {  // experts: every query has one amateur row, q0 of them before the group
+      const int e = row0 - q0 + tid;
+      e_row = a.exp_seq[e] - row0;
+      e_beta = a.beta[e];
+      e_prior = a.prior[e];
     }
-    if (tid <= a.n_queries) e_qs = a.query_seq0[tid];
+    if (tid <= nq) e_qs = a.query_seq0[q0 + tid] - row0;
   }
   // prologue: the loads of half steps -LEAD .. -1 in the loop's order (half step
   // h loads W(h + LEAD) and, at even h, x(h / 2 + XL); LEAD = 2 XL + 1)
@@ -1797,7 +1833,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       epi.beta_row[e_row] = e_beta;
       epi.prior_row[e_row] = e_prior;
     }
-    if (tid <= a.n_queries) epi.qs[tid] = e_qs;
+    if (tid <= nq) epi.qs[tid] = e_qs;
   }
   wait_vmcnt<WAITN>();
   __builtin_amdgcn_s_barrier();
@@ -1835,10 +1871,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       return base + (c & 15) * RSP;
     };
     int T = 512;
-    while (T > 2 && T * a.n_queries > 512) T >>= 1;
+    while (T > 2 && T * nq > 512) T >>= 1;
     const int es = T > 64 ? T / 64 : 1, cpl = T < 64 ? 64 / T : 1;
     const int qb = tid / T, ti = tid % T, sp = ti % es;
-    const bool active = qb < a.n_queries;
+    const bool active = qb < nq;
     const int s0 = active ? epi.qs[qb] : 0;
     const int N = active ? epi.qs[qb + 1] - s0 - 1 : 0;
     const int rb = (s0 + 1) & ~3, nb = ((s0 + N) >> 2) - (rb >> 2) + 1;  // 4-row groups holding the experts
@@ -1864,7 +1900,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int i = 0; i < cpl; ++i) {
           const int c = es > 1 ? ti / es : ti + T * i;
           const int wc = 2 * (c >> 4) + ((c >> 1) & 1);
-          const int v = blockIdx.x * 256 + 32 * wc + 16 * (c & 1) + 4 * ((c >> 2) & 3) + p;
+          const int v = chunk * 256 + 32 * wc + 16 * (c & 1) + 4 * ((c >> 2) & 3) + p;
           const float* cp = colp(c);
           float best = kNegInf;
           int bk = 0;
@@ -1901,10 +1937,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int w = 1; w < T / 64; ++w) cand = merge(cand, red[wave + w]);
     }
     if (ti == 0 && active) {
-      float* pp = a.fuse_part + ((size_t)qb * a.fuse_nblk + 2 * blockIdx.x) * 5;
+      float* pp = a.fuse_part + ((size_t)(q0 + qb) * a.fuse_nblk + 2 * chunk) * 5;
       pp[0] = cand.v1; pp[1] = __int_as_float(cand.i1); pp[2] = __int_as_float(cand.k1);
       pp[3] = cand.v2; pp[4] = __int_as_float(cand.i2);
-      if (2 * (int)blockIdx.x + 1 < a.fuse_nblk) {  // (the last block's second slot may not exist)
+      if (2 * chunk + 1 < a.fuse_nblk) {  // (the last block's second slot may not exist)
         pp[5] = kNegInf; pp[6] = __int_as_float(0x7FFFFFFF); pp[7] = __int_as_float(0);
         pp[8] = kNegInf; pp[9] = __int_as_float(0x7FFFFFFF);
       }
@@ -1915,12 +1951,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   for (int t = 0; t < MTP; ++t) {
     const int m = 16 * t + col;
     if (m >= M) continue;
-    const float rho = a.rho_in[m];
+    const float rho = a.rho_in[row0 + m];
 #pragma unroll
     for (int vt = 0; vt < 2; ++vt) {
       if (vb0 + vt >= nvb) continue;
       const int v = 16 * (vb0 + vt) + 4 * quad;
-      float* out = a.logits + (size_t)m * a.V + v;
+      float* out = a.logits + (size_t)(row0 + m) * a.V + v;
       const f32x4 cc = acc[vt][t];
       if (v + 3 < a.V && (a.V & 3) == 0) {
         *(float4*)out = make_float4(cc[0] * rho, cc[1] * rho, cc[2] * rho, cc[3] * rho);
@@ -3132,18 +3168,58 @@ hipError_t launch_rho(const float* ss, int parts, int ld, int M, float inv_dim, 
             rho);
 }
 
-int lmhead_wide_tiles(int M, int V, int K) {
-  if (M <= kLmRowsPad || M > kLmWideMaxRows || K % 256 != 0) return 0;
-  if ((size_t)((V + 15) / 16) * 16 * K * 2 >= 0x7FFFFFFFull) return 0;  // 32-bit buffer offsets into W
-  const int mt = (M + 15) / 16;
-  return mt <= 8 ? 4 : mt <= 12 ? 6 : 9;  // the instantiated tile counts per row half
+// rows per block as the instantiated tile counts (32-row steps) give them; one
+// row group's counts are coarser (W, not the products, paces it)
+static int wide_tiles_for(int rows, bool groups) {
+  const int mth = (rows + 31) / 32;
+  return groups ? std::max(mth, 5) : mth <= 4 ? 4 : mth <= 6 ? 6 : 9;
 }
 
-int lmhead_fused_nblk(int M, int V) {
+LmWidePlan lmhead_wide_plan(int M, int V, int K) {
+  LmWidePlan p;
+  if (M <= kLmRowsPad || K % 256 != 0) return p;
+  if ((size_t)((V + 15) / 16) * 16 * K * 2 >= 0x7FFFFFFFull) return p;  // 32-bit buffer offsets into W
+  p.groups = (M + kLmWideMaxRows - 1) / kLmWideMaxRows;
+  p.rows = ((M + 15) / 16 + p.groups - 1) / p.groups * 16;
+  p.mth = wide_tiles_for(p.rows, p.groups > 1);
+  return p;
+}
+
+LmWidePlan lmhead_wide_plan_queries(const int32_t* seq_off, int n_queries, int V, int K, int max_packed_rows) {
+  const int M = seq_off[n_queries];
+  LmWidePlan best;
+  if (lmhead_wide_plan(M, V, K).groups <= 1) return best;
+  // fewest products first: for each number of groups the smallest group size
+  // (in 32-row steps) that a fill in query order manages with
+  for (int rows = 160; rows <= kLmWideMaxRows; rows += 32) {
+    LmWidePlan p;
+    p.mth = rows / 32;
+    p.rows = rows;
+    bool ok = true;
+    for (int b = 0; b < n_queries && ok; ++b) {
+      const int n = seq_off[b + 1] - seq_off[b];
+      if (b == 0 || seq_off[b + 1] - p.row0[p.groups - 1] > rows) {
+        ok = n <= rows && p.groups < kLmMaxGroups;
+        if (!ok) break;
+        p.row0[p.groups] = seq_off[b];
+        p.q0[p.groups++] = b;
+      }
+    }
+    if (!ok || p.groups * 32 * p.mth > max_packed_rows) continue;
+    p.row0[p.groups] = M;
+    p.q0[p.groups] = n_queries;
+    if (best.groups == 0 || p.groups * p.mth < best.groups * best.mth) best = p;
+  }
+  return best;
+}
+
+int lmhead_fused_nblk(int M, int V, bool groups) {
   if (M <= kLmRowsPad) return (V + 255) / 256;         // 48-row kernel: 256 columns per block
-  if (M <= 32 * kLmRowsMTW) return (V + 127) / 128;    // many-row kernel: 128 columns per block
+  if (M <= 32 * kLmRowsMTW || groups) return (V + 127) / 128;  // many-row kernels: 128 columns per candidate
   return 0;
 }
+
+size_t lmhead_packed_rows(const LmWidePlan& p) { return (size_t)p.groups * 32 * p.mth; }
 
 hipError_t launch_lmhead(const LmArgs& a0, bool bf16, hipStream_t st, const Timing* tm) {
   LmArgs a = a0;
@@ -3152,27 +3228,39 @@ hipError_t launch_lmhead(const LmArgs& a0, bool bf16, hipStream_t st, const Timi
     a.w_vb = kLmKMajor ? 128 : (size_t)(a.K / 64) * 128;
     a.w_ks = kLmKMajor ? (size_t)nvb * 128 : 128;
     const bool fused = a.fuse_part != nullptr;
-    if (fused && lmhead_fused_nblk(a.M, a.V) == 0) return hipErrorInvalidValue;
-    const int mtk = lmhead_wide_tiles(a.M, a.V, a.K);
-    if (mtk > 0 && a.x_packed && a.rho_buf) {
-      // many rows: W streamed once for all of them; x packed into operand order
-      // (and the row scales) first
-      hipError_t e = go(k_pack_x, dim3((32 * mtk + 3) / 4), dim3(256), 0, st, t0(tm), nullptr, (const uint16_t*)a.x,
-                        a.M, a.K, 2 * mtk, a.rms, (uint4*)a.x_packed, a.rho_buf);
+    if (fused && lmhead_fused_nblk(a.M, a.V, a.wide_plan && a.wide_plan->groups > 0) == 0) return hipErrorInvalidValue;
+    LmWidePlan wp = lmhead_wide_plan(a.M, a.V, a.K);
+    if (fused && wp.groups > 1) wp = a.wide_plan ? *a.wide_plan : LmWidePlan{};
+    if (wp.groups > 0 && a.x_packed && a.rho_buf) {
+      // many rows: x packed into operand order (and the row scales) first
+      a.row_groups = wp.groups;
+      a.grp_rows = wp.rows;
+      for (int i = 0; i <= kLmMaxGroups; ++i) {
+        a.grp_row0[i] = wp.row0[i];
+        a.grp_q0[i] = wp.q0[i];
+      }
+      hipError_t e = go(k_pack_x, dim3(wp.groups * 8 * wp.mth), dim3(256), 0, st, t0(tm), nullptr, a, 2 * wp.mth);
       if (e != hipSuccess) return e;
       if (!a.rho_in) a.rho_in = a.rho_buf;
-      a.x = a.x_packed;
-      const dim3 g((nvb + 15) / 16), b(512);
+      const int chunks = (nvb + 15) / 16;
+      const dim3 g(wp.groups > 1 ? (chunks + 7) / 8 * 8 * wp.groups : chunks), b(512);
       // up to 128 rows the x stages are small enough for eight of them (and a
       // 16-slot W ring), when the hidden size is a multiple of 8 steps
-      const bool deep = mtk == 4 && a.K % 512 == 0;
-#define PCED_WIDE(MT, NS)                                                                                    \
-  return fused ? go(k_lmhead_wide_bf16<MT, NS, true>, g, b, 0, st, nullptr, t1(tm), a)                       \
-               : go(k_lmhead_wide_bf16<MT, NS, false>, g, b, 0, st, nullptr, t1(tm), a);
-      if (deep) PCED_WIDE(4, 8)
-      if (mtk == 4) PCED_WIDE(4, 4)
-      if (mtk == 6) PCED_WIDE(6, 4)
-      if (mtk == 9) PCED_WIDE(9, 4)
+      const bool deep = wp.mth == 4 && a.K % 512 == 0;
+#define PCED_WIDE(MT, NS, GR)                                                                                 \
+  return fused ? go(k_lmhead_wide_bf16<MT, NS, true, GR>, g, b, 0, st, nullptr, t1(tm), a)                    \
+               : go(k_lmhead_wide_bf16<MT, NS, false, GR>, g, b, 0, st, nullptr, t1(tm), a);
+      if (wp.groups > 1) {
+        if (wp.mth == 5) PCED_WIDE(5, 4, true)
+        if (wp.mth == 6) PCED_WIDE(6, 4, true)
+        if (wp.mth == 7) PCED_WIDE(7, 4, true)
+        if (wp.mth == 8) PCED_WIDE(8, 4, true)
+        PCED_WIDE(9, 4, true)
+      }
+      if (deep) PCED_WIDE(4, 8, false)
+      if (wp.mth == 4) PCED_WIDE(4, 4, false)
+      if (wp.mth == 6) PCED_WIDE(6, 4, false)
+      PCED_WIDE(9, 4, false)
 #undef PCED_WIDE
     }
     if (a.M > kLmRowsPad && a.M <= 32 * kLmRowsMTW) {  // many rows: W streamed once for all of them
