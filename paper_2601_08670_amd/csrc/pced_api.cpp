@@ -81,7 +81,7 @@ struct Layout {
   size_t len0, page_table, seq_query, query_seq0, query_exp0, exp_seq, exp_query, prior, logw, beta_fixed,
       load_items, src_k, src_v, meta_end;
   size_t chunk_info, seg, nparts, work_pages, prev_tok, beta, part_acc, part_ml, x, logits,
-      rho, x_packed, fuse_part, lse_part, jsd_part, agg_lse, syn_q, syn_k, syn_v, dec_h, dec_a, dec_act, dec_ss, dec_rho, dec_part,
+      rho, x_packed, fuse_part, lse_part, jsd_part, syn_q, syn_k, syn_v, dec_h, dec_a, dec_act, dec_ss, dec_rho, dec_part,
       rope, pf_len0, pf_pt, pf_tok, pf_glen0, pf_gpt, pf_nparts, pf_rho, pf_h, pf_a, pf_act, pf_ss, pf_q, pf_x, pf_part_acc, pf_part_ml, pf_proj,
       load_stage, stage_bytes, total;
   int packed_rows;      // rows x_packed holds
@@ -98,7 +98,7 @@ Layout make_layout(const pced_config& c) {
   const int G = c.n_q_heads / c.n_kv_heads;
   L.rows_pad = ceil_div(c.max_seqs, kLmRowsPad) * kLmRowsPad;
   L.nblk_fuse = ceil_div(c.vocab, 512);  // at most: the stand-alone fuse's slices are 512 or 1024 tokens
-  L.nblk_agg = ceil_div(c.vocab, kFuseBlock);
+  L.nblk_agg = ceil_div(c.vocab, kAggSlice);
   L.nchunk = ceil_div(c.vocab, kBetaChunk);
   // every attention chunk holds at least one page: chunks <= pages in use (a
   // prefill chunk's rows count their shared pages once per row)
@@ -147,7 +147,6 @@ Layout make_layout(const pced_config& c) {
   L.fuse_part = take(B * (size_t)ceil_div(c.vocab, 128) * 5 * 4);
   L.lse_part = take(S * L.nchunk * 2 * 4);
   L.jsd_part = take(S * L.nchunk * 4);
-  L.agg_lse = take(S * 4);
   L.syn_q = take(S * c.n_layers * c.n_q_heads * c.head_dim * es);
   L.syn_k = take(S * c.n_layers * c.n_kv_heads * c.head_dim * es);
   L.syn_v = take(S * c.n_layers * c.n_kv_heads * c.head_dim * es);
@@ -454,6 +453,9 @@ pced_status copy_beta_used(pced_ctx* c, const pced_step_out* extra, hipStream_t 
 pced_status run_fuse(pced_ctx* c, const float* logits, bool refresh_beta, int32_t* tokens_out,
                      int tok_stride, const pced_step_out* extra, hipStream_t st) {
   const pced_config& cfg = c->cfg;
+  FuseArgs f = fuse_args(c, logits, tokens_out, tok_stride, extra,
+                         cfg.aggregation != PCED_AGG_MAX ? c->lay.nblk_agg
+                                                         : ceil_div(cfg.vocab, fuse_slice(cfg.vocab, c->B, c->num_cus)));
   if (c->dynamic_beta && refresh_beta) {
     BetaArgs b{};
     b.logits = logits;
@@ -467,13 +469,18 @@ pced_status run_fuse(pced_ctx* c, const float* logits, bool refresh_beta, int32_
     b.nchunk = c->lay.nchunk;
     b.query_exp0 = c->at<int32_t>(c->lay.query_exp0);
     ProfScope ps(c, PCED_PROF_BETA, (double)(c->S + 2.0 * c->NE) * cfg.vocab * 4, 0);
-    HIP_OK(launch_beta(b, c->S, c->NE, st, ps.timing()));
+    // the launch that uses beta sums its partials itself, unless their mean over a query is wanted
+    // or a query has more experts than the fuse holds
+    const bool sums = cfg.beta_scalar || (cfg.aggregation == PCED_AGG_MAX && f.max_n > kBetaFoldMax);
+    HIP_OK(launch_beta(b, c->S, c->NE, sums, st, ps.timing()));
     if (cfg.beta_scalar) HIP_OK(launch_beta_mean(b, c->B, st));
+    if (!sums) {
+      f.jsd_part = b.jsd_part;
+      f.beta_out = b.beta;
+      f.nchunk = b.nchunk;
+    }
     c->beta_frozen = true;
   }
-  FuseArgs f = fuse_args(c, logits, tokens_out, tok_stride, extra,
-                         cfg.aggregation != PCED_AGG_MAX ? c->lay.nblk_agg
-                                                         : ceil_div(cfg.vocab, fuse_slice(cfg.vocab, c->B, c->num_cus)));
   if (cfg.aggregation != PCED_AGG_MAX) {
     AggArgs g{};
     g.logits = logits;
@@ -484,7 +491,8 @@ pced_status run_fuse(pced_ctx* c, const float* logits, bool refresh_beta, int32_
     g.beta = f.beta;
     g.logw = c->at<float>(c->lay.logw);
     g.lse_part = c->at<float>(c->lay.lse_part);
-    g.lse = c->at<float>(c->lay.agg_lse);
+    g.jsd_part = f.jsd_part;
+    g.beta_out = f.beta_out;
     g.part = f.part;
     g.V = cfg.vocab;
     g.nchunk = c->lay.nchunk;

@@ -12,6 +12,9 @@ constexpr int kMaxGroup = 16;      // q-heads per kv-head (MFMA N edge)
 constexpr int kFuseBlock = 256;    // threads of the fuse work-groups
 constexpr int kFuseInlineQueries = 32;  // queries whose row offsets the fuse gets in its kernel arguments
 constexpr int kBetaChunk = 4096;   // vocab entries per beta work-group
+constexpr int kBetaFoldMax = 1024; // experts of a query whose beta the fuse sums itself (LDS)
+constexpr int kAggSlice = 256;     // vocab entries per MoE / PoE work-group
+constexpr int kAggExperts = 256;   // experts whose coefficients it holds in LDS at a time
 constexpr int kLmRowsPad = 48;     // hidden-state rows are padded to a multiple of this
 constexpr int kLmRowsMTW = 9;      // many-row LM head: row tiles per wave (up to 32 * 9 = 288 rows at once)
 constexpr int kMaxSplitPages = 64; // pages per attention chunk (one page id per lane)
@@ -167,6 +170,11 @@ struct FuseArgs {
   float* top2;              // optional [B]
   int V, nblk, tok_stride;
   int max_n;                // most experts of any query (load batch of the stand-alone fuse)
+  // optional: beta is summed from the divergence's chunk partials [sum N][nchunk]
+  // (max_n <= kBetaFoldMax) and stored to beta_out
+  const float* jsd_part;
+  float* beta_out;
+  int nchunk;
   int32_t inl_seq0[kFuseInlineQueries + 1];  // query_seq0 / query_exp0 of the first queries
   int32_t inl_exp0[kFuseInlineQueries + 1];
 };
@@ -182,9 +190,10 @@ struct AggArgs {
   const int32_t* exp_query; // [sum N]
   const float* beta;        // [sum N]
   const float* logw;        // [sum N] log pi_k, pi_k = r_k^gamma / sum_j r_j^gamma within the query
+  const float* jsd_part;    // optional [sum N][nchunk]: beta is summed from these and stored to beta_out
+  float* beta_out;
   float* lse_part;          // [sum N][nchunk][2]
-  float* lse;               // [sum N]
-  float* part;              // [B][nblk][5] slice candidates for k_fuse_final
+  float* part;              // [B][nblk][5] slice candidates for k_fuse_final (kAggSlice tokens each)
   int V, nchunk, nblk, product;  // product: 0 = mixture (MoE), 1 = product (PoE)
 };
 
@@ -306,7 +315,8 @@ int attn_blocks_per_cu(int head_dim, bool bf16);  // resident one-wave blocks pe
 hipError_t launch_attn_combine(const AttnArgs& a, int head_dim, int max_splits, bool bf16, hipStream_t st, const Timing* tm = nullptr);
 hipError_t launch_pack_lm_head(const void* w, void* wp, int V, int K, bool bf16, hipStream_t st);
 hipError_t launch_lmhead(const LmArgs& a, bool bf16, hipStream_t st, const Timing* tm = nullptr);
-hipError_t launch_beta(const BetaArgs& a, int n_seqs, int n_exp, hipStream_t st, const Timing* tm = nullptr);
+// the divergence's chunk partials, and with `sums` beta itself
+hipError_t launch_beta(const BetaArgs& a, int n_seqs, int n_exp, bool sums, hipStream_t st, const Timing* tm = nullptr);
 // k_fuse (timed by tm) then the per-query merge k_fuse_final (timed by tm_merge)
 hipError_t launch_fuse(const FuseArgs& a, int n_queries, hipStream_t st, const Timing* tm = nullptr,
                        const Timing* tm_merge = nullptr);

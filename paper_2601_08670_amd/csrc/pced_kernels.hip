@@ -2107,10 +2107,33 @@ __device__ __forceinline__ Top2 wave_top2(Top2 c) {
   return c;
 }
 
-template <bool VEC, int NB, int SW>
+// beta_k of a query's N experts (at e0) from the divergence's chunk partials (see
+// k_beta_jsd), for every block that needs them: 8 lanes per expert, to LDS and,
+// with `out`, to the beta array. A launch of its own for these sums (k_beta_final)
+// takes 2.5 to 5 us, the reads here (4 KiB at 32 experts, from the L2) under 1 us.
+__device__ __forceinline__ void betas_from_parts(const float* jsd_part, int nchunk, int e0, int N, float* sb,
+                                                 float* out) {
+  const int sub = threadIdx.x & 7;
+  for (int k = threadIdx.x >> 3; k < N; k += 32) {
+    const float* p = jsd_part + (size_t)(e0 + k) * nchunk;
+    float t = 0.f;
+    for (int c = sub; c < nchunk; c += 8) t += p[c];
+#pragma unroll
+    for (int o = 4; o >= 1; o >>= 1) t += __shfl_xor(t, o);
+    if (sub == 0) {
+      sb[k] = t;
+      if (out) out[e0 + k] = t;
+    }
+  }
+  __syncthreads();
+}
+
+// BETA: beta comes from the divergence's chunk partials (the first step).
+template <bool VEC, int NB, int SW, bool BETA>
 __global__ __launch_bounds__(256) void k_fuse(FuseArgs a) {
 #pragma clang fp contract(off)
   constexpr int RI = SW / 256;  // 16-byte loads per lane and row
+  __shared__ float sbeta[BETA ? kBetaFoldMax : 1];
   __shared__ float sbest[4][SW];
   __shared__ int sk[4][SW];
   __shared__ Top2 swave[4];
@@ -2134,6 +2157,7 @@ __global__ __launch_bounds__(256) void k_fuse(FuseArgs a) {
   }
 #pragma unroll
   for (int u = 0; u < 4 * RI; ++u) { best[u] = kNegInf; bk[u] = 0; }
+  if constexpr (BETA) betas_from_parts(a.jsd_part, a.nchunk, e0, N, sbeta, blockIdx.x == 0 ? a.beta_out : nullptr);
   for (int kb = k_lo; kb <= k_hi; kb += NB) {
     float4 x[NB][RI];
     float cb[NB], cp[NB];
@@ -2145,9 +2169,9 @@ __global__ __launch_bounds__(256) void k_fuse(FuseArgs a) {
     }
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-      const int e = e0 + min(kb + j, k_hi) - 1;
-      cb[j] = a.beta[e];
-      cp[j] = a.prior[e];
+      const int k = min(kb + j, k_hi) - 1;
+      cb[j] = BETA ? sbeta[k] : a.beta[e0 + k];
+      cp[j] = a.prior[e0 + k];
     }
     __builtin_amdgcn_sched_barrier(0);  // all of the batch's loads go out before the arithmetic
 #pragma unroll
@@ -2374,21 +2398,50 @@ __global__ __launch_bounds__(64) void k_beta_mean(BetaArgs a) {
 
 // ------------------------------------------------ MoE / PoE aggregation
 
+// exp(x - m) for x <= m, also where both are the same infinity
+__device__ __forceinline__ float exp_rel(float x, float m) { return x == m ? 1.0f : expf(x - m); }
+
 // Per (expert, vocabulary chunk): max and sum of exp(c - max) of the contrastive
-// logits c = (1 + beta) s_k - beta s_0 (Eq. 2's order, no contraction).
+// logits c = (1 + beta) s_k - beta s_0 (Eq. 2's order, no contraction), the
+// block's values staying in registers between the two reductions. With
+// a.jsd_part beta comes from the divergence's chunk partials (the first step),
+// and the expert's first block stores it. 32 experts x 128256: 7.2 us (10.5 us with
+// two passes of 4-byte loads, and 2.5 us for the sum of the partials).
 __global__ __launch_bounds__(256) void k_agg_lse(AggArgs a) {
 #pragma clang fp contract(off)
+  constexpr int PER = kBetaChunk / 256;
   const int e = blockIdx.y, ch = blockIdx.x;
   const float* rk = a.logits + (size_t)a.exp_seq[e] * a.V;
   const float* r0 = a.logits + (size_t)a.query_seq0[a.exp_query[e]] * a.V;
-  const float beta = a.beta[e], coef = 1.0f + beta;
   const int v0 = ch * kBetaChunk, v1 = min(a.V, v0 + kBetaChunk);
-  auto cval = [&](int v) { const float t1 = coef * rk[v]; const float t2 = beta * r0[v]; return t1 - t2; };
+  float xk[PER], x0[PER];
+  beta_chunk_values(rk, a.V, v0, v1, xk);
+  beta_chunk_values(r0, a.V, v0, v1, x0);
+  float beta;
+  if (a.jsd_part) {
+    float t = 0.f;  // every wave the whole sum
+    for (int c = threadIdx.x & 63; c < a.nchunk; c += 64) t += a.jsd_part[(size_t)e * a.nchunk + c];
+    beta = wave_sum(t);
+    if (ch == 0 && threadIdx.x == 0) a.beta_out[e] = beta;
+  } else {
+    beta = a.beta[e];
+  }
+  const float coef = 1.0f + beta;
+  const bool vec = (a.V & 3) == 0;
+  auto valid = [&](int i) {
+    return v0 + (vec ? 4 * ((int)threadIdx.x + 256 * (i / 4)) : (int)threadIdx.x + 256 * i) < v1;
+  };
   float m = kNegInf;
-  for (int v = v0 + threadIdx.x; v < v1; v += blockDim.x) m = fmaxf(m, cval(v));
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const float t1 = coef * xk[i], t2 = beta * x0[i];
+    xk[i] = t1 - t2;
+    if (valid(i)) m = fmaxf(m, xk[i]);
+  }
   m = block_reduce_max(m);
   float sum = 0.f;
-  for (int v = v0 + threadIdx.x; v < v1; v += blockDim.x) sum += expf(cval(v) - m);
+#pragma unroll
+  for (int i = 0; i < PER; ++i) sum += valid(i) ? exp_rel(xk[i], m) : 0.f;
   sum = block_reduce_sum(sum);
   if (threadIdx.x == 0) {
     a.lse_part[((size_t)e * a.nchunk + ch) * 2] = m;
@@ -2396,58 +2449,135 @@ __global__ __launch_bounds__(256) void k_agg_lse(AggArgs a) {
   }
 }
 
-// lse_k from the chunk partials, in chunk order.
-__global__ __launch_bounds__(256) void k_agg_lse_final(AggArgs a, int n_exp) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n_exp) return;
-  const float* p = a.lse_part + (size_t)e * a.nchunk * 2;
+// lse_k of one expert from its chunk partials, by 8 lanes (each returns it).
+__device__ __forceinline__ float agg_row_lse(const AggArgs& a, int e) {
+  const float2* p = (const float2*)a.lse_part + (size_t)e * a.nchunk;
+  const int sub = threadIdx.x & 7;
   float m = kNegInf;
-  for (int c = 0; c < a.nchunk; ++c) m = fmaxf(m, p[2 * c]);
+  for (int c = sub; c < a.nchunk; c += 8) m = fmaxf(m, p[c].x);
+#pragma unroll
+  for (int o = 4; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
   float sum = 0.f;
-  for (int c = 0; c < a.nchunk; ++c) sum += p[2 * c + 1] * expf(p[2 * c] - m);
-  a.lse[e] = m + logf(sum);
+  for (int c = sub; c < a.nchunk; c += 8) sum += p[c].y * exp_rel(p[c].x, m);
+#pragma unroll
+  for (int o = 4; o >= 1; o >>= 1) sum += __shfl_xor(sum, o);
+  return m + logf(sum);
 }
 
-// One block per (query, 256-token slice): per token v the experts' weighted
+// Per (query, slice of kAggSlice = 256 tokens): per token v the experts' weighted
 // log-probabilities j_k = log pi_k + c_k(v) - lse_k, then
-//   MoE: log sum_k exp(j_k)  (running max and rescaled sum, expert order)
+//   MoE: log sum_k exp(j_k)  (running max and rescaled sum)
 //   PoE: sum_k pi_k (c_k(v) - lse_k)
 // and the expert with the largest j_k (lowest k on ties); the block's best two
-// tokens go to the same partial buffer k_fuse_final merges.
-__global__ __launch_bounds__(kFuseBlock) void k_agg(AggArgs a) {
+// tokens go to the same partial buffer k_fuse_final merges. As in k_fuse, the
+// four waves take a quarter of the experts each and a lane 4 tokens (one 16-byte
+// load per row, NB rows in flight); the sum is rescaled once per batch of rows,
+// and the waves' states meet in LDS. The experts' lse come from the chunk
+// partials in every block (8 KiB at 32 experts), kAggExperts of them at a time
+// in LDS. 32 experts x 128256: 12.5 us (one token per thread, row after row:
+// 17.2 us, and 7.8 us for a launch that finished lse).
+template <bool VEC>
+__global__ __launch_bounds__(256) void k_agg(AggArgs a) {
 #pragma clang fp contract(off)
-  const int b = blockIdx.y;
+  constexpr int NB = 8;
+  __shared__ float s_beta[kAggExperts], s_lse[kAggExperts], s_logw[kAggExperts];
+  __shared__ float sm[4][kAggSlice], ssum[4][kAggSlice], sj[4][kAggSlice];
+  __shared__ int sk[4][kAggSlice];
+  const int b = blockIdx.y, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int s0 = a.query_seq0[b];
   const int N = a.query_seq0[b + 1] - s0 - 1;
   const int e0 = a.query_exp0[b];
-  const int v = blockIdx.x * kFuseBlock + threadIdx.x;
-  Top2 c{kNegInf, 0x7FFFFFFF, 0, kNegInf, 0x7FFFFFFF};
-  if (v < a.V) {
-    const float sa = a.logits[(size_t)s0 * a.V + v];
-    float m = kNegInf, sum = 0.f, prod = 0.f, jbest = kNegInf;
-    int bk = 0;
-    for (int k = 1; k <= N; ++k) {
-      const int e = e0 + k - 1;
-      const float beta = a.beta[e], coef = 1.0f + beta;
-      const float t1 = coef * a.logits[(size_t)(s0 + k) * a.V + v];
-      const float t2 = beta * sa;
-      const float lp = (t1 - t2) - a.lse[e];
-      const float j = a.logw[e] + lp;
-      if (j > jbest) { jbest = j; bk = k; }
-      if (a.product) {
-        prod += expf(a.logw[e]) * lp;
-      } else if (j > m) {
-        sum = sum * expf(m - j) + 1.0f;
-        m = j;
-      } else {
-        sum += expf(j - m);
+  const int vb = blockIdx.x * kAggSlice;
+  const float* L0 = a.logits + (size_t)s0 * a.V;
+  const float4 sa4 = load_tok4<VEC>(L0, vb + 4 * lane, a.V);
+  const float sa[4] = {sa4.x, sa4.y, sa4.z, sa4.w};
+  // MoE: running max m and sum of exp(j - m); PoE: the weighted sum in `sum`
+  float m[4], sum[4], jb[4];
+  int bk[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) { m[c] = kNegInf; sum[c] = 0.f; jb[c] = kNegInf; bk[c] = 0; }
+  for (int g0 = 0; g0 < N; g0 += kAggExperts) {
+    const int n = min(N - g0, kAggExperts);  // experts g0 + 1 .. g0 + n
+    if (g0 > 0) __syncthreads();             // the previous group's have been read
+    for (int k = threadIdx.x >> 3; k < n; k += 32) {
+      const float lse = agg_row_lse(a, e0 + g0 + k);
+      if ((threadIdx.x & 7) == 0) {
+        s_lse[k] = lse;
+        s_beta[k] = a.beta[e0 + g0 + k];
+        s_logw[k] = a.logw[e0 + g0 + k];
       }
     }
-    c.v1 = a.product ? prod : m + logf(sum);
-    c.i1 = v;
-    c.k1 = bk;
+    __syncthreads();
+    const int per = (n + 3) / 4, lo = wave * per, hi = min(n, lo + per) - 1;  // (in the group)
+    for (int kb = lo; kb <= hi; kb += NB) {
+      float4 x[NB];
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+        x[j] = load_tok4<VEC>(L0 + (size_t)(1 + g0 + min(kb + j, hi)) * a.V, vb + 4 * lane, a.V);
+      __builtin_amdgcn_sched_barrier(0);  // all of the batch's loads go out before the arithmetic
+      float jv[NB][4], mb[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) mb[c] = m[c];
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const int k = min(kb + j, hi);
+        const bool ok = kb + j <= hi;
+        const float beta = s_beta[k], coef = 1.0f + beta, lse = s_lse[k], lw = s_logw[k];
+        const float pi = a.product ? expf(lw) : 0.f;
+        const float xs[4] = {x[j].x, x[j].y, x[j].z, x[j].w};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const float t1 = coef * xs[c], t2 = beta * sa[c];
+          const float lp = (t1 - t2) - lse;
+          jv[j][c] = lw + lp;
+          if (ok && jv[j][c] > jb[c]) { jb[c] = jv[j][c]; bk[c] = g0 + k + 1; }
+          if (ok) {
+            mb[c] = fmaxf(mb[c], jv[j][c]);
+            if (a.product) sum[c] += pi * lp;
+          }
+        }
+      }
+      if (!a.product) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          float t = sum[c] * exp_rel(m[c], mb[c]);
+#pragma unroll
+          for (int j = 0; j < NB; ++j) t += kb + j <= hi ? exp_rel(jv[j][c], mb[c]) : 0.f;
+          sum[c] = t;
+          m[c] = mb[c];
+        }
+      }
+    }
   }
-  c = block_top2<kFuseBlock / 64>(c);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    sm[wave][4 * lane + c] = m[c];
+    ssum[wave][4 * lane + c] = sum[c];
+    sj[wave][4 * lane + c] = jb[c];
+    sk[wave][4 * lane + c] = bk[c];
+  }
+  __syncthreads();
+  const int t = threadIdx.x, v = vb + t;
+  float mt = kNegInf, tot = 0.f, j = sj[0][t];
+  int k = sk[0][t];
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    mt = fmaxf(mt, sm[w][t]);
+    // (an expert of a later wave may have a lower number once a query has several groups of experts)
+    const float jw = sj[w][t];
+    const int kw = sk[w][t];
+    if (jw > j || (jw == j && kw < k)) { j = jw; k = kw; }
+  }
+#pragma unroll
+  for (int w = 0; w < 4; ++w) tot += a.product ? ssum[w][t] : ssum[w][t] * exp_rel(sm[w][t], mt);
+  Top2 c{kNegInf, 0x7FFFFFFF, 0, kNegInf, 0x7FFFFFFF};
+  if (v < a.V) {
+    c.v1 = a.product ? tot : mt + logf(tot);
+    c.i1 = v;
+    c.k1 = k;
+  }
+  c = block_top2<4>(c);
   if (threadIdx.x == 0) {
     float* p = a.part + ((size_t)b * a.nblk + blockIdx.x) * 5;
     p[0] = c.v1; p[1] = __int_as_float(c.i1); p[2] = __int_as_float(c.k1);
@@ -3298,11 +3428,11 @@ hipError_t launch_lmhead(const LmArgs& a0, bool bf16, hipStream_t st, const Timi
 #undef PCED_F32
 }
 
-hipError_t launch_beta(const BetaArgs& a, int n_seqs, int n_exp, hipStream_t st, const Timing* tm) {
+hipError_t launch_beta(const BetaArgs& a, int n_seqs, int n_exp, bool sums, hipStream_t st, const Timing* tm) {
   hipError_t e = go(k_beta_lse, dim3(a.nchunk, n_seqs), dim3(256), 0, st, t0(tm), nullptr, a);
   if (e != hipSuccess) return e;
-  e = go(k_beta_jsd, dim3(a.nchunk, n_exp), dim3(256), 0, st, nullptr, nullptr, a);
-  if (e != hipSuccess) return e;
+  e = go(k_beta_jsd, dim3(a.nchunk, n_exp), dim3(256), 0, st, nullptr, sums ? nullptr : t1(tm), a);
+  if (e != hipSuccess || !sums) return e;
   return go(k_beta_final, dim3(n_exp), dim3(64), 0, st, nullptr, t1(tm), a, n_exp);
 }
 
@@ -3311,22 +3441,29 @@ int fuse_slice(int V, int n_queries, int num_cus) {
   return (long)((V + 1023) / 1024) * n_queries >= num_cus ? 1024 : 512;
 }
 
-template <int SW>
+template <int SW, bool BETA>
 hipError_t launch_fuse_sw(const FuseArgs& a, dim3 g, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   const bool vec = a.V % 4 == 0 && a.V >= 4;
   // rows per load batch: a wave's quarter of the experts in one batch up to 16 or 32 experts
   if ((a.max_n + 3) / 4 <= 4)
-    return vec ? go(k_fuse<true, 4, SW>, g, dim3(256), 0, st, e0, e1, a)
-               : go(k_fuse<false, 4, SW>, g, dim3(256), 0, st, e0, e1, a);
-  return vec ? go(k_fuse<true, 8, SW>, g, dim3(256), 0, st, e0, e1, a)
-             : go(k_fuse<false, 8, SW>, g, dim3(256), 0, st, e0, e1, a);
+    return vec ? go(k_fuse<true, 4, SW, BETA>, g, dim3(256), 0, st, e0, e1, a)
+               : go(k_fuse<false, 4, SW, BETA>, g, dim3(256), 0, st, e0, e1, a);
+  return vec ? go(k_fuse<true, 8, SW, BETA>, g, dim3(256), 0, st, e0, e1, a)
+             : go(k_fuse<false, 8, SW, BETA>, g, dim3(256), 0, st, e0, e1, a);
 }
 
 hipError_t launch_fuse(const FuseArgs& a, int n_queries, hipStream_t st, const Timing* tm, const Timing* tm_merge) {
   // a.nblk: slices of fuse_slice() tokens
   const int sw = (a.V + a.nblk - 1) / a.nblk > 512 ? 1024 : 512;
   const dim3 g(a.nblk, n_queries);
-  hipError_t e = sw == 1024 ? launch_fuse_sw<1024>(a, g, st, t0(tm), t1(tm)) : launch_fuse_sw<512>(a, g, st, t0(tm), t1(tm));
+  if (a.jsd_part && a.max_n > kBetaFoldMax) return hipErrorInvalidValue;
+  hipError_t e;
+  if (a.jsd_part)
+    e = sw == 1024 ? launch_fuse_sw<1024, true>(a, g, st, t0(tm), t1(tm))
+                   : launch_fuse_sw<512, true>(a, g, st, t0(tm), t1(tm));
+  else
+    e = sw == 1024 ? launch_fuse_sw<1024, false>(a, g, st, t0(tm), t1(tm))
+                   : launch_fuse_sw<512, false>(a, g, st, t0(tm), t1(tm));
   if (e != hipSuccess) return e;
   return go(k_fuse_final, dim3(n_queries), dim3(kFuseBlock), 0, st, t0(tm_merge), t1(tm_merge), a);
 }
@@ -3338,9 +3475,9 @@ hipError_t launch_beta_mean(const BetaArgs& a, int n_queries, hipStream_t st) {
 hipError_t launch_agg(const AggArgs& a, int n_exp, int n_queries, hipStream_t st, const Timing* tm) {
   hipError_t e = go(k_agg_lse, dim3(a.nchunk, n_exp), dim3(256), 0, st, t0(tm), nullptr, a);
   if (e != hipSuccess) return e;
-  e = go(k_agg_lse_final, dim3((n_exp + 255) / 256), dim3(256), 0, st, nullptr, nullptr, a, n_exp);
-  if (e != hipSuccess) return e;
-  return go(k_agg, dim3(a.nblk, n_queries), dim3(kFuseBlock), 0, st, nullptr, t1(tm), a);
+  const dim3 g(a.nblk, n_queries);
+  return a.V % 4 == 0 ? go(k_agg<true>, g, dim3(256), 0, st, nullptr, t1(tm), a)
+                      : go(k_agg<false>, g, dim3(256), 0, st, nullptr, t1(tm), a);
 }
 
 hipError_t launch_fuse_final(const FuseArgs& a, int n_queries, hipStream_t st, const Timing* tm) {

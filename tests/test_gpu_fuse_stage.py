@@ -1,0 +1,100 @@
+"""The token choice over given logits (pced_fuse) at the edges of its slices and
+expert groups, against float64: max, mixture and product aggregation, with beta
+computed from the logits (and frozen, as a second call shows) or fixed."""
+import math
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+GAMMA = 2.5
+
+
+def _reference(s, n_exp, rel, beta, rule):
+    """Per query: beta, every token's score, every (expert, token) score, in 64 bits."""
+    out, row, e = [], 0, 0
+    for n in n_exp:
+        s0, sk = s[row], s[row + 1:row + 1 + n]
+        if beta is None:
+            p, q = sk.softmax(-1), s0.softmax(-1)
+            m = (p + q) / 2
+            b = 0.5 * (torch.xlogy(p, p / m) + torch.xlogy(q, q / m)).sum(-1) / math.log(2.0)
+        else:
+            b = torch.tensor(beta[e:e + n], dtype=torch.float64)
+        prior = GAMMA * torch.tensor(rel[e:e + n], dtype=torch.float32).double().log()
+        ck = (1 + b)[:, None] * sk - b[:, None] * s0
+        if rule == "max":
+            every = ck + prior[:, None]
+            score = every.max(0).values
+        else:
+            lw = prior - torch.logsumexp(prior, 0)
+            lp = ck - torch.logsumexp(ck, 1, keepdim=True)
+            every = lw[:, None] + lp
+            score = torch.logsumexp(every, 0) if rule == "moe" else (lw.exp()[:, None] * lp).sum(0)
+        out.append((b, score, every))
+        row, e = row + n + 1, e + n
+    return out
+
+
+@pytest.mark.parametrize("experts,vocab", [
+    ([1], 5), ([3, 1], 255), ([33], 4097), ([8, 31], 1026), ([32, 5, 64], 8192),
+    ([257], 260), ([600, 2], 515),     # more experts than one group
+    ([1100], 36),                      # more than the fuse sums beta for itself
+])
+@pytest.mark.parametrize("rule", ["max", "moe", "poe"])
+@pytest.mark.parametrize("fixed", [False, True])
+def test_fuse_stage(experts, vocab, rule, fixed):
+    from paper_2601_08670_amd.session import PcedSession
+    S, NE = sum(experts) + len(experts), sum(experts)
+    sess = PcedSession(n_layers=1, n_q_heads=4, n_kv_heads=1, head_dim=64, vocab=vocab, dtype="bf16",
+                       max_queries=len(experts), max_seqs=S, max_pages=S, max_pages_per_seq=1, device=DEV,
+                       aggregation=rule, poison=True)
+    r = np.random.RandomState(S + vocab)
+    rel, beta = r.uniform(0.05, 0.95, NE).tolist(), (r.uniform(0.1, 1.0, NE).astype(np.float32).tolist() if fixed else None)
+    cache = [torch.zeros(1, 1, 1, 64, dtype=torch.bfloat16, device=DEV)] * S
+    sess.load(experts, [1] * S, cache, cache, rel, gamma=GAMMA, beta=beta)
+    g = torch.Generator().manual_seed(S)
+    s = 2.0 * torch.randn(1, vocab, generator=g) + 0.8 * torch.randn(S, vocab, generator=g)
+    dev = s.to(DEV)
+    ref = _reference(s.double(), experts, rel, beta, rule)
+    # scores below 100 in size from fp32 operations on values of that size, and beta and the
+    # log-sum-exp (each within 1e-5 of 64 bits: up to `vocab` terms) times values below 20
+    tol = 100 * 2.0 ** -23 * 8 + 3e-4
+    for refresh in (1, 0):
+        tokens = torch.full((len(experts),), -1, dtype=torch.int32, device=DEV)
+        out = sess.out_buffers(("winner", "top1", "top2", "beta_used"))
+        sess.ctx.pced_fuse(dev, refresh, tokens, out)
+        e = 0
+        for b, (bk, score, every) in enumerate(ref):
+            n = experts[b]
+            assert torch.allclose(out["beta_used"][e:e + n].cpu().double(), bk, rtol=0, atol=1e-5)
+            two = score.topk(2).values
+            tok, win = int(tokens[b]), int(out["winner"][b])
+            assert abs(float(out["top1"][b]) - float(two[0])) < tol and abs(float(out["top2"][b]) - float(two[1])) < tol
+            assert float(score[tok]) > float(two[0]) - 2 * tol
+            assert 1 <= win <= n and float(every[win - 1, tok]) > float(every[:, tok].max()) - 2 * tol
+            e += n
+
+
+@pytest.mark.parametrize("rule", ["moe", "poe"])
+def test_masked_tokens(rule):
+    """-inf scores of single (expert, token) pairs leave every other token's result as it is."""
+    from paper_2601_08670_amd.session import PcedSession
+    n, vocab = 9, 700
+    sess = PcedSession(n_layers=1, n_q_heads=4, n_kv_heads=1, head_dim=64, vocab=vocab, dtype="bf16", max_queries=1,
+                       max_seqs=n + 1, max_pages=n + 1, max_pages_per_seq=1, device=DEV, aggregation=rule)
+    cache = [torch.zeros(1, 1, 1, 64, dtype=torch.bfloat16, device=DEV)] * (n + 1)
+    beta, rel = [0.5] * n, [0.1 * (i + 1) for i in range(n)]
+    sess.load([n], [1] * (n + 1), cache, cache, rel, gamma=GAMMA, beta=beta)
+    g = torch.Generator().manual_seed(1)
+    s = torch.randn(n + 1, vocab, generator=g)
+    s[3, 17], s[5, 400:500] = -math.inf, -math.inf
+    tokens, out = torch.empty(1, dtype=torch.int32, device=DEV), sess.out_buffers(("winner", "top1", "top2"))
+    sess.ctx.pced_fuse(s.to(DEV), 0, tokens, out)
+    (_, score, _), = _reference(s.double(), [n], rel, beta, rule)
+    two = score.topk(2)
+    assert int(tokens[0]) == int(two.indices[0])
+    assert abs(float(out["top1"][0]) - float(two.values[0])) < 1e-4
+    assert abs(float(out["top2"][0]) - float(two.values[1])) < 1e-4
