@@ -966,75 +966,139 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-// fp32 caches (small/validation shapes): one wave per (chunk, kv-head) of the
-// balanced plan, lanes over head dims (D <= 128), one token at a time, per-head
-// online softmax in base 2; the chunk's segments one after another.
+// fp32 caches: one wave per (chunk, kv-head) of the balanced plan, a page at a
+// time on the fp32 matrix cores, the q-heads in their N dimension:
+//   S^T[16 tok x 16 heads] += K[16 x 4] Q^T[4 x 16]     (v_mfma_f32_16x16x4_f32)
+//   O^T[16 dims x 16 heads] += V^T[16 x 4] P^T[4 x 16]
+// Lane (col, quad) loads 4 consecutive dims 16u + 4 quad of K row `col` and of q
+// head `col`; product e of unit u contracts element e of every quad. The S^T
+// accumulator (head col, tokens 4 quad + r) is the B operand of the second
+// product when product r contracts the tokens 4 quad + r; its A operand is
+// element e of the lane's 4 dims 64j + 4 col .. + 3 of V row 4 quad + r, so that
+// accumulator (j, e) holds dims 64j + 4c + e for c = 4 quad + rr. Online softmax
+// in base 2, the reference moved at every page. Bound: at small shapes one
+// memory round trip per page, so the next page's loads are issued before a
+// page's products, and page ids come from the plan. NJ: 64-dim blocks of D <= 128.
+// 5 caches of 128 tokens, 2 kv-heads x 64 dims: 4.6 us (one token at a time with
+// a wave-wide sum per head and token: 18.7 us).
+template <int NJ>
 __global__ __launch_bounds__(64) void k_attn_f32(AttnArgs a, int D) {
-  const int lane = threadIdx.x;
+  constexpr int NU = 4 * NJ;  // 16-dim units of a row, at most
+  const int lane = threadIdx.x, col = lane & 15, quad = lane >> 4;
   const int G = a.group, Hkv = a.n_kv_heads;
   const int c = blockIdx.x / Hkv, g = blockIdx.x % Hkv;
-  const int nseg = a.chunk_info[c].x;
-  const bool has0 = lane < D, has1 = lane + 64 < D;
-  const size_t tile = (size_t)kPage * D;
+  const int2 ci = a.chunk_info[c];
+  const int nseg = ci.x, np = ci.y;
+  const int my_pid = a.work_pages[(size_t)c * kMaxSplitPages + lane];
+  const int4* sd = a.seg + (size_t)c * kMaxSeg * 2;
+  const int4 d0 = sd[2 * min(lane, kMaxSeg - 1)];
+  const int4 d1 = sd[2 * min(lane, kMaxSeg - 1) + 1];
   const float* kp = (const float*)a.kpool;
   const float* vp = (const float*)a.vpool;
-  const size_t lay = (size_t)a.layer * a.max_pages * Hkv + g;
+  const size_t lay = (size_t)a.layer * a.max_pages * Hkv + g, tile = (size_t)kPage * D;
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  struct Page {
+    f32x4 k[NU], v[4][NJ];
+  };
+  // dims past D read the row's first (in bounds) and count as zero
+  auto load_page = [&](int i, Page& P) __attribute__((always_inline)) {
+    const size_t t0 = (lay + (size_t)__builtin_amdgcn_readlane(my_pid, min(i, np - 1)) * Hkv) * tile;
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int d = 16 * u + 4 * quad;
+      P.k[u] = *(const f32x4*)(kp + t0 + (size_t)col * D + (d < D ? d : 0));
+      if (d >= D) P.k[u] = zero;
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int d = 64 * j + 4 * col;
+        P.v[r][j] = *(const f32x4*)(vp + t0 + (size_t)(4 * quad + r) * D + (d < D ? d : 0));
+      }
+  };
+  Page cur, nxt;
+  load_page(0, cur);
   for (int k = 0; k < nseg; ++k) {
-    const int4 d0 = a.seg[((size_t)c * kMaxSeg + k) * 2], d1 = a.seg[((size_t)c * kMaxSeg + k) * 2 + 1];
-    const int s = d0.x, tok_end = d0.w;
-    const float* q = (const float*)a.q + (((size_t)s * a.n_layers + a.layer) * a.n_q_heads + (size_t)g * G) * D;
-    float qv[kMaxGroup][2], m[kMaxGroup], l[kMaxGroup], acc[kMaxGroup][2];
+    const int s = __builtin_amdgcn_readlane(d0.x, k), i0 = __builtin_amdgcn_readlane(d0.y, k);
+    const int poff = __builtin_amdgcn_readlane(d0.z, k), end = __builtin_amdgcn_readlane(d0.w, k);
+    const int part = __builtin_amdgcn_readlane(d1.x, k), parts = __builtin_amdgcn_readlane(d1.y, k);
+    const int i1 = k + 1 < nseg ? __builtin_amdgcn_readlane(d0.y, k + 1) : np;
+    const float* q = (const float*)a.q +
+                     (((size_t)s * a.n_layers + a.layer) * a.n_q_heads + (size_t)g * G + min(col, G - 1)) * D;
+    f32x4 qv[NU], acc[NJ][4];
 #pragma unroll
-    for (int h = 0; h < kMaxGroup; ++h) {
-      qv[h][0] = (h < G && has0) ? q[h * D + lane] : 0.f;
-      qv[h][1] = (h < G && has1) ? q[h * D + lane + 64] : 0.f;
-      m[h] = kNegInf; l[h] = 0.f; acc[h][0] = 0.f; acc[h][1] = 0.f;
+    for (int u = 0; u < NU; ++u) {
+      const int d = 16 * u + 4 * quad;
+      qv[u] = *(const f32x4*)(q + (d < D ? d : 0));
+      if (d >= D) qv[u] = zero;
     }
-    const int32_t* pt = a.page_table + (size_t)s * a.maxpps;
-    for (int tok = (d0.y + d0.z) * kPage; tok < tok_end; ++tok) {
-      const size_t base = (lay + (size_t)pt[tok / kPage] * Hkv) * tile + (size_t)(tok % kPage) * D;
-      const float k0 = has0 ? kp[base + lane] : 0.f, k1 = has1 ? kp[base + lane + 64] : 0.f;
-      const float v0 = has0 ? vp[base + lane] : 0.f, v1 = has1 ? vp[base + lane + 64] : 0.f;
 #pragma unroll
-      for (int h = 0; h < kMaxGroup; ++h) {
-        if (h >= G) continue;  // (G is uniform: the rest are skipped too)
-        const float z = wave_sum(qv[h][0] * k0 + qv[h][1] * k1) * a.scale_log2;
-        const float mn = fmaxf(m[h], z);
-        const float al = exp2f(m[h] - mn), pz = exp2f(z - mn);
-        l[h] = l[h] * al + pz;
-        acc[h][0] = acc[h][0] * al + pz * v0;
-        acc[h][1] = acc[h][1] * al + pz * v1;
-        m[h] = mn;
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[j][e] = zero;
+    float m = kNegInf, l = 0.f;
+    for (int i = i0; i < i1; ++i) {
+      load_page(i + 1, nxt);
+      f32x4 sc = zero;
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          sc = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.k[u][e], qv[u][e], sc, 0, 0, 0);
+      const int tb = (i + poff) * kPage + 4 * quad;
+      float z[4], mx = kNegInf;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        z[r] = tb + r < end ? sc[r] * a.scale_log2 : kNegInf;
+        mx = fmaxf(mx, z[r]);
       }
-    }
-    if (d1.y == 1) {  // the sequence lies in this chunk alone: final output
+      mx = fmaxf(mx, __shfl_xor(mx, 16));
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      const float mn = fmaxf(m, mx), al = exp2f(m - mn);
+      l *= al;
+      m = mn;
 #pragma unroll
-      for (int h = 0; h < kMaxGroup; ++h) {
-        if (h >= G) continue;  // (G is uniform: the rest are skipped too)
-        const float inv = 1.0f / l[h];
-        const int head = g * G + h;
-        const size_t xo = (size_t)s * a.n_q_heads * D + (size_t)head * D;
-        const size_t ao = (((size_t)s * a.n_layers + a.layer) * a.n_q_heads + head) * D;
-        for (int cc = 0; cc < 2; ++cc) {
-          const int d = lane + 64 * cc;
-          if (d >= D) break;
-          const float o = acc[h][cc] * inv;
-          ((float*)a.x_out)[xo + d] = o;
-          if (a.attn_out) a.attn_out[ao + d] = o;
-          if (a.is_last_layer && a.hidden_out) a.hidden_out[xo + d] = o;
+      for (int r = 0; r < 4; ++r) {
+        z[r] = exp2f(z[r] - mn);
+        l += z[r];
+      }
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[j][e] *= al;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const bool live = tb + r < end;  // (slots past the end may hold anything: 0 x NaN is NaN)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            acc[j][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(live && 64 * j + 4 * col < D ? cur.v[r][j][e] : 0.f, z[r],
+                                                             acc[j][e], 0, 0, 0);
+      }
+      cur = nxt;
+    }
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    if (col < G) {
+      const size_t w = ((size_t)(s * Hkv + g) * a.split_stride + part) * G + col;
+      const float inv = 1.0f / l;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) {
+          const int d = 64 * j + 16 * quad + 4 * rr;
+          if (d >= D) continue;
+          const float4 o = make_float4(acc[j][0][rr], acc[j][1][rr], acc[j][2][rr], acc[j][3][rr]);
+          if (parts == 1)  // the sequence lies in this chunk alone: final output
+            write_o4<false>(a, s, g * G + col, d, D, make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv));
+          else
+            *(float4*)(a.part_acc + w * D + d) = o;
         }
-      }
-      continue;
-    }
-    const size_t w = (size_t)(s * Hkv + g) * a.split_stride + d1.x;
-#pragma unroll
-    for (int h = 0; h < kMaxGroup; ++h) {
-      if (h >= G) continue;
-      if (has0) a.part_acc[(w * G + h) * D + lane] = acc[h][0];
-      if (has1) a.part_acc[(w * G + h) * D + lane + 64] = acc[h][1];
-      if (lane == 0) {
-        a.part_ml[(w * G + h) * 2] = m[h];
-        a.part_ml[(w * G + h) * 2 + 1] = l[h];
+      if (parts > 1 && quad == 0) {
+        a.part_ml[w * 2] = m;
+        a.part_ml[w * 2 + 1] = l;
       }
     }
   }
@@ -3153,7 +3217,8 @@ hipError_t launch_attn(const AttnArgs& a, int n_blocks, int head_dim, bool bf16,
                : go(k_attn_bf16<64, 4, false>, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a);
     return hipErrorInvalidValue;
   }
-  return go(k_attn_f32, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a, head_dim);
+  return head_dim <= 64 ? go(k_attn_f32<1>, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a, head_dim)
+                        : go(k_attn_f32<2>, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a, head_dim);
 }
 
 int attn_blocks_per_cu(int head_dim, bool bf16) {
@@ -3161,7 +3226,8 @@ int attn_blocks_per_cu(int head_dim, bool bf16) {
   hipError_t e;
   if (bf16 && head_dim == 128) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_attn_bf16<128, 3, true>, 64, 0);
   else if (bf16) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_attn_bf16<64, 4, true>, 64, 0);
-  else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_attn_f32, 64, 0);
+  else if (head_dim <= 64) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_attn_f32<1>, 64, 0);
+  else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_attn_f32<2>, 64, 0);
   return (e == hipSuccess && n > 0) ? n : 8;
 }
 

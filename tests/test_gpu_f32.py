@@ -32,3 +32,39 @@ def test_lmhead_f32(rows, vocab, hq, d, norm):
     bound = (2 * K + 8) * 2.0 ** -24 * (x64.abs() @ w64.abs().T) * rho
     err = (out.cpu().double() - (x64 @ w64.T) * rho).abs()
     assert np.isfinite(out.cpu().numpy()).all() and bool((err <= bound).all()), float((err / bound).max())
+
+
+@pytest.mark.parametrize("hq,hkv,d,lens,chunks", [
+    (1, 1, 4, [1, 16], 0), (3, 3, 12, [15, 17], 0), (16, 1, 32, [40, 100], 0), (7, 1, 36, [31, 64], 0),
+    (4, 2, 64, [128, 250, 5], 0), (5, 5, 80, [33, 90], 3), (8, 4, 100, [200, 1], 1), (16, 4, 128, [16, 700], 2),
+])
+def test_attention_f32(hq, hkv, d, lens, chunks):
+    """Two steps over caches whose reserved slots hold NaN; several pages and sequences per chunk, and split ones."""
+    from paper_2601_08670_amd.session import PcedSession
+    S, L, G = len(lens), 2, hq // hkv
+    need = [-(-(n + 2) // 16) for n in lens]
+    g = torch.Generator().manual_seed(hq * 100 + d)
+    rnd = lambda *shape: torch.randn(*shape, generator=g)  # noqa: E731
+    k, v = [rnd(L, n, hkv, d) for n in lens], [rnd(L, n, hkv, d) for n in lens]
+    sess = PcedSession(n_layers=L, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, vocab=33, dtype="f32", max_queries=1,
+                       max_seqs=S, max_pages=sum(need), max_pages_per_seq=max(need), device=DEV, poison=True,
+                       max_attn_chunks=chunks)
+    sess.load([S - 1], lens, [t.to(DEV) for t in k], [t.to(DEV) for t in v], [0.5] * (S - 1), reserve_tokens=2)
+    w = sess.pack_lm_head(rnd(33, hq * d).to(DEV))
+    eps = 2.0 ** -24
+    for _ in range(2):
+        q, kn, vn = rnd(S, L, hq, d), rnd(S, L, hkv, d), rnd(S, L, hkv, d)
+        got = sess.step(q.to(DEV), kn.to(DEV), vn.to(DEV), w, want=("attn_out", "hidden"))
+        out = got["attn_out"].cpu().double()
+        for s in range(S):
+            k[s] = torch.cat([k[s], kn[s][:, None]], 1)
+            v[s] = torch.cat([v[s], vn[s][:, None]], 1)
+            T = k[s].shape[1]
+            kk, vv = (t[s].double().repeat_interleave(G, 2) for t in (k, v))  # [L][T][hq][d]
+            z = torch.einsum("lhd,lthd->lht", q[s].double(), kk) / d ** 0.5
+            ref = torch.einsum("lht,lthd->lhd", z.softmax(-1), vv)
+            # scores: d products and their scaling; weights: the score's error, exp2, sums over T terms
+            dz = (d + 8) * eps * torch.einsum("lhd,lthd->lht", q[s].double().abs(), kk.abs()).max().item() / d ** 0.5
+            bound = 2 * (2 * dz + (T + 32) * eps) * vv.abs().max().item()
+            assert (out[s] - ref).abs().max().item() <= bound, (s, T)
+        assert torch.equal(got["hidden"].view(S, hq, d), got["attn_out"][:, -1])
