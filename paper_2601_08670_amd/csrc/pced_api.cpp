@@ -87,6 +87,7 @@ struct Layout {
   int packed_rows;      // rows x_packed holds
   int pf_rows;          // rows of one prefill chunk (sequences x suffix tokens)
   size_t pf_proj_cols;  // slices x columns per row of the prefill projection partials
+  size_t pf_proj_elems; // floats of that buffer
   int rows_pad, nblk_fuse, nblk_agg, nchunk, max_work;
   size_t part_slots;
   size_t part_cols;  // slices x columns one row of the projection partial buffer holds
@@ -171,7 +172,7 @@ Layout make_layout(const pced_config& c) {
   L.pf_rows = dec ? (int)ceil_div(std::max(c.max_seqs, kPrefillRows), 16) * 16 : 0;
   const size_t PR = L.pf_rows;
   // projection products of a chunk: one slice of up to max_cols columns for
-  // more than 48 rows (library GEMM), the split-K slices for up to 48
+  // more than 128 rows (library GEMM), the split-K slices for up to 128
   const size_t max_cols = std::max<size_t>({(size_t)(c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim,
                                             (size_t)c.hidden, 2 * (size_t)c.ffn_dim});
   L.pf_proj_cols = max_cols;
@@ -191,7 +192,8 @@ Layout make_layout(const pced_config& c) {
   L.pf_x = take(PR * c.hidden * 2);
   L.pf_part_acc = take(PR * c.n_kv_heads * kPrefillParts * G * c.head_dim * 4);
   L.pf_part_ml = take(PR * c.n_kv_heads * kPrefillParts * G * 2 * 4);
-  L.pf_proj = take(std::max(PR * max_cols, (size_t)kLmRowsPad * L.part_cols) * 4);
+  L.pf_proj_elems = std::max(PR * max_cols, (size_t)kLmRowsPad * L.part_cols);
+  L.pf_proj = take(L.pf_proj_elems * 4);
   // staging of caches loaded from host memory: the longest sequence's K and V, at
   // most kLoadStage (longer ones go in pieces), at least one page of one layer
   const size_t page_bytes = (size_t)kPage * c.n_kv_heads * c.head_dim * es;
@@ -680,15 +682,14 @@ struct FwdRows {
 
 AttnPlan plan_for_lengths(const pced_ctx* c, const std::vector<int>& lens, int group, bool pad);
 
-// One projection of a pass through the stack. Up to 48 rows: the split-K
+// One projection of a pass through the stack. Up to 128 rows: the split-K
 // kernel on the packed tiles, whose weight stream is the cost. More rows (the
-// prefill's chunks): the products are a dense contraction that the split-K
-// kernel would stream W for once per 48-row group, so rocBLAS computes them
+// prefill's chunks): a dense contraction, so rocBLAS computes the products
 // (bf16 operands, fp32 accumulation and output) from the row-major copy as a
 // single K slice, and the epilogue kernel finishes the projection.
 pced_status project(pced_ctx* c, const GemmArgs& g, const char* w_rm, GemmEpi epi, hipStream_t st,
                     const Timing* tm) {
-  if (g.M <= kLmRowsPad) {
+  if (g.M <= kProjMaxRows) {
     HIP_OK(launch_gemm(g, epi, st, tm));
     return PCED_OK;
   }
@@ -834,21 +835,9 @@ pced_status run_model_forward(pced_ctx* c, const char* model, const FwdRows& R, 
   g.num_cus = c->num_cus;
   g.part = R.proj_part;
   g.rho_rows = R.rho_rows;
-  // K slices per projection: about one block per compute unit, more where the
-  // staged x slice would not fit in LDS
-  const int stage_rows = std::min(M, M <= 16 ? 16 : M <= 32 ? 32 : 48);
-  // (more than 48 rows: one slice, the library GEMM's products)
-  auto slices = [&](int n_tiles, int K) {
-    if (M > kLmRowsPad) return 1;
-    const int groups = ceil_div(n_tiles, 8 * proj_tiles_per_wave(n_tiles));
-    int ks = std::max(1, std::min({kProjMaxSplit, K / 64, c->num_cus / groups}));
-    while (ks < std::min(kProjMaxSplit, K / 64) && proj_lds_bytes(stage_rows, K, ks) > kProjMaxLds) ++ks;
-    return ks;
-  };
-  auto fits = [&](const GemmArgs& p) {
-    return (M > kLmRowsPad || proj_lds_bytes(stage_rows, p.K, p.ksplit) <= kProjMaxLds) &&
-           (size_t)p.ksplit * 16 * p.n_tiles <= R.proj_cols;
-  };
+  // (beyond the projection kernel's rows: one slice, the library GEMM's products)
+  auto slices = [&](int n_tiles, int K) { return M > kProjMaxRows ? 1 : proj_ksplit(n_tiles, K, c->num_cus); };
+  auto fits = [&](const GemmArgs& p) { return (size_t)p.ksplit * 16 * p.n_tiles <= R.proj_cols; };
   const double F = cfg.ffn_dim;
   for (int l = 0; l < cfg.n_layers; ++l) {
     const char* lw = model + (size_t)l * ml.layer_bytes;
@@ -877,7 +866,7 @@ pced_status run_model_forward(pced_ctx* c, const char* model, const FwdRows& R, 
       q.qkv_trace = R.qkv_trace ? R.qkv_trace + (size_t)l * M * (qd + 2 * kd) : nullptr;
       ProfScope ps(c, PCED_PROF_QKV, (double)(qd + 2 * kd) * H * 2 + (double)M * (H * 2 + (qd + 2 * kd) * 2),
                    2.0 * M * (qd + 2 * kd) * H);
-      if (!fits(q)) return fail(PCED_ERR_UNSUPPORTED, "QKV projection does not fit the partial buffer or LDS");
+      if (!fits(q)) return fail(PCED_ERR_UNSUPPORTED, "QKV projection does not fit the partial buffer");
       r = project(c, q, lw + ml.qkv_rm, kEpiQkv, st, ps.timing());
       if (r != PCED_OK) return r;
     }
@@ -902,7 +891,7 @@ pced_status run_model_forward(pced_ctx* c, const char* model, const FwdRows& R, 
       o.ksplit = slices(o.n_tiles, qd);
       o.g_next = (const uint16_t*)(lw + ml.mlp_norm);
       ProfScope ps(c, PCED_PROF_OPROJ, (double)H * qd * 2 + (double)M * (qd * 2 + H * 10), 2.0 * M * H * qd);
-      if (!fits(o)) return fail(PCED_ERR_UNSUPPORTED, "O projection does not fit the partial buffer or LDS");
+      if (!fits(o)) return fail(PCED_ERR_UNSUPPORTED, "O projection does not fit the partial buffer");
       r = project(c, o, lw + ml.o_rm, kEpiResid, st, ps.timing());
       if (r != PCED_OK) return r;
     }
@@ -916,7 +905,7 @@ pced_status run_model_forward(pced_ctx* c, const char* model, const FwdRows& R, 
       u.ksplit = slices(u.n_tiles, H);
       u.ss_in = R.ss;
       ProfScope ps(c, PCED_PROF_GATEUP, 2.0 * F * H * 2 + (double)M * (H * 2 + F * 2), 4.0 * M * F * H);
-      if (!fits(u)) return fail(PCED_ERR_UNSUPPORTED, "gate/up projection does not fit the partial buffer or LDS");
+      if (!fits(u)) return fail(PCED_ERR_UNSUPPORTED, "gate/up projection does not fit the partial buffer");
       r = project(c, u, lw + ml.gu_rm, kEpiSwiglu, st, ps.timing());
       if (r != PCED_OK) return r;
     }
@@ -932,7 +921,7 @@ pced_status run_model_forward(pced_ctx* c, const char* model, const FwdRows& R, 
       d.ksplit = slices(d.n_tiles, cfg.ffn_dim);
       d.g_next = g_next;
       ProfScope ps(c, PCED_PROF_DOWN, F * H * 2 + (double)M * (F * 2 + H * 10), 2.0 * M * H * F);
-      if (!fits(d)) return fail(PCED_ERR_UNSUPPORTED, "down projection does not fit the partial buffer or LDS");
+      if (!fits(d)) return fail(PCED_ERR_UNSUPPORTED, "down projection does not fit the partial buffer");
       r = project(c, d, lw + ml.down_rm, kEpiResid, st, ps.timing());
       if (r != PCED_OK) return r;
     }
@@ -1050,7 +1039,7 @@ pced_status run_prefill_chunk(pced_ctx* c, const char* model, const int32_t* tok
   R.part_slots = part_slots;
   R.rho_rows = c->at<float>(c->lay.pf_rho);
   R.proj_part = c->at<float>(c->lay.pf_proj);
-  R.proj_cols = M > kLmRowsPad ? c->lay.pf_proj_cols : c->lay.part_cols;
+  R.proj_cols = M > kProjMaxRows ? c->lay.pf_proj_cols : c->lay.pf_proj_elems / M;
   return run_model_forward(c, model, R, st);
 }
 

@@ -224,8 +224,8 @@ struct SynthArgs {
 // for the M step rows, W packed in 16-row tiles (k_pack_w_bf16 layout), with an
 // epilogue per projection.
 enum GemmEpi { kEpiQkv = 0, kEpiResid = 1, kEpiSwiglu = 2 };
+constexpr int kProjMaxRows = 128;  // rows of the projection kernels (more: the library GEMM)
 constexpr int kProjMaxSplit = 16;  // K slices of a projection (partial buffer sized for this many)
-constexpr size_t kProjMaxLds = 150 * 1024;  // staged x slice of a projection block
 constexpr int kPrefillRows = 2304;  // (sequence, suffix token) rows of one prefill chunk, at least
 constexpr int kPrefillParts = 8;   // attention partial states per prefill row and kv-head
 struct GemmArgs {
@@ -346,8 +346,7 @@ hipError_t launch_gemm(const GemmArgs& a, GemmEpi epi, hipStream_t st, const Tim
 // The projection epilogue alone, over products already in a.part as one K
 // slice ([M][16 n_tiles] fp32, e.g. from a library GEMM).
 hipError_t launch_proj_epilogue(const GemmArgs& a, GemmEpi epi, hipStream_t st, const Timing* tm = nullptr);
-int proj_tiles_per_wave(int n_tiles);                // 16-column tiles per wave of a projection block
-size_t proj_lds_bytes(int rows, int K, int ksplit);  // LDS of a projection block
+int proj_ksplit(int n_tiles, int K, int num_cus);  // K slices of a projection of at most kProjMaxRows rows
 hipError_t launch_embed(const EmbedArgs& a, int n_seqs, hipStream_t st, const Timing* tm = nullptr);
 hipError_t launch_prefill_meta(const PrefillMetaArgs& a, hipStream_t st);
 // rho[m] = 1/sqrt(sum_p ss[p][m] * inv_dim + eps) for m < M

@@ -2697,127 +2697,129 @@ __global__ __launch_bounds__(256) void k_synth(SynthArgs a) {
 constexpr int kProjWaves = 8;  // waves per projection block
 
 
-// Decoder projection for the rows of one decode step (M <= 16 NT <= 48 rows,
-// in the matrix cores' N dimension): K-slice partial sums part[split][m][n] = sum_{k in slice}
-// x[m][k] W[n][k] on the matrix cores, C^T[16 columns x 16 rows] += W[16 x 32]
-// X^T[32 x 16] (v_mfma_f32_16x16x32_bf16); k_proj_reduce adds the slices in
-// order and applies the projection's epilogue.
-// Block b covers column group b / ksplit (8 TPW consecutive 16-column tiles,
-// TPW per wave) over K slice b % ksplit. The block first stages its x slice
-// (rows x slice, row-major, rows padded by 16 bytes against bank conflicts) in
-// LDS with coalesced loads; each wave then streams only its packed W tiles
-// (contiguous 1 KiB loads, every byte read once) through an R-deep register ring
-// and reads its x operands from LDS, so the whole register ring holds W bytes
-// in flight. The barrier after staging waits on LDS only; it does not drain the
-// ring.
-template <int NT, int TPW>
-__global__ __launch_bounds__(64 * kProjWaves) void k_proj(GemmArgs a) {
-  constexpr int WPB = kProjWaves, CT = WPB * TPW, R = TPW == 1 ? 8 : 5;
-  extern __shared__ __align__(16) uint16_t xs[];
-  // the wave index (and so the tiles) is scalar; the ring's tail guards depend
-  // only on kernel arguments, so they are branches: matrix-core instructions do
-  // not honour EXEC, a guard turned into an EXEC mask would not stop them
+// Decoder projection for up to 16 NT <= 128 rows (in the matrix cores' N
+// dimension): K-slice partial sums part[split][m][n] = sum_{k in slice} x[m][k]
+// W[n][k], C^T[16 columns x 16 rows] += W[16 x 32] X^T[32 x 16]
+// (v_mfma_f32_16x16x32_bf16); k_proj_reduce adds the slices in order and applies
+// the projection's epilogue. Bound: the W stream.
+// Block b covers column group b / ksplit (8 consecutive 16-column tiles, one per
+// wave) over K slice b % ksplit. Both operands are streamed through rings of NS
+// 64-wide steps, NS - 1 of them in flight: each wave's own packed W tiles
+// (contiguous 1 KiB loads, every byte read once) through registers, and the x
+// operands of all row tiles straight into LDS (buffer loads with the LDS flag,
+// the eight waves an equal share each, every lane the 16 bytes of its place in
+// the B operand). At a step the wave waits until its own loads of that step have
+// landed, leaving the later ones in flight, and meets the others at a barrier;
+// then every wave's x of the step is in LDS, and all waves have left the stage
+// that the next loads fill. Loads past the slice's end go past the descriptors'
+// range and so cost no memory access (re-reading the last step doubled the loads
+// of a short slice).
+// Per layer at 4096 / 1024 / 14336 (QKV, O, gate/up and down together): 33 rows
+// 84 us (93 us with the x slice staged whole before a weights-only ring), 65 rows
+// 107 us (144 us with the library GEMM).
+template <int NT>
+__global__ __launch_bounds__(64 * kProjWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_proj(GemmArgs a) {
+  constexpr int WPB = kProjWaves, NS = 8, LEAD = NS - 1;
+  constexpr int XU = 2 * NT, XB = (XU + WPB - 1) / WPB;  // 1 KiB x operands of a step; of which each wave loads
+  constexpr int WAITN = (LEAD - 1) * (2 + XB);
+  static_assert(WAITN < 64, "vmcnt has 6 bits");
+  // separate arrays, so that the compiler can tell the stage being loaded from the one being read
+  __shared__ __align__(16) uint4 xs0[XU][64];
+  __shared__ __align__(16) uint4 xs1[XU][64];
+  __shared__ __align__(16) uint4 xs2[XU][64];
+  __shared__ __align__(16) uint4 xs3[XU][64];
+  __shared__ __align__(16) uint4 xs4[XU][64];
+  __shared__ __align__(16) uint4 xs5[XU][64];
+  __shared__ __align__(16) uint4 xs6[XU][64];
+  __shared__ __align__(16) uint4 xs7[XU][64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 15, quad = lane >> 4;
   const int grp = blockIdx.x / a.ksplit, split = blockIdx.x - grp * a.ksplit;
   const int K = a.K, KS = K / 64;
   const int ks0 = split * KS / a.ksplit;
   const int n = (split + 1) * KS / a.ksplit - ks0;
-  const int LDX = 64 * n + 8;  // staged row length (elements)
   const int N = 16 * a.n_tiles;
-  // packed W: tile (t, ks) at (t * t_vb + ks * t_ks) * 128 16-byte units
   const size_t t_vb = kProjKMajor ? 1 : KS, t_ks = kProjKMajor ? (size_t)a.n_tiles : 1;
-  const uint4* wt[TPW];
+  const int tile = grp * WPB + wave;
+  const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)((const char*)a.w + ks0 * t_ks * 2048), 0, 0x7FFFFFFF, 0x00020000);
+  const uint32_t w_t = (uint32_t)(min(tile, a.n_tiles - 1) * t_vb) * 2048u;
+  const uint32_t w_ks = (uint32_t)t_ks * 2048u;
+  const uint32_t lane16 = 16u * lane;
+  const __amdgpu_buffer_rsrc_t xrs =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(a.x + 64 * (size_t)ks0), 0, 0x7FFFFFFF, 0x00020000);
+  uint32_t xo[XB];  // this lane's place in the wave's x operands: row min(16 t + col, M - 1), 16 bytes at 16 quad + 8 h
 #pragma unroll
-  for (int tt = 0; tt < TPW; ++tt)
-    wt[tt] = (const uint4*)a.w + ((size_t)min(grp * CT + wave * TPW + tt, a.n_tiles - 1) * t_vb + ks0 * t_ks) * 128 +
-             lane;
-
-  const int m0 = 0, rows = a.M;  // one row group: M <= 16 NT
-  f32x4 acc[TPW][NT];
+  for (int i = 0; i < XB; ++i) {
+    const int j = min(wave + WPB * i, XU - 1);
+    xo[i] = 2u * ((uint32_t)min(16 * (j >> 1) + col, a.M - 1) * K + 16 * quad + 8 * (j & 1));
+  }
+  auto stage = [&](auto st_c) __attribute__((always_inline)) -> uint4(*)[64] {
+    constexpr int ST = decltype(st_c)::value;
+    if constexpr (ST < 4) return ST == 0 ? xs0 : ST == 1 ? xs1 : ST == 2 ? xs2 : xs3;
+    else return ST == 4 ? xs4 : ST == 5 ? xs5 : ST == 6 ? xs6 : xs7;
+  };
+  u32x4 wr[NS][2];
+  auto load = [&](auto st_c, int i) __attribute__((always_inline)) {
+    constexpr int ST = decltype(st_c)::value;
+    // past the slice's end: an offset past the descriptors' range, which reads as zero without a memory access
+    const uint32_t past = i < n ? 0u : 0x80000000u;
+    i = min(i, n - 1);
+    uint4(*dst)[64] = stage(st_c);
 #pragma unroll
-  for (int tt = 0; tt < TPW; ++tt)
+    for (int b = 0; b < XB; ++b) {
+      const int j = min(wave + WPB * b, XU - 1);
+      const uint32_t vo = xo[b] | past, so = 128u * (uint32_t)i;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(xrs, (lds_void*)&dst[j][0], 16, vo, so, 0, 0);
+    }
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[tt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  struct Stage { uint4 w[TPW][2]; };
-  Stage st[R];
-  auto load = [&](Stage& S, int i) __attribute__((always_inline)) {
-    i = min(i, n - 1);  // past the end: the last step again (a cache hit), the ring stays branch-free
+    for (int h = 0; h < 2; ++h)  // (cache policy 2: non-temporal)
+      wr[ST][h] = __builtin_amdgcn_raw_buffer_load_b128(wrs, lane16 | past, (uint32_t)i * w_ks + w_t + 1024u * h, 2);
+  };
+  f32x4 acc[NT];
 #pragma unroll
-    for (int tt = 0; tt < TPW; ++tt) {
-      S.w[tt][0] = ld_w<true>(&wt[tt][(size_t)i * t_ks * 128]);
-      S.w[tt][1] = ld_w<true>(&wt[tt][(size_t)i * t_ks * 128 + 64]);
+  for (int nt = 0; nt < NT; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto step = [&](auto st_c, int i) __attribute__((always_inline)) {
+    constexpr int ST = decltype(st_c)::value;
+    wait_vmcnt<WAITN>();
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    load(std::integral_constant<int, (ST + LEAD) % NS>{}, i + LEAD);
+    __builtin_amdgcn_sched_barrier(0);
+    if (i < n) {
+      uint4(*src)[64] = stage(st_c);
+      constexpr int PF = NT < 3 ? NT : 3;  // row tiles whose operands are read ahead of their products
+      bf16x8 b[PF + 1][2];
+#pragma unroll
+      for (int t = 0; t < PF; ++t)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) b[t][h] = as_bf16x8(src[2 * t + h][lane]);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          if (t + PF < NT) b[(t + PF) % (PF + 1)][h] = as_bf16x8(src[2 * (t + PF) + h][lane]);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wr[ST][h]), b[t % (PF + 1)][h],
+                                                           acc[t], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
   };
-  // x operand rows of this lane in LDS (rows past the group's end read the last row)
-  const uint16_t* xl[NT];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) xl[nt] = xs + (size_t)min(16 * nt + col, rows - 1) * LDX + 16 * quad;
-  auto mma = [&](const Stage& S, int i) __attribute__((always_inline)) {
-    uint4 xv[NT][2];
+  static_for<LEAD>([&](auto jc) __attribute__((always_inline)) {
+    load(jc, (int)decltype(jc)::value);
+    __builtin_amdgcn_sched_barrier(0);  // in this order: the waits count on it
+  });
+  for (int i = 0; i < n; i += NS)
+    static_for<NS>([&](auto jc) __attribute__((always_inline)) { step(jc, i + (int)decltype(jc)::value); });
+  wait_vmcnt<0>();  // the loads past the end (some into LDS) have landed
+  if (tile < a.n_tiles) {
+    float* dst = a.part + (size_t)split * a.M * N + 16 * tile + 4 * quad;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-      xv[nt][0] = *(const uint4*)(xl[nt] + 64 * i);
-      xv[nt][1] = *(const uint4*)(xl[nt] + 64 * i + 8);
-    }
-#pragma unroll
-    for (int tt = 0; tt < TPW; ++tt)
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        acc[tt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(S.w[tt][0]), as_bf16x8(xv[nt][0]),
-                                                              acc[tt][nt], 0, 0, 0);
-        acc[tt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(S.w[tt][1]), as_bf16x8(xv[nt][1]),
-                                                              acc[tt][nt], 0, 0, 0);
-      }
-  };
-  // Stage the x slice: units of 8 elements, consecutive threads along a row, SB
-  // units per thread in flight at once (indices past the end repeat the last
-  // unit: same value, same place). The first batch is issued before the W ring,
-  // so its wait leaves the ring in flight; a load-then-store loop paid one
-  // memory round trip per unit with the ring stalled.
-  constexpr int SB = 8;
-  const int upr = 8 * n, units = rows * upr;  // units per row, in all
-  uint4 xv[SB];
-  int xo[SB];  // LDS element offsets of the batch's units
-#pragma unroll
-  for (int j = 0; j < SB; ++j) {
-    const int u = min((int)threadIdx.x + j * 64 * WPB, units - 1), r = u / upr, c = u - r * upr;
-    xv[j] = *(const uint4*)(a.x + (size_t)(m0 + r) * K + 64 * ks0 + 8 * c);
-    xo[j] = r * LDX + 8 * c;
-  }
-#pragma unroll
-  for (int j = 0; j < R; ++j) load(st[j], j);
-#pragma unroll
-  for (int j = 0; j < SB; ++j) *(uint4*)(xs + xo[j]) = xv[j];
-  for (int u0 = threadIdx.x + SB * 64 * WPB; u0 < units; u0 += SB * 64 * WPB) {
-#pragma unroll
-    for (int j = 0; j < SB; ++j) {
-      const int u = min(u0 + j * 64 * WPB, units - 1), r = u / upr, c = u - r * upr;
-      xv[j] = *(const uint4*)(a.x + (size_t)(m0 + r) * K + 64 * ks0 + 8 * c);
-      xo[j] = r * LDX + 8 * c;
-    }
-#pragma unroll
-    for (int j = 0; j < SB; ++j) *(uint4*)(xs + xo[j]) = xv[j];
-  }
-  __syncthreads();
-  for (int i = 0; i < n; i += R) {
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      if (i + j < n) mma(st[j], i + j);
-      load(st[j], i + j + R);
-    }
-  }
-#pragma unroll
-  for (int tt = 0; tt < TPW; ++tt) {
-    const int tile = grp * CT + wave * TPW + tt;
-    if (tile < a.n_tiles) {
-      float* dst = a.part + (size_t)split * a.M * N + 16 * tile + 4 * quad;
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int m = m0 + 16 * nt + col;
-        if (m < a.M)
-          *(float4*)(dst + (size_t)m * N) = make_float4(acc[tt][nt][0], acc[tt][nt][1], acc[tt][nt][2], acc[tt][nt][3]);
-      }
+      const int m = 16 * nt + col;
+      if (m < a.M) *(float4*)(dst + (size_t)m * N) = make_float4(acc[nt][0], acc[nt][1], acc[nt][2], acc[nt][3]);
     }
   }
 }
@@ -3265,11 +3267,12 @@ hipError_t launch_pack_tiles(const void* w, void* wp, int rows, int K, int strid
   return hipGetLastError();
 }
 
-int proj_tiles_per_wave(int n_tiles) { return n_tiles >= 1024 ? 2 : 1; }
-
-size_t proj_lds_bytes(int rows, int K, int ksplit) {
-  const int n = (K / 64 + ksplit - 1) / ksplit;  // longest slice
-  return (size_t)rows * (64 * n + 8) * 2;
+int proj_ksplit(int n_tiles, int K, int num_cus) {
+  const int KS = K / 64, groups = (n_tiles + kProjWaves - 1) / kProjWaves;
+  int ks = std::max(1, std::min({kProjMaxSplit, KS / 4, num_cus / groups}));
+  // 32-bit buffer offsets into a slice's W
+  while (ks < std::min(kProjMaxSplit, KS) && (size_t)((KS + ks - 1) / ks) * n_tiles * 2048 >= 0x7FFFFFFFull) ++ks;
+  return ks;
 }
 
 namespace {
@@ -3298,26 +3301,23 @@ hipError_t launch_reduce(const GemmArgs& a, GemmEpi epi, hipStream_t st, hipEven
 }  // namespace
 
 hipError_t launch_gemm(const GemmArgs& a, GemmEpi epi, hipStream_t st, const Timing* tm) {
-  // up to 48 rows (three 16-row groups in the matrix cores' N dimension); more
-  // rows are dense contractions for the library GEMM (launch_proj_epilogue)
-  if (a.K % 64 != 0 || a.M < 1 || a.M > kLmRowsPad || a.n_tiles < 1) return hipErrorInvalidValue;
+  if (a.K % 64 != 0 || a.M < 1 || a.M > kProjMaxRows || a.n_tiles < 1) return hipErrorInvalidValue;
   if (epi == kEpiSwiglu && a.n_tiles % 2) return hipErrorInvalidValue;
-  if (a.ksplit < 1 || a.ksplit > a.K / 64) return hipErrorInvalidValue;
-  const int NT = a.M <= 16 ? 1 : a.M <= 32 ? 2 : 3;
-  const int tpw = proj_tiles_per_wave(a.n_tiles);
-  const size_t lds = proj_lds_bytes(a.M, a.K, a.ksplit);
-  if (lds > kProjMaxLds) return hipErrorInvalidValue;
-  const dim3 b(64 * kProjWaves);
-  const dim3 g((a.n_tiles + kProjWaves * tpw - 1) / (kProjWaves * tpw) * a.ksplit);
+  const int KS = a.K / 64;
+  if (a.ksplit < 1 || a.ksplit > KS) return hipErrorInvalidValue;
+  if ((size_t)((KS + a.ksplit - 1) / a.ksplit) * a.n_tiles * 2048 >= 0x7FFFFFFFull) return hipErrorInvalidValue;
+  const dim3 g((a.n_tiles + kProjWaves - 1) / kProjWaves * a.ksplit), b(64 * kProjWaves);
   hipError_t e;
-  if (tpw == 1)
-    e = NT == 1 ? go(k_proj<1, 1>, g, b, lds, st, t0(tm), nullptr, a)
-        : NT == 2 ? go(k_proj<2, 1>, g, b, lds, st, t0(tm), nullptr, a)
-                  : go(k_proj<3, 1>, g, b, lds, st, t0(tm), nullptr, a);
-  else
-    e = NT == 1 ? go(k_proj<1, 2>, g, b, lds, st, t0(tm), nullptr, a)
-        : NT == 2 ? go(k_proj<2, 2>, g, b, lds, st, t0(tm), nullptr, a)
-                  : go(k_proj<3, 2>, g, b, lds, st, t0(tm), nullptr, a);
+  switch ((a.M + 15) / 16) {
+    case 1: e = go(k_proj<1>, g, b, 0, st, t0(tm), nullptr, a); break;
+    case 2: e = go(k_proj<2>, g, b, 0, st, t0(tm), nullptr, a); break;
+    case 3: e = go(k_proj<3>, g, b, 0, st, t0(tm), nullptr, a); break;
+    case 4: e = go(k_proj<4>, g, b, 0, st, t0(tm), nullptr, a); break;
+    case 5: e = go(k_proj<5>, g, b, 0, st, t0(tm), nullptr, a); break;
+    case 6: e = go(k_proj<6>, g, b, 0, st, t0(tm), nullptr, a); break;
+    case 7: e = go(k_proj<7>, g, b, 0, st, t0(tm), nullptr, a); break;
+    default: e = go(k_proj<8>, g, b, 0, st, t0(tm), nullptr, a); break;
+  }
   if (e != hipSuccess) return e;
   return launch_reduce(a, epi, st, t1(tm));
 }
