@@ -76,11 +76,12 @@ bool cfg_valid(const pced_config* c, std::string* why) {
 }
 
 constexpr size_t kLoadStage = (size_t)64 << 20;  // staging of host-memory caches, at most
+constexpr size_t kPartBytes = (size_t)128 << 20;  // attention partial states of several layers, at most
 
 struct Layout {
   size_t len0, page_table, seq_query, query_seq0, query_exp0, exp_seq, exp_query, prior, logw, beta_fixed,
       load_items, src_k, src_v, meta_end;
-  size_t chunk_info, seg, nparts, work_pages, prev_tok, beta, part_acc, part_ml, x, logits,
+  size_t chunk_info, seg, nparts, work_pages, prev_tok, beta, part_acc, part_ml, x, x_layers, logits,
       rho, x_packed, fuse_part, lse_part, jsd_part, syn_q, syn_k, syn_v, dec_h, dec_a, dec_act, dec_ss, dec_rho, dec_part,
       rope, pf_len0, pf_pt, pf_tok, pf_glen0, pf_gpt, pf_nparts, pf_rho, pf_h, pf_a, pf_act, pf_ss, pf_q, pf_x, pf_part_acc, pf_part_ml, pf_proj,
       load_stage, stage_bytes, total;
@@ -129,14 +130,16 @@ Layout make_layout(const pced_config& c) {
   L.work_pages = take((size_t)L.max_work * kMaxSplitPages * 4);
   L.prev_tok = take(B * 4);
   L.beta = take(S * 4);
-  // split partials: [S*Hkv][stride][G][D] with stride <= pages per sequence.
-  // The decode step alternates two sets by layer parity (bf16: both fit the
-  // fp32-sized accumulator buffer), so that a layer's attention launch can merge
-  // the previous layer's partials while writing its own.
+  // split partials: [layer][S*Hkv][stride][G][D] (bf16 or fp32) with stride <=
+  // pages per sequence; a launch takes as many layers as fit at the step's stride
+  // (room for one layer at least; for all of them up to kPartBytes)
   L.part_slots = (size_t)c.max_seqs * c.n_kv_heads * c.max_pages_per_seq;
+  L.part_slots = std::max(L.part_slots, std::min(L.part_slots * c.n_layers, kPartBytes / ((size_t)G * c.head_dim * 4)));
   L.part_acc = take(L.part_slots * G * c.head_dim * 4);
   L.part_ml = take(2 * L.part_slots * G * 2 * 4);
   L.x = take((size_t)L.rows_pad * c.hidden * es);
+  // the outputs of the layers before the last, for launches that take several layers
+  L.x_layers = take(c.n_layers > 1 ? S * c.n_layers * c.hidden * es : 0);
   L.logits = take(S * c.vocab * 4);
   L.rho = take((size_t)L.rows_pad * 4);
   // the many-row LM head's operand-ordered copy of x (bf16, more than 48 rows)
@@ -324,10 +327,11 @@ void plan_stats(const std::vector<long>& pre, long P, long C, AttnPlan* out) {
 // wave starts in the first round and streams the same number of pages), at
 // least P/64 (one page id per lane), raised when a chunk would meet more
 // sequences than a wave can stage q rows for.
-AttnPlan plan_for_lengths(const pced_ctx* c, const std::vector<int>& lens, int group = 0, bool pad = false);
+AttnPlan plan_for_lengths(const pced_ctx* c, const std::vector<int>& lens, int group = 0, bool pad = false,
+                          int layers = 1);
 
-AttnPlan plan_attention(const pced_ctx* c) {
-  return plan_for_lengths(c, std::vector<int>(c->len.begin(), c->len.end()));
+AttnPlan plan_attention(const pced_ctx* c, int layers) {
+  return plan_for_lengths(c, std::vector<int>(c->len.begin(), c->len.end()), 0, false, layers);
 }
 
 // The same plan for rows of the given lengths (before the step's append);
@@ -335,9 +339,24 @@ AttnPlan plan_attention(const pced_ctx* c) {
 // pad: every item counts at least the chunk length of the unconstrained plan
 // (at most kMaxSplitPages / 2 pages), so that a run of short items does not
 // force small chunks when a wave can stage few segments.
-AttnPlan plan_for_lengths(const pced_ctx* c, const std::vector<int>& lens, int group, bool pad) {
+// layers: layers per launch. Their waves share the chip, so each layer is cut
+// into fewer chunks: whole rounds of waves over all layers, at about 32 pages per
+// chunk or more (a wave's start and its partial states weigh less in a longer
+// chunk; 64 is the most). Eight steps over 33 caches x 32 layers with their load:
+// 11.35 ms at one round's chunks per layer cut by the layers (85 pages, capped at
+// 64), 11.0 at 16 pages, 10.5 at 32, 10.5 to 11.0 at 24 to 48; with one launch
+// per layer, each cut for a round of its own, 11.0 ms. Where a layer is short the
+// launches themselves weigh most: 16 layers over 8 caches of 256 to 1024 tokens,
+// 2.1 -> 1.36 ms for eight steps.
+AttnPlan plan_for_lengths(const pced_ctx* c, const std::vector<int>& lens, int group, bool pad, int layers) {
   const int S = (int)lens.size();
   long cap = std::max<long>(1, (long)c->num_cus * c->attn_waves_per_cu / c->cfg.n_kv_heads);
+  if (layers > 1) {
+    long pages = 0;
+    for (int s = 0; s < S; ++s) pages += ceil_div(lens[s] + 1, kPage);
+    const long rounds = std::max<long>(1, pages * layers / (cap * 32));
+    cap = std::max<long>(1, cap * rounds / layers);
+  }
   if (c->cfg.max_attn_chunks > 0) cap = std::min<long>(cap, c->cfg.max_attn_chunks);
   auto first_c = [&](long P) { return std::max<long>(std::min(cap, P), ceil_div(P, (long)kMaxSplitPages)); };
   int min_pages = 1;
@@ -680,8 +699,6 @@ struct FwdRows {
   uint16_t* act_trace = nullptr;
 };
 
-AttnPlan plan_for_lengths(const pced_ctx* c, const std::vector<int>& lens, int group, bool pad);
-
 // One projection of a pass through the stack. Up to 128 rows: the split-K
 // kernel on the packed tiles, whose weight stream is the cost. More rows (the
 // prefill's chunks): a dense contraction, so rocBLAS computes the products
@@ -802,6 +819,8 @@ pced_status run_model_forward(pced_ctx* c, const char* model, const FwdRows& R, 
   at.maxpps = cfg.max_pages_per_seq;
   at.t = c->t;
   at.split_stride = plan.max_parts;
+  at.launch_layers = 1;
+  at.n_chunks = plan.chunks;
   at.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)D));
   double kv_tokens = 0, kv_item_tokens = 0;  // keys per query row; keys read per item
   for (int r = 0; r < M; ++r) kv_tokens += R.lens[r] + 1;
@@ -876,11 +895,11 @@ pced_status run_model_forward(pced_ctx* c, const char* model, const FwdRows& R, 
     at.is_last_layer = l == cfg.n_layers - 1;
     {
       ProfScope ps(c, PCED_PROF_ATTN, attn_bytes, attn_flops);
-      HIP_OK(launch_attn(at, plan.chunks * cfg.n_kv_heads, D, true, st, ps.timing()));
+      HIP_OK(launch_attn(at, D, true, st, ps.timing()));
     }
     if (plan.max_parts > 1) {
       ProfScope ps(c, PCED_PROF_COMBINE, 0, 0);
-      HIP_OK(launch_attn_combine(at, D, plan.max_parts, true, st, ps.timing()));
+      HIP_OK(launch_attn_combine(at, D, true, st, ps.timing()));
     }
     {  // O projection + residual; the MLP norm's input
       GemmArgs o = g;
@@ -1082,7 +1101,21 @@ pced_status run_step(pced_ctx* c, const void* q, const void* k_new, const void* 
     if (pidx >= P || c->page_table[(size_t)s * P + pidx] < 0)
       return fail(PCED_ERR_CAPACITY, "sequence %d has no page for token %d", s, c->len[s]);
   }
-  const AttnPlan plan = plan_attention(c);
+  // Layers per launch: all, or what the partial states of the plan leave room for
+  const size_t es_part = c->bf16 ? 2 : 4;
+  const size_t part_bytes = c->lay.part_slots * c->G * cfg.head_dim * 4;  // (part_ml holds 2 part_slots of them)
+  AttnPlan plan;
+  size_t slots = 0;  // partial slots of one layer
+  int per_launch = cfg.n_layers;
+  for (;;) {
+    plan = plan_attention(c, per_launch);
+    slots = (size_t)c->S * cfg.n_kv_heads * plan.max_parts;
+    const size_t room = plan.max_parts > 1
+                            ? std::min(part_bytes / (slots * c->G * cfg.head_dim * es_part), 2 * c->lay.part_slots / slots)
+                            : (size_t)cfg.n_layers;
+    if (per_launch == 1 || (size_t)per_launch <= room) break;
+    per_launch = std::max(1, std::min<int>(per_launch - 1, (int)room));
+  }
   if (plan.chunks > c->lay.max_work) return fail(PCED_ERR_CAPACITY, "attention plan exceeds workspace");
   const double es = (double)esize_of(cfg);
 
@@ -1142,37 +1175,25 @@ pced_status run_step(pced_ctx* c, const void* q, const void* k_new, const void* 
   const double attn_bytes = kv_tokens * 2.0 * cfg.n_kv_heads * cfg.head_dim * es +
                             2.0 * c->S * cfg.n_q_heads * cfg.head_dim * es;
   const double attn_flops = kv_tokens * 4.0 * cfg.n_q_heads * cfg.head_dim;
-  // Sequences that span several chunks need a merge of their partial states.
-  // bf16: layer l's partials go to set l % 2 and the attention launch of layer
-  // l + 1 merges them (one launch per layer instead of two); only the last
-  // layer's merge is a launch of its own.
-  const bool split = plan.max_parts > 1;
-  const bool fold = split && c->bf16;
-  const size_t acc_set = c->lay.part_slots * c->G * cfg.head_dim / 2;  // floats per bf16 set
-  const size_t ml_set = c->lay.part_slots * c->G * 2;
-  float* acc0 = at.part_acc;
-  float* ml0 = at.part_ml;
-  for (int l = 0; l < cfg.n_layers; ++l) {
+  // The layers are independent (every layer's q is given): a launch takes
+  // per_launch of them, and one more merges the sequences that span several chunks.
+  at.n_chunks = plan.chunks;
+  at.acc_layer_bytes = slots * c->G * cfg.head_dim * es_part;
+  at.ml_layer = slots * c->G * 2;
+  at.x_layers = c->at<void>(c->lay.x_layers);
+  at.x_layer_bytes = (size_t)c->S * cfg.hidden * esize_of(cfg);
+  for (int l = 0; l < cfg.n_layers; l += per_launch) {
     at.layer = l;
-    at.is_last_layer = l == cfg.n_layers - 1;
-    const int set = fold ? l & 1 : 0;
-    at.part_acc = acc0 + set * acc_set;
-    at.part_ml = ml0 + set * ml_set;
-    const bool merge_prev = fold && l > 0;
-    at.mrg_acc = merge_prev ? (const uint16_t*)(acc0 + (set ^ 1) * acc_set) : nullptr;
-    at.mrg_ml = merge_prev ? ml0 + (set ^ 1) * ml_set : nullptr;
-    at.mrg_layer = l - 1;
+    at.launch_layers = std::min(per_launch, cfg.n_layers - l);
     {
-      ProfScope ps(c, PCED_PROF_ATTN, attn_bytes, attn_flops);
-      HIP_OK(launch_attn(at, plan.chunks * cfg.n_kv_heads, cfg.head_dim, c->bf16, st, ps.timing()));
+      ProfScope ps(c, PCED_PROF_ATTN, at.launch_layers * attn_bytes, at.launch_layers * attn_flops);
+      HIP_OK(launch_attn(at, cfg.head_dim, c->bf16, st, ps.timing()));
     }
-    if (split && (!fold || l == cfg.n_layers - 1)) {
+    if (plan.max_parts > 1) {
       ProfScope ps(c, PCED_PROF_COMBINE, 0, 0);
-      HIP_OK(launch_attn_combine(at, cfg.head_dim, plan.max_parts, c->bf16, st, ps.timing()));
+      HIP_OK(launch_attn_combine(at, cfg.head_dim, c->bf16, st, ps.timing()));
     }
   }
-  at.mrg_acc = nullptr;
-  at.mrg_ml = nullptr;
 
   const pced_status r = run_head(c, at.x_out, nullptr, w, tokens_out, tok_stride, extra, st);
   if (r != PCED_OK) return r;

@@ -42,7 +42,7 @@ __device__ inline int vswz(int t, int d) {
   return (((j >> 1) * 64 + (d & 15) + 16 * (t >> 2)) * 2 + (j & 1)) * 4 + (t & 3);
 }
 
-// Per-step attention launch arguments (one launch per layer).
+// Attention launch arguments: launch_layers layers from `layer` on.
 struct AttnArgs {
   const void* q;            // [S][L][Hq][D]
   const void* kpool;        // [L][max_pages][Hkv][tile]
@@ -65,12 +65,12 @@ struct AttnArgs {
   void* x_out;              // [S][Hq*D] layer output, storage type
   float* attn_out;          // optional [S][L][Hq][D]
   float* hidden_out;        // optional [S][Hq*D] (last layer only)
-  // bf16 decode attention only, optional: the previous layer's partial states
-  // (same plan, [S*Hkv][split_stride][G][D] bf16 and [S*Hkv][split_stride][G][2]),
-  // merged by this launch into x_out (and attn_out at layer mrg_layer)
-  const uint16_t* mrg_acc;
-  const float* mrg_ml;
-  int mrg_layer;
+  int launch_layers, n_chunks;             // layers of this launch; chunks C of the plan
+  size_t acc_layer_bytes, ml_layer;        // partial states: bytes of part_acc and floats of part_ml per layer
+  // with x_layers, x_out receives the last layer's output and x_layers
+  // [L][S][Hq*D] the others' (is_last_layer is then set by the kernel)
+  void* x_layers;
+  size_t x_layer_bytes;
   int n_seqs, n_layers, layer, n_q_heads, n_kv_heads, group;
   int max_pages, maxpps, t, split_stride, is_last_layer;
   int kv_reread;            // pages are read by several rows of the launch (prefill): plain loads
@@ -310,9 +310,9 @@ hipError_t launch_fill_i32(int32_t* p, int32_t v, size_t n, hipStream_t st);
 hipError_t launch_zero_bytes(void* p, size_t nbytes, hipStream_t st);
 hipError_t launch_load(const LoadArgs& a, int n_items, bool bf16, hipStream_t st, const Timing* tm = nullptr);
 hipError_t launch_append(const AppendArgs& a, bool bf16, hipStream_t st, const Timing* tm = nullptr);
-hipError_t launch_attn(const AttnArgs& a, int n_blocks, int head_dim, bool bf16, hipStream_t st, const Timing* tm = nullptr);
+hipError_t launch_attn(const AttnArgs& a, int head_dim, bool bf16, hipStream_t st, const Timing* tm = nullptr);
 int attn_blocks_per_cu(int head_dim, bool bf16);  // resident one-wave blocks per CU
-hipError_t launch_attn_combine(const AttnArgs& a, int head_dim, int max_splits, bool bf16, hipStream_t st, const Timing* tm = nullptr);
+hipError_t launch_attn_combine(const AttnArgs& a, int head_dim, bool bf16, hipStream_t st, const Timing* tm = nullptr);
 hipError_t launch_pack_lm_head(const void* w, void* wp, int V, int K, bool bf16, hipStream_t st);
 hipError_t launch_lmhead(const LmArgs& a, bool bf16, hipStream_t st, const Timing* tm = nullptr);
 // the divergence's chunk partials, and with `sums` beta itself

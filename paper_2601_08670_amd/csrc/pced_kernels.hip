@@ -378,6 +378,17 @@ __device__ __forceinline__ int mq_end_off(const AttnArgs& a, int v, int c) {
   return last - min(c / gk, last);
 }
 
+// The launch's layer l (of a.launch_layers) as the arguments of a one-layer launch.
+__device__ __forceinline__ void select_layer(AttnArgs& a, int l) {
+  a.layer += l;
+  a.part_acc = (float*)((char*)a.part_acc + l * a.acc_layer_bytes);
+  a.part_ml += l * a.ml_layer;
+  if (a.x_layers) {
+    a.is_last_layer = a.layer == a.n_layers - 1;
+    if (!a.is_last_layer) a.x_out = (char*)a.x_layers + a.layer * a.x_layer_bytes;
+  }
+}
+
 // Write 4 consecutive output dims of one q-head: fp32 debug copy, the layer
 // output in the storage type, and (last layer) the fp32 value of the stored x.
 // MQ: s is a prefill token group and head = kv-head x group + column (mq_col);
@@ -416,10 +427,7 @@ __device__ __forceinline__ void write_o4(const AttnArgs& a, int s, int head, int
 // output o_j in bf16 (the fp32 path keeps acc_j in fp32). Sequences that fit
 // one split were written directly by the attention kernel.
 //
-// bf16: one wave per item (sequence, kv-head, q-head), in the merge kernel and
-// in the prologue of the next layer's attention launch alike, through the
-// functions below (same operations in the same order: bit-identical results).
-// Splits go in groups of 16, merged online. Within a group, lane l loads 8
+// bf16: one wave per item (layer, sequence, kv-head, q-head). Splits go in groups of 16, merged online. Within a group, lane l loads 8
 // dims (16 bytes) of split 4 i + l / (D/8) in load i (D = 128: 4 splits per
 // load), and lane l % 16 holds (m, l) of split l % 16; a lane sums its splits in
 // order, then the lane groups are added by a butterfly (every group ends with
@@ -540,7 +548,8 @@ template <int D>
 __global__ __launch_bounds__(64) void k_attn_combine_bf16(AttnArgs a) {
   const int lane = threadIdx.x;
   const int G = a.group, Hkv = a.n_kv_heads;
-  const int it = blockIdx.x;
+  const int items = a.n_seqs * Hkv * G, l = blockIdx.x / items, it = blockIdx.x - l * items;
+  select_layer(a, l);
   const int s = it / (Hkv * G), g = (it / G) % Hkv, h = it % G;
   const int n = a.nparts[s];
   const uint16_t* acc = (const uint16_t*)a.part_acc;
@@ -612,9 +621,11 @@ __global__ __launch_bounds__(256) void k_attn_combine_mq(AttnArgs a) {
 // groups of 16 online.
 __global__ __launch_bounds__(128) void k_attn_combine_f32(AttnArgs a, int D) {
   constexpr int J = 16;
-  const int s = blockIdx.x / a.n_kv_heads, g = blockIdx.x % a.n_kv_heads;
+  const int items = a.n_seqs * a.n_kv_heads, l = blockIdx.x / items, it = blockIdx.x - l * items;
+  select_layer(a, l);
+  const int s = it / a.n_kv_heads, g = it % a.n_kv_heads;
   const int G = a.group, stride = a.split_stride;
-  const size_t w0 = (size_t)blockIdx.x * stride;
+  const size_t w0 = (size_t)it * stride;
   const int nsplit = a.nparts[s];
   for (int idx = threadIdx.x; idx < G * D / 4; idx += blockDim.x) {
     const int h = (idx * 4) / D, d = (idx * 4) % D;
@@ -653,8 +664,10 @@ __global__ __launch_bounds__(128) void k_attn_combine_f32(AttnArgs a, int D) {
   }
 }
 
-// Flash decoding for bf16 caches over the balanced plan, one wave per (chunk,
-// kv-head). The G q-heads of the kv-head ride in the N dimension of the matrix
+// Flash decoding for bf16 caches over the balanced plan, one wave per (layer,
+// chunk, kv-head): the layers of a step whose q rows are all given are
+// independent, so one launch takes as many of them as the partial-state buffer
+// holds. The G q-heads of the kv-head ride in the N dimension of the matrix
 // cores, so every K/V byte is read once for all of them:
 //   S^T[16 tok x 16 heads] = K[16 x D] Q^T          (D/32 x 16x16x32 MFMA)
 //   O^T[D x 16 heads]     += V^T[D x 16 tok] P^T    (D/16 x 16x16x16 MFMA)
@@ -681,24 +694,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RING <= 4 ? 
   const int lane = threadIdx.x;
   const int col = lane & 15, quad = lane >> 4;
   const int G = a.group, Hkv = a.n_kv_heads;
-  const int c = blockIdx.x / Hkv, g = blockIdx.x % Hkv;
-  // Merge of the previous layer's split sequences (when a.mrg_acc is set):
-  // items (sequence, kv-head, q-head) it = blockIdx.x, + gridDim.x, ... The
-  // first item's loads are issued before anything else, so they arrive with
-  // the first pages; the merge itself runs just before the page loop.
-  const int n_mrg = a.mrg_acc ? a.n_seqs * Hkv * G : 0;
-  MergeRegs<D> mr;
-  int m_s = 0, m_g = 0, m_h = 0, m_n = 0;
-  auto mrg_item = [&](int it) __attribute__((always_inline)) {
-    m_s = it / (Hkv * G);
-    m_g = (it / G) % Hkv;
-    m_h = it % G;
-    m_n = a.nparts[m_s];
-    merge_load<D>(mr, a.mrg_acc, a.mrg_ml, (size_t)(m_s * Hkv + m_g) * a.split_stride, a.split_stride, G, m_h, 0,
-                  lane);
-  };
-  if ((int)blockIdx.x < n_mrg) mrg_item(blockIdx.x);
-
+  const int lc = blockIdx.x / Hkv, g = blockIdx.x % Hkv, l = lc / a.n_chunks, c = lc - l * a.n_chunks;
+  select_layer(a, l);
   const int2 ci = a.chunk_info[c];
   const int nseg = ci.x, np = ci.y;  // 1 .. kMaxSeg segments, 1 .. kMaxSplitPages pages
   // the chunk's physical page ids and segment descriptors, lane k holding entry
@@ -940,10 +937,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RING <= 4 ? 
   stg1 = stage(1);
   stg2 = stage(2);
   stg3 = stage(3);
-  for (int it = blockIdx.x; it < n_mrg; it += gridDim.x) {
-    if (it != (int)blockIdx.x) mrg_item(it);
-    merge_item<D>(a, mr, a.mrg_acc, a.mrg_ml, m_s, m_g, m_h, m_n, a.mrg_layer, false, lane);
-  }
   for (int i = 0; i < np; i += RING) {
 #pragma unroll
     for (int j = 0; j < RING; ++j) {
@@ -966,7 +959,7 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-// fp32 caches: one wave per (chunk, kv-head) of the balanced plan, a page at a
+// fp32 caches: one wave per (layer, chunk, kv-head) of the balanced plan, a page at a
 // time on the fp32 matrix cores, the q-heads in their N dimension:
 //   S^T[16 tok x 16 heads] += K[16 x 4] Q^T[4 x 16]     (v_mfma_f32_16x16x4_f32)
 //   O^T[16 dims x 16 heads] += V^T[16 x 4] P^T[4 x 16]
@@ -986,7 +979,8 @@ __global__ __launch_bounds__(64) void k_attn_f32(AttnArgs a, int D) {
   constexpr int NU = 4 * NJ;  // 16-dim units of a row, at most
   const int lane = threadIdx.x, col = lane & 15, quad = lane >> 4;
   const int G = a.group, Hkv = a.n_kv_heads;
-  const int c = blockIdx.x / Hkv, g = blockIdx.x % Hkv;
+  const int lc = blockIdx.x / Hkv, g = blockIdx.x % Hkv, l0 = lc / a.n_chunks, c = lc - l0 * a.n_chunks;
+  select_layer(a, l0);
   const int2 ci = a.chunk_info[c];
   const int nseg = ci.x, np = ci.y;
   const int my_pid = a.work_pages[(size_t)c * kMaxSplitPages + lane];
@@ -3205,7 +3199,8 @@ hipError_t launch_append(const AppendArgs& a, bool bf16, hipStream_t st, const T
   return go(k_append<false>, dim3(blocks), dim3(128), 0, st, t0(tm), t1(tm), a);
 }
 
-hipError_t launch_attn(const AttnArgs& a, int n_blocks, int head_dim, bool bf16, hipStream_t st, const Timing* tm) {
+hipError_t launch_attn(const AttnArgs& a, int head_dim, bool bf16, hipStream_t st, const Timing* tm) {
+  const int n_blocks = a.n_chunks * a.n_kv_heads * a.launch_layers;
   if (bf16) {
     const bool s = !a.kv_reread;
     // decode at head dim 128: a 3-page ring (two pages in flight) measured
@@ -3233,10 +3228,8 @@ int attn_blocks_per_cu(int head_dim, bool bf16) {
   return (e == hipSuccess && n > 0) ? n : 8;
 }
 
-hipError_t launch_attn_combine(const AttnArgs& a, int head_dim, int max_splits, bool bf16, hipStream_t st,
-                               const Timing* tm) {
-  const int blocks = a.n_seqs * a.n_kv_heads;
-  (void)max_splits;
+hipError_t launch_attn_combine(const AttnArgs& a, int head_dim, bool bf16, hipStream_t st, const Timing* tm) {
+  const int blocks = a.n_seqs * a.n_kv_heads * a.launch_layers;
   if (bf16) {
     const int items = blocks * a.group;
     // the prefill's token groups (kv_reread): a wave per (item, kv-head)
