@@ -452,6 +452,7 @@ FuseArgs fuse_args(pced_ctx* c, const float* logits, int32_t* tokens_out, int to
   f.winner = extra ? extra->winner : nullptr;
   f.top1 = extra ? extra->top1 : nullptr;
   f.top2 = extra ? extra->top2 : nullptr;
+  f.beta_used = extra ? extra->beta_used : nullptr;
   f.V = c->cfg.vocab;
   f.nblk = nblk;
   f.max_n = c->n_experts.empty() ? 0 : *std::max_element(c->n_experts.begin(), c->n_experts.end());
@@ -461,13 +462,6 @@ FuseArgs fuse_args(pced_ctx* c, const float* logits, int32_t* tokens_out, int to
   }
   f.tok_stride = tok_stride;
   return f;
-}
-
-pced_status copy_beta_used(pced_ctx* c, const pced_step_out* extra, hipStream_t st) {
-  if (extra && extra->beta_used)
-    HIP_OK(hipMemcpyAsync(extra->beta_used, c->at<float>(c->lay.beta), (size_t)c->NE * 4,
-                          hipMemcpyDeviceToDevice, st));
-  return PCED_OK;
 }
 
 // Launch the beta (first step) and fuse kernels over `logits`.
@@ -527,14 +521,14 @@ pced_status run_fuse(pced_ctx* c, const float* logits, bool refresh_beta, int32_
       ProfScope ps(c, PCED_PROF_FUSE, (double)c->B * f.nblk * 5 * 4, 0);
       HIP_OK(launch_fuse_final(f, c->B, st, ps.timing()));
     }
-    return copy_beta_used(c, extra, st);
+    return PCED_OK;
   }
   {
     ProfScope ps(c, PCED_PROF_FUSE, (double)c->S * cfg.vocab * 4, 0);
     ProfScope pm(c, PCED_PROF_FUSE_MERGE, (double)c->B * f.nblk * 5 * 4, 0);
     HIP_OK(launch_fuse(f, c->B, st, ps.timing(), pm.timing()));
   }
-  return copy_beta_used(c, extra, st);
+  return PCED_OK;
 }
 
 // After an LM head with the fused Eq. 2 epilogue: only the per-query merge of
@@ -546,7 +540,7 @@ pced_status run_fuse_final(pced_ctx* c, int nblk, int32_t* tokens_out, int tok_s
     ProfScope ps(c, PCED_PROF_FUSE_MERGE, (double)c->B * nblk * 5 * 4, 0);
     HIP_OK(launch_fuse_final(f, c->B, st, ps.timing()));
   }
-  return copy_beta_used(c, extra, st);
+  return PCED_OK;
 }
 
 // LM head over M rows of x. With fuse_nblk > 0 the kernel's epilogue applies
@@ -1620,7 +1614,10 @@ pced_status pced_lmhead(pced_ctx* c, const void* x, int32_t n_rows, const void* 
   if (!x || !lm_head || !logits) return fail(PCED_ERR_INVALID_ARG, "NULL argument");
   if (n_rows < 1 || n_rows > c->cfg.max_seqs)
     return fail(PCED_ERR_INVALID_ARG, "n_rows %d not in [1, %d]", n_rows, c->cfg.max_seqs);
-  // the kernel reads whole 48-row tiles of x: stage the rows in the padded buffer
+  // the many-row kernel reads only these rows of x, through its packed copy
+  if (c->bf16 && lmhead_wide_plan(n_rows, c->cfg.vocab, c->cfg.hidden).groups > 0)
+    return run_lmhead(c, x, n_rows, lm_head, logits, st);
+  // the others read whole 48-row tiles: stage the rows in the padded buffer
   void* xw = c->at<void>(c->lay.x);
   HIP_OK(launch_copy_rows(x, xw, (size_t)n_rows * c->cfg.hidden * esize_of(c->cfg), st));
   return run_lmhead(c, xw, n_rows, lm_head, logits, st);

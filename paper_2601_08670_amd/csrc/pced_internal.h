@@ -168,6 +168,7 @@ struct FuseArgs {
   int32_t* winner;          // optional [B]
   float* top1;              // optional [B]
   float* top2;              // optional [B]
+  float* beta_used;         // optional [sum N]: beta as used
   int V, nblk, tok_stride;
   int max_n;                // most experts of any query (load batch of the stand-alone fuse)
   // optional: beta is summed from the divergence's chunk partials [sum N][nchunk]

@@ -1672,7 +1672,9 @@ __global__ __launch_bounds__(256) void k_pack_x(LmArgs a, int MTP) {
   const int t = lm >> 4, col = lm & 15;
   float ss = 0.f;
   for (int k = 8 * lane; k < K; k += 512) {
-    const uint4 v = valid ? *(const uint4*)(x + k) : make_uint4(0u, 0u, 0u, 0u);
+    u32x4 u = {0u, 0u, 0u, 0u};
+    if (valid) u = *(const u32x4_a2*)(x + k);  // (a caller's rows may start at any element)
+    const uint4 v = __builtin_bit_cast(uint4, u);
     ss += sumsq8(as_bf16x8(v));
     const int ks = k >> 6, kk = k & 63, quad = kk >> 4, h = (kk >> 3) & 1;
     xp[(((size_t)ks * MTP + t) * 2 + h) * 64 + col + 16 * quad] = v;
@@ -2290,9 +2292,14 @@ __global__ __launch_bounds__(256) void k_fuse(FuseArgs a) {
 }
 
 // One block per query: merges the vocabulary slices' candidates and writes
-// y_t (Eq. 3), the expert that scored it, and the two best distinct scores.
+// y_t (Eq. 3), the expert that scored it, and the two best distinct scores; also
+// the query's beta into the caller's buffer, if wanted (a copy of its own: 4.5 us).
 __global__ __launch_bounds__(kFuseBlock) void k_fuse_final(FuseArgs a) {
   const int b = blockIdx.x;
+  if (a.beta_used) {
+    const int e1 = a.query_exp0[b + 1];
+    for (int e = a.query_exp0[b] + threadIdx.x; e < e1; e += blockDim.x) a.beta_used[e] = a.beta[e];
+  }
   Top2 r{kNegInf, 0x7FFFFFFF, 0, kNegInf, 0x7FFFFFFF};
   for (int i = threadIdx.x; i < a.nblk; i += blockDim.x) {
     const float* p = a.part + ((size_t)b * a.nblk + i) * 5;
