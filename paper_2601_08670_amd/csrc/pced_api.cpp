@@ -299,7 +299,6 @@ struct AttnPlan {
   int chunks = 0;     // C
   int max_seg = 0;    // most sequences met by one chunk
   int max_parts = 0;  // most chunks met by one sequence (partial slots per sequence)
-  int min_pages = 1;  // planned pages per sequence at least (padding pages are masked)
 };
 
 void plan_stats(const std::vector<long>& pre, long P, long C, AttnPlan* out) {
@@ -327,18 +326,21 @@ void plan_stats(const std::vector<long>& pre, long P, long C, AttnPlan* out) {
 // wave starts in the first round and streams the same number of pages), at
 // least P/64 (one page id per lane), raised when a chunk would meet more
 // sequences than a wave can stage q rows for.
-AttnPlan plan_for_lengths(const pced_ctx* c, const std::vector<int>& lens, int group = 0, bool pad = false,
-                          int layers = 1);
+AttnPlan plan_for_lengths(const pced_ctx* c, const std::vector<int>& lens, int layers = 1, int groups = 0,
+                          bool longest = false);
 
 AttnPlan plan_attention(const pced_ctx* c, int layers) {
-  return plan_for_lengths(c, std::vector<int>(c->len.begin(), c->len.end()), 0, false, layers);
+  return plan_for_lengths(c, std::vector<int>(c->len.begin(), c->len.end()), layers);
 }
 
-// The same plan for rows of the given lengths (before the step's append);
-// group: query columns per kv-head of an item (0: the model's q-heads per kv-head).
-// pad: every item counts at least the chunk length of the unconstrained plan
-// (at most kMaxSplitPages / 2 pages), so that a run of short items does not
-// force small chunks when a wave can stage few segments.
+// The same plan for rows of the given lengths (before the step's append).
+// groups: the prefill's token groups per sequence, each a wave of every chunk and
+// kv-head (k_attn_prefill; 0: decode).
+// A prefill wave computes for long on a page, so its chunks make whole rounds
+// of waves (a round and a bit would leave most of the chip idle in the second),
+// but hold at least 4 pages, below which a wave's start and its partial states
+// outweigh its pages; longest: the longest chunks instead, for the fewest
+// partial states.
 // layers: layers per launch. Their waves share the chip, so each layer is cut
 // into fewer chunks: whole rounds of waves over all layers, at about 32 pages per
 // chunk or more (a wave's start and its partial states weigh less in a longer
@@ -348,37 +350,32 @@ AttnPlan plan_attention(const pced_ctx* c, int layers) {
 // per layer, each cut for a round of its own, 11.0 ms. Where a layer is short the
 // launches themselves weigh most: 16 layers over 8 caches of 256 to 1024 tokens,
 // 2.1 -> 1.36 ms for eight steps.
-AttnPlan plan_for_lengths(const pced_ctx* c, const std::vector<int>& lens, int group, bool pad, int layers) {
+AttnPlan plan_for_lengths(const pced_ctx* c, const std::vector<int>& lens, int layers, int groups, bool longest) {
   const int S = (int)lens.size();
+  std::vector<long> pre(S + 1, 0);
+  for (int s = 0; s < S; ++s) pre[s + 1] = pre[s] + ceil_div(lens[s] + 1, kPage);
+  const long P = pre[S];
   long cap = std::max<long>(1, (long)c->num_cus * c->attn_waves_per_cu / c->cfg.n_kv_heads);
   if (layers > 1) {
-    long pages = 0;
-    for (int s = 0; s < S; ++s) pages += ceil_div(lens[s] + 1, kPage);
-    const long rounds = std::max<long>(1, pages * layers / (cap * 32));
+    const long rounds = std::max<long>(1, P * layers / (cap * 32));
     cap = std::max<long>(1, cap * rounds / layers);
   }
-  if (c->cfg.max_attn_chunks > 0) cap = std::min<long>(cap, c->cfg.max_attn_chunks);
-  auto first_c = [&](long P) { return std::max<long>(std::min(cap, P), ceil_div(P, (long)kMaxSplitPages)); };
-  int min_pages = 1;
-  if (pad && S > 0) {
-    long P0 = 0;
-    for (int s = 0; s < S; ++s) P0 += ceil_div(lens[s] + 1, kPage);
-    min_pages = (int)std::min<long>(kMaxSplitPages / 2, ceil_div(P0, first_c(P0)));
+  if (groups > 0) {
+    cap = std::max<long>(1, (long)c->num_cus * kPrefillWaves / (c->cfg.n_kv_heads * groups));
+    cap *= ceil_div(P, cap * kMaxSplitPages);
+    cap = longest ? 1 : std::min(cap, std::max<long>(1, P / 4));
   }
-  std::vector<long> pre(S + 1, 0);
-  for (int s = 0; s < S; ++s) pre[s + 1] = pre[s] + std::max(min_pages, ceil_div(lens[s] + 1, kPage));
-  const long P = pre[S];
-  long C = first_c(P);
-  // bf16: the later segments' q rows of a chunk are staged by its wave in LDS
-  const int per_seg_units = (group > 0 ? group : c->G) * c->cfg.head_dim / 8;
-  const int seg_limit = c->bf16 ? std::min(kMaxSeg, 1 + 64 * kStageUnits / per_seg_units) : kMaxSeg;
+  if (c->cfg.max_attn_chunks > 0) cap = std::min<long>(cap, c->cfg.max_attn_chunks);
+  long C = std::max<long>(std::min(cap, P), ceil_div(P, (long)kMaxSplitPages));
+  // bf16 decode: the later segments' q rows of a chunk are staged by its wave in LDS
+  const int per_seg_units = c->G * c->cfg.head_dim / 8;
+  const int seg_limit = c->bf16 && groups == 0 ? std::min(kMaxSeg, 1 + 64 * kStageUnits / per_seg_units) : kMaxSeg;
   AttnPlan plan;
   for (;;) {
     plan_stats(pre, P, C, &plan);
     if (plan.max_seg <= seg_limit || C >= P) break;
     C = std::min(P, C + std::max<long>(1, C / 16));
   }
-  plan.min_pages = min_pages;
   return plan;
 }
 
@@ -652,9 +649,9 @@ ModelLayout model_layout(const pced_config& c) {
 // step has one row per sequence; a prefill chunk has one row per (sequence,
 // suffix token), each a virtual sequence that shares its base sequence's pages
 // and ends at its own token (so attention over it is causal by construction).
-// The prefill's attention runs on groups of consecutive suffix tokens of one
-// sequence instead (the att_* members): one plan item per group, ending at its
-// last token, whose tokens take their own query columns and causal ends.
+// The prefill's attention is planned by whole sequences instead (the att_*
+// members), each ending at its last token; groups of a sequence's suffix tokens
+// take query columns and causal ends of their own.
 struct FwdRows {
   int M = 0;
   std::vector<int> lens;             // host: length of each row's sequence before its append
@@ -678,11 +675,11 @@ struct FwdRows {
   size_t proj_cols = 0;              // slices x columns per row of the projection partials
   float* attn_out = nullptr;
   float* rho_rows = nullptr;         // device [M]: the many-row epilogues' row scales
-  // The attention's items: the rows (att_tq = 1), or for the prefill groups of
-  // att_tq suffix tokens of one sequence (att_T tokens per sequence), each item
-  // ending at its last token; the kernels give a group's tokens their own
-  // query columns and causal ends.
-  int att_n = 0, att_tq = 1, att_T = 1;
+  // The attention's sequences: the rows, or for the prefill the
+  // sequences, whose att_T rows each go in att_ng groups of att_tq tokens; the
+  // kernels give a group's tokens their own query columns and causal ends.
+  int att_n = 0, att_ng = 1, att_tq = 1, att_T = 1;
+  AttnPlan att_plan;                 // of att_lens
   std::vector<int> att_lens;
   const int32_t* att_len0 = nullptr;
   const int32_t* att_pt = nullptr;
@@ -732,10 +729,10 @@ pced_status run_model_forward(pced_ctx* c, const char* model, const FwdRows& R, 
   const int M = R.M, H = cfg.hidden, D = cfg.head_dim;
   const int qd = cfg.n_q_heads * D, kd = cfg.n_kv_heads * D;
   const int AG = c->G * R.att_tq;  // query columns per kv-head of an attention item
-  const AttnPlan plan = plan_for_lengths(c, R.att_lens, AG, R.att_tq > 1);
+  const AttnPlan& plan = R.att_plan;
   if (plan.chunks > c->lay.max_work) return fail(PCED_ERR_CAPACITY, "attention plan exceeds workspace");
   // (the partial buffers hold part_slots states of G columns)
-  if ((size_t)R.att_n * cfg.n_kv_heads * plan.max_parts * AG > R.part_slots * c->G)
+  if ((size_t)R.att_n * R.att_ng * cfg.n_kv_heads * plan.max_parts * AG > R.part_slots * c->G)
     return fail(PCED_ERR_CAPACITY, "attention partial states exceed workspace");
   // per-layer pool offset when the queries are not laid out per layer (the
   // kernels then address layer 0 of the offset pools)
@@ -759,7 +756,6 @@ pced_status run_model_forward(pced_ctx* c, const char* model, const FwdRows& R, 
   ap.t = c->t;
   ap.n_chunks = plan.chunks;
   ap.total_pages = (int)plan.pages;
-  ap.min_pages = plan.min_pages;
   {
     ProfScope ps(c, PCED_PROF_APPEND, 0, 0);
     HIP_OK(launch_append(ap, true, st, ps.timing()));
@@ -953,6 +949,7 @@ FwdRows decode_rows(pced_ctx* c, const int32_t* in_tok, const pced_step_out* ext
   R.page_table = c->at<int32_t>(c->lay.page_table);
   R.att_n = R.M;
   R.att_lens = R.lens;
+  R.att_plan = plan_attention(c, 1);
   R.att_len0 = R.len0;
   R.att_pt = R.page_table;
   R.att_nparts = c->at<int32_t>(c->lay.nparts);
@@ -1009,28 +1006,30 @@ pced_status run_prefill_chunk(pced_ctx* c, const char* model, const int32_t* tok
     for (int i = 0; i < T; ++i) R.lens[(size_t)s * T + i] = c->len[s] + i;
   R.len0 = pm.len0_out;
   R.page_table = pm.page_table_out;
-  // attention items: groups of tq tokens of a sequence fill the matrix cores' 16
-  // query columns per kv-head (tq x q-heads per kv-head), so each group reads
-  // the sequence's pages once for all its tokens
-  // (fewer tokens per group where the partial states of the plan would not fit)
+  // attention: groups of tq tokens of a sequence, at most kPrefillTiles x 16
+  // query columns per kv-head (tq x q-heads per kv-head) and all of about the
+  // same size, so each group reads the sequence's pages once for all its tokens
+  // (the longest chunks, then fewer tokens per group, where the partial states
+  // of the plan would not fit)
   const size_t part_slots = (size_t)c->lay.pf_rows * cfg.n_kv_heads * kPrefillParts;
-  int tq = std::max(1, std::min(T, kMaxGroup / c->G)), ng = 0;
-  for (;; tq = (tq + 1) / 2) {
+  R.att_lens.resize(S);  // keys of each sequence's last token
+  for (int s = 0; s < S; ++s) R.att_lens[s] = c->len[s] + T - 1;
+  int tq = std::max(1, std::min(T, kPrefillTiles * kMaxGroup / c->G)), ng = 0;
+  for (bool longest = false;; longest = !longest) {
+    if (!longest) tq = ceil_div(T, ceil_div(T, tq));
     ng = ceil_div(T, tq);
-    R.att_lens.resize((size_t)S * ng);
-    for (int s = 0; s < S; ++s)
-      for (int j = 0; j < ng; ++j) R.att_lens[(size_t)s * ng + j] = c->len[s] + std::min(tq * j + tq, T) - 1;
-    if (tq == 1) break;
-    const AttnPlan p = plan_for_lengths(c, R.att_lens, c->G * tq, true);
-    if ((size_t)S * ng * cfg.n_kv_heads * p.max_parts * tq <= part_slots) break;
+    R.att_plan = plan_for_lengths(c, R.att_lens, 1, ng, longest);
+    if ((size_t)S * ng * cfg.n_kv_heads * R.att_plan.max_parts * tq <= part_slots || (longest && tq == 1)) break;
+    if (longest) tq = (tq + 1) / 2;
   }
   PrefillMetaArgs gm = pm;
   gm.len0_out = c->at<int32_t>(c->lay.pf_glen0);
   gm.page_table_out = c->at<int32_t>(c->lay.pf_gpt);
   gm.tok_map = nullptr;
-  gm.tq = tq;
+  gm.tq = T;  // (planned by whole sequences)
   HIP_OK(launch_prefill_meta(gm, st));
-  R.att_n = S * ng;
+  R.att_n = S;
+  R.att_ng = ng;
   R.att_tq = tq;
   R.att_T = T;
   R.att_len0 = gm.len0_out;
@@ -1133,7 +1132,6 @@ pced_status run_step(pced_ctx* c, const void* q, const void* k_new, const void* 
   ap.t = c->t;
   ap.n_chunks = plan.chunks;
   ap.total_pages = (int)plan.pages;
-  ap.min_pages = plan.min_pages;
   {
     ProfScope ps(c, PCED_PROF_APPEND, 4.0 * c->S * cfg.n_layers * cfg.n_kv_heads * cfg.head_dim * es, 0);
     HIP_OK(launch_append(ap, c->bf16, st, ps.timing()));

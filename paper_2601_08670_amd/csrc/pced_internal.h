@@ -73,10 +73,10 @@ struct AttnArgs {
   size_t x_layer_bytes;
   int n_seqs, n_layers, layer, n_q_heads, n_kv_heads, group;
   int max_pages, maxpps, t, split_stride, is_last_layer;
-  int kv_reread;            // pages are read by several rows of the launch (prefill): plain loads
-  // prefill only: each item of the plan is a group of tq suffix tokens of one
-  // sequence (tq_T tokens per sequence in the chunk, rows s * tq_T + i), and
-  // `group` counts its tq x (Hq / Hkv) query columns per kv-head
+  int kv_reread;            // prefill (k_attn_prefill): pages are read by several token groups
+  // prefill only: a sequence's tq_T tokens of the chunk (rows s * tq_T + i) in
+  // groups of tq, and `group` counts a token group's tq x (Hq / Hkv) query
+  // columns per kv-head; partial states per (sequence, token group)
   int tq, tq_T;
   float scale_log2;         // log2(e) / sqrt(D)
 };
@@ -94,9 +94,6 @@ struct AppendArgs {
   int32_t* work_pages;
   int n_seqs, n_layers, n_kv_heads, head_dim, max_pages, maxpps, t;
   int n_chunks, total_pages;  // C and P of the balanced plan (P = pages after the append)
-  // Planned pages per sequence are at least min_pages (0, 1: none): the pages
-  // past a sequence's own read its last page again and are masked.
-  int min_pages;
 };
 
 struct LoadArgs {
@@ -228,6 +225,8 @@ enum GemmEpi { kEpiQkv = 0, kEpiResid = 1, kEpiSwiglu = 2 };
 constexpr int kProjMaxRows = 128;  // rows of the projection kernels (more: the library GEMM)
 constexpr int kProjMaxSplit = 16;  // K slices of a projection (partial buffer sized for this many)
 constexpr int kPrefillRows = 2304;  // (sequence, suffix token) rows of one prefill chunk, at least
+constexpr int kPrefillTiles = 2;   // 16-column query tiles of a prefill token group, at most
+constexpr int kPrefillWaves = 8;   // waves per compute unit, and at most per block, of the prefill attention (its registers)
 constexpr int kPrefillParts = 8;   // attention partial states per prefill row and kv-head
 struct GemmArgs {
   const void* w;            // packed tiles of this projection

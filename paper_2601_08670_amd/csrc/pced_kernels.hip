@@ -29,6 +29,8 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));  // at any float's address
 
 constexpr float kNegInf = -INFINITY;
@@ -231,7 +233,7 @@ __global__ __launch_bounds__(128) void k_append(AppendArgs a) {
   if ((int)blockIdx.x >= n_app) {
     const int s = blockIdx.x - n_app;
     const long P = a.total_pages, C = a.n_chunks;
-    auto pages_of = [&](int r) { return max(a.min_pages, (a.len0[r] + a.t + 1 + kPage - 1) / kPage); };
+    auto pages_of = [&](int r) { return (a.len0[r] + a.t + 1 + kPage - 1) / kPage; };
     // first global page of this sequence: sum over earlier sequences; the page
     // counts of the kMaxSeg sequences just before s also go to LDS for the walk
     // back below (one round of loads instead of a chain of dependent ones)
@@ -248,7 +250,7 @@ __global__ __launch_bounds__(128) void k_append(AppendArgs a) {
     for (int o = 32; o >= 1; o >>= 1) part += __shfl_xor(part, o);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = part;
     const int len = a.len0[s] + a.t + 1;
-    const int ps_own = (len + kPage - 1) / kPage, ps = max(a.min_pages, ps_own);
+    const int ps = (len + kPage - 1) / kPage;
     __syncthreads();
     const long pre = red[0] + red[1];
     const int c0 = chunk_of(pre, P, C), c1 = chunk_of(pre + ps - 1, P, C);
@@ -280,7 +282,7 @@ __global__ __launch_bounds__(128) void k_append(AppendArgs a) {
     for (int p = threadIdx.x; p < ps; p += blockDim.x) {
       const long u = pre + p;
       const int c = chunk_of(u, P, C);
-      a.work_pages[(size_t)c * kMaxSplitPages + (u - chunk_lo(c, P, C))] = pt[min(p, ps_own - 1)];
+      a.work_pages[(size_t)c * kMaxSplitPages + (u - chunk_lo(c, P, C))] = pt[p];
     }
     return;
   }
@@ -354,28 +356,20 @@ __global__ __launch_bounds__(128) void k_append(AppendArgs a) {
 
 // ----------------------------------------------------------- decode attention
 
-// Prefill token groups (a.tq tokens per plan item): item v is token group
-// v % ng of sequence v / ng (ng = ceil(tq_T / tq)); of its a.group columns per
-// kv-head g, column c is token c / gk of the group and q-head g gk + c % gk
-// (gk = a.group / tq). Returns the physical row (s tq_T + token) and q-head,
-// the token clamped to the group's last, and whether the token exists.
+// Prefill token groups: group j (of ng = ceil(tq_T / tq)) of sequence s holds
+// the chunk's tokens tq j .. tq j + tq - 1 as a.group columns per kv-head g,
+// column c being token c / gk of the group and q-head g gk + c % gk (gk =
+// a.group / tq). Returns the physical row (s tq_T + token) and q-head, the token
+// clamped to the group's last, whether the token exists, and how many positions
+// the column's keys end before those of the sequence's last token.
 struct MqCol {
-  int row, head, valid;
+  int row, head, valid, end_off;
 };
-__device__ __forceinline__ MqCol mq_col(const AttnArgs& a, int v, int g, int c) {
-  const int gk = a.group / a.tq, ng = (a.tq_T + a.tq - 1) / a.tq;
-  const int s = v / ng, j = v - s * ng;
+__device__ __forceinline__ MqCol mq_col(const AttnArgs& a, int s, int j, int g, int c) {
+  const int gk = a.group / a.tq, u = c / gk;
   const int last = min(a.tq, a.tq_T - a.tq * j) - 1;
-  const int u = c / gk;
-  return MqCol{s * a.tq_T + a.tq * j + min(u, last), g * gk + c % gk, u <= last};
-}
-// Tokens between column c's own token and the last token of group v: the
-// column's keys end that many positions before the group's.
-__device__ __forceinline__ int mq_end_off(const AttnArgs& a, int v, int c) {
-  const int gk = a.group / a.tq, ng = (a.tq_T + a.tq - 1) / a.tq;
-  const int j = v % ng;
-  const int last = min(a.tq, a.tq_T - a.tq * j) - 1;
-  return last - min(c / gk, last);
+  const int tok = a.tq * j + min(u, last);
+  return MqCol{s * a.tq_T + tok, g * gk + c % gk, u <= last, a.tq_T - 1 - tok};
 }
 
 // The launch's layer l (of a.launch_layers) as the arguments of a one-layer launch.
@@ -391,17 +385,9 @@ __device__ __forceinline__ void select_layer(AttnArgs& a, int l) {
 
 // Write 4 consecutive output dims of one q-head: fp32 debug copy, the layer
 // output in the storage type, and (last layer) the fp32 value of the stored x.
-// MQ: s is a prefill token group and head = kv-head x group + column (mq_col);
-// columns of tokens past the group's end are not written.
-template <bool BF16, bool MQ = false>
+template <bool BF16>
 __device__ __forceinline__ void write_o4(const AttnArgs& a, int s, int head, int d, int D, float4 o) {
   const int Hq = a.n_q_heads;
-  if constexpr (MQ) {
-    const MqCol m = mq_col(a, s, head / a.group, head % a.group);
-    if (!m.valid) return;
-    s = m.row;
-    head = m.head;
-  }
   const size_t xo = (size_t)s * Hq * D + (size_t)head * D + d;
   if (a.attn_out) {
     float4* p = (float4*)(a.attn_out + (((size_t)s * a.n_layers + a.layer) * Hq + head) * D + d);
@@ -419,6 +405,12 @@ __device__ __forceinline__ void write_o4(const AttnArgs& a, int s, int head, int
     *(float4*)((float*)a.x_out + xo) = o;
     if (a.is_last_layer && a.hidden_out) *(float4*)(a.hidden_out + xo) = o;
   }
+}
+
+// Write 4 consecutive output dims of a prefill column (bf16 layer output only).
+__device__ __forceinline__ void write_x4(const AttnArgs& a, const MqCol& m, int d, int D, float4 o) {
+  *(uint2*)((uint16_t*)a.x_out + ((size_t)m.row * a.n_q_heads + m.head) * D + d) =
+      make_uint2(f2bf(o.x) | (f2bf(o.y) << 16), f2bf(o.z) | (f2bf(o.w) << 16));
 }
 
 // Merge of a sequence's split partial states:
@@ -558,9 +550,9 @@ __global__ __launch_bounds__(64) void k_attn_combine_bf16(AttnArgs a) {
   merge_item<D>(a, R, acc, a.part_ml, s, g, h, n, a.layer, a.is_last_layer != 0, lane);
 }
 
-// The merge for the prefill's token groups, whose items are many and mostly
-// split in a few parts: one wave per (item, kv-head), each lane merging whole
-// 8-dim units (column h, dims d .. d+7) over the parts in order, with the same
+// The merge for the prefill's token groups (items), which are many and mostly
+// split in a few parts: one wave per 64 units of an (item, kv-head), a unit being
+// 8 dims of a column, which a lane merges over the parts in order, with the same
 // formula as above (m* = max_j m_j, weights l_j 2^(m_j - m*) on the stored
 // normalised outputs) and no cross-lane traffic. Parts of a column without keys
 // hold l = 0 and zeros.
@@ -569,51 +561,37 @@ __global__ __launch_bounds__(256) void k_attn_combine_mq(AttnArgs a) {
 #pragma clang fp contract(off)
   const int lane = threadIdx.x & 63;
   const int G = a.group, Hkv = a.n_kv_heads;
-  const int wv = blockIdx.x * 4 + (int)(threadIdx.x >> 6);
-  if (wv >= a.n_seqs * Hkv) return;
-  const int s = wv / Hkv, g = wv - s * Hkv;
+  const int per = (G * (D / 8) + 63) / 64;  // waves of an (item, kv-head)
+  const int wu = blockIdx.x * 4 + (int)(threadIdx.x >> 6), wv = wu / per;
+  const int ng = (a.tq_T + a.tq - 1) / a.tq;
+  if (wv >= a.n_seqs * ng * Hkv) return;
+  const int it = wv / Hkv, g = wv - it * Hkv, s = it / ng;
   const int n = a.nparts[s];
   if (n <= 1) return;  // written directly by the attention kernel
   const size_t w0 = (size_t)wv * a.split_stride;
   const uint16_t* acc = (const uint16_t*)a.part_acc;
-  for (int u = lane; u < G * (D / 8); u += 64) {
-    const int h = u / (D / 8), d = 8 * (u % (D / 8));
-    float mx = kNegInf;
-    for (int j = 0; j < n; ++j) mx = fmaxf(mx, a.part_ml[((w0 + j) * G + h) * 2]);
-    float den = 0.f, num[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int j = 0; j < n; ++j) {
-      const float2 ml = *(const float2*)(a.part_ml + ((w0 + j) * G + h) * 2);
-      const uint4 v = *(const uint4*)(acc + ((w0 + j) * G + h) * D + d);
-      const float wt = ml.y * exp2f(ml.x - mx);
-      den += wt;
-      const uint32_t b[4] = {v.x, v.y, v.z, v.w};
+  const int u = (wu - wv * per) * 64 + lane;
+  if (u >= G * (D / 8)) return;
+  // elements e0 .. e0 + 7 of column h, in the accumulators' order (k_attn_prefill):
+  // dims d .. d + 3 and d + 16 .. d + 19
+  const int h = u / (D / 8), e0 = 8 * (u % (D / 8)), d = 4 * (e0 % (D / 4)) + 4 * (e0 / (D / 4));
+  float mx = kNegInf;
+  for (int j = 0; j < n; ++j) mx = fmaxf(mx, a.part_ml[((w0 + j) * G + h) * 2]);
+  float den = 0.f, num[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  for (int j = 0; j < n; ++j) {
+    const float2 ml = *(const float2*)(a.part_ml + ((w0 + j) * G + h) * 2);
+    const uint4 v = *(const uint4*)(acc + ((w0 + j) * G + h) * D + e0);
+    const float wt = ml.y * exp2f(ml.x - mx);
+    den += wt;
+    const uint32_t b[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-      for (int e = 0; e < 8; ++e) num[e] = fmaf(bf2f((b[e >> 1] >> (16 * (e & 1))) & 0xFFFFu), wt, num[e]);
-    }
-    const MqCol m = mq_col(a, s, g, h);
-    if (!m.valid) continue;
-    const float inv = 1.0f / den;
-    float o[8];
-    uint32_t bb[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      o[e] = num[e] * inv;
-      bb[e] = f2bf(o[e]);
-    }
-    const size_t row = (size_t)m.row * a.n_q_heads + m.head;
-    *(uint4*)((uint16_t*)a.x_out + row * D + d) = make_uint4(bb[0] | (bb[1] << 16), bb[2] | (bb[3] << 16),
-                                                            bb[4] | (bb[5] << 16), bb[6] | (bb[7] << 16));
-    if (a.attn_out) {
-      float* p = a.attn_out + (((size_t)m.row * a.n_layers + a.layer) * a.n_q_heads + m.head) * D + d;
-      *(float4*)p = make_float4(o[0], o[1], o[2], o[3]);
-      *(float4*)(p + 4) = make_float4(o[4], o[5], o[6], o[7]);
-    }
-    if (a.is_last_layer && a.hidden_out) {
-      float* p = a.hidden_out + row * D + d;
-      *(float4*)p = make_float4(bf2f(bb[0]), bf2f(bb[1]), bf2f(bb[2]), bf2f(bb[3]));
-      *(float4*)(p + 4) = make_float4(bf2f(bb[4]), bf2f(bb[5]), bf2f(bb[6]), bf2f(bb[7]));
-    }
+    for (int e = 0; e < 8; ++e) num[e] = fmaf(bf2f((b[e >> 1] >> (16 * (e & 1))) & 0xFFFFu), wt, num[e]);
   }
+  const MqCol m = mq_col(a, s, it - s * ng, g, h);
+  if (!m.valid) return;
+  const float inv = 1.0f / den;
+  write_x4(a, m, d, D, make_float4(num[0] * inv, num[1] * inv, num[2] * inv, num[3] * inv));
+  write_x4(a, m, d + 16, D, make_float4(num[4] * inv, num[5] * inv, num[6] * inv, num[7] * inv));
 }
 
 // fp32: one block per (sequence, kv-head); each thread owns 4 output dims of
@@ -679,12 +657,10 @@ __global__ __launch_bounds__(128) void k_attn_combine_f32(AttnArgs a, int D) {
 // alone, else a partial state for the merge kernel) and continues with the next
 // sequence's q, staged in LDS by the prologue, and a fresh softmax state; the
 // page stream itself does not stop at a switch.
-template <int D, int RING, bool STREAM>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RING <= 4 ? 2 : 1, RING <= 4 ? 8 : 1))) void k_attn_bf16(AttnArgs a) {
+template <int D, int RING>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_attn_bf16(AttnArgs a) {
   constexpr int NC = D / 32;
   constexpr int NJ = D / 16;
-  // the prefill launch (pages re-read: plain loads) runs on token groups (mq_col)
-  constexpr bool MQ = !STREAM;
   // q rows of the chunk's later segments, [segment - 1][G][D]
   __shared__ __align__(16) uint16_t q_lds[kStageUnits * 64 * 8];
   // finished segments' softmax states, [segment][G][D] accumulators and
@@ -706,14 +682,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RING <= 4 ? 
   const int4 d1 = sd[2 * min(lane, kMaxSeg - 1) + 1];
   const int4 e0 = sd[0], e1 = sd[1];  // segment 0, uniform loads
   int cur_s = e0.x, cur_poff = e0.z, cur_end = e0.w, cur_j = e1.x, cur_parts = e1.y;
-  // Token groups: this lane's column ends mq_end_off keys before the group's
-  // last token, so its keys in the segment end at min(segment end, keys of the
-  // sequence - offset); a column may have none in a later split of its sequence.
-  int col_end = cur_end;
-  if constexpr (MQ) col_end = min(cur_end, e1.z - mq_end_off(a, cur_s, min(col, G - 1)));
-  // (finite start in the grouped launch: a column without keys so far gives
-  // weights 2^(-inf - m0) = 0 rather than NaN)
-  constexpr float m0 = MQ ? -1e30f : kNegInf;
 
   const size_t q_layer = (size_t)a.layer * a.n_q_heads + (size_t)g * G;
   bf16x8 qop[NC];
@@ -721,11 +689,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RING <= 4 ? 
     // Columns past the group repeat its last head: their scores and outputs are
     // never stored, and the loads stay unconditional, so waiting for the page
     // ids below does not also wait for these.
-    size_t qrow = (size_t)cur_s * a.n_layers * a.n_q_heads + q_layer + min(col, G - 1);
-    if constexpr (MQ) {
-      const MqCol m = mq_col(a, cur_s, g, min(col, G - 1));
-      qrow = (size_t)m.row * a.n_q_heads + m.head;
-    }
+    const size_t qrow = (size_t)cur_s * a.n_layers * a.n_q_heads + q_layer + min(col, G - 1);
     const uint16_t* q = (const uint16_t*)a.q + qrow * D;
 #pragma unroll
     for (int i = 0; i < NC; ++i) qop[i] = as_bf16x8(*(const uint4*)(q + 32 * i + 8 * quad));
@@ -746,8 +710,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RING <= 4 ? 
     const size_t t0 = (lay + (size_t)phys * Hkv) * tile16;
 #pragma unroll
     for (int cc = 0; cc < NC; ++cc) {
-      kb[cc] = ld_w<STREAM>(&kp[t0 + cc * 64 + lane]);
-      vb[cc] = ld_w<STREAM>(&vp[t0 + cc * 64 + lane]);
+      kb[cc] = ld_w<true>(&kp[t0 + cc * 64 + lane]);
+      vb[cc] = ld_w<true>(&vp[t0 + cc * 64 + lane]);
     }
   };
 
@@ -758,7 +722,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RING <= 4 ? 
   // m_ref per head, shared by the head's four lanes. m_ref (and the accumulators)
   // only move when some score of the page exceeds m_ref + 8, so weights stay
   // <= 2^8 and the common page needs neither cross-lane traffic nor a rescale.
-  float m_ref = m0, l_part = 0.f;
+  float m_ref = kNegInf, l_part = 0.f;
   int k = 0;
   int next_i0 = nseg > 1 ? sd[2].y : 0x7fffffff;
 
@@ -775,8 +739,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RING <= 4 ? 
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
         const float4 v = *(const float4*)(sa + col * D + 16 * j + 4 * quad);
-        write_o4<true, MQ>(a, s, g * G + col, 16 * j + 4 * quad, D,
-                           make_float4(v.x * inv, v.y * inv, v.z * inv, v.w * inv));
+        write_o4<true>(a, s, g * G + col, 16 * j + 4 * quad, D,
+                       make_float4(v.x * inv, v.y * inv, v.z * inv, v.w * inv));
       }
       return;
     }
@@ -785,8 +749,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RING <= 4 ? 
     const size_t w = (size_t)(s * Hkv + g) * a.split_stride + part;
     uint16_t* dst = (uint16_t*)a.part_acc + w * G * D;
     for (int e = 8 * lane; e < G * D; e += 512) {
-      const float l = sm[2 * (e / D) + 1];
-      const float inv = l > 0.f ? 1.0f / l : 0.f;  // (a token-group column with no keys here: zeros)
+      const float inv = 1.0f / sm[2 * (e / D) + 1];
       const float4 v0 = *(const float4*)(sa + e), v1 = *(const float4*)(sa + e + 4);
       uint4 pk;
       pk.x = f2bf(v0.x * inv) | (f2bf(v0.y * inv) << 16);
@@ -838,13 +801,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RING <= 4 ? 
       cur_j = __builtin_amdgcn_readlane(d1.x, k);
       cur_parts = __builtin_amdgcn_readlane(d1.y, k);
       next_i0 = k + 1 < nseg ? __builtin_amdgcn_readlane(d0.y, k + 1) : 0x7fffffff;
-      col_end = cur_end;
-      if constexpr (MQ)
-        col_end = min(cur_end, __builtin_amdgcn_readlane(d1.z, k) - mq_end_off(a, cur_s, min(col, G - 1)));
       const uint16_t* qs = q_lds + ((k - 1) * G + min(col, G - 1)) * D + 8 * quad;
 #pragma unroll
       for (int cc = 0; cc < NC; ++cc) qop[cc] = as_bf16x8(*(const uint4*)(qs + 32 * cc));
-      m_ref = m0;
+      m_ref = kNegInf;
       l_part = 0.f;
 #pragma unroll
       for (int j = 0; j < NJ; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -856,7 +816,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RING <= 4 ? 
     const int tb = (i + cur_poff) * kPage + 4 * quad;  // token of element r = 0 in the sequence
     float z[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) z[r] = (tb + r < col_end) ? sc[r] * a.scale_log2 : kNegInf;
+    for (int r = 0; r < 4; ++r) z[r] = (tb + r < cur_end) ? sc[r] * a.scale_log2 : kNegInf;
     const float zmax = fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]));
     if (__builtin_amdgcn_ballot_w64(zmax > m_ref + 8.0f) != 0) {
       float mx = fmaxf(zmax, __shfl_xor(zmax, 16));
@@ -926,11 +886,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RING <= 4 ? 
     const bool valid = u < n_units;
     const int kk = min(1 + u / per_seg, kMaxSeg - 1), rem = valid ? u % per_seg : 0;
     const int sk = valid ? __shfl(d0.x, kk) : e0.x;
-    size_t qrow = (size_t)sk * a.n_layers * a.n_q_heads + q_layer + rem / (D / 8);
-    if constexpr (MQ) {
-      const MqCol m = mq_col(a, sk, g, rem / (D / 8));
-      qrow = (size_t)m.row * a.n_q_heads + m.head;
-    }
+    const size_t qrow = (size_t)sk * a.n_layers * a.n_q_heads + q_layer + rem / (D / 8);
     return *(const uint4*)((const uint16_t*)a.q + qrow * D + 8 * (rem % (D / 8)));
   };
   stg0 = stage(0);
@@ -2693,6 +2649,227 @@ __global__ __launch_bounds__(256) void k_synth(SynthArgs a) {
   synth_fill<BF16>(a.v_new, row * a.kvdim, base[2], a.kvdim, a.value_scale);
 }
 
+// --------------------------------------------------------- prefill attention
+
+// Prefill attention over the balanced plan of the sequences' pages: a block is
+// (chunk, kv-head), its waves the token groups of the sequence (mq_col, up to
+// 16 NQ query columns each), up to kPrefillWaves of them. The block brings every
+// page once into a ring of NS LDS stages (direct loads, the waves an equal share
+// of LW 1 KiB units each; NS - 1 pages in flight), and every wave uses it for all
+// of its columns:
+//   S^T[16 tok x 16 cols] = K[16 x D] Q^T          (D/32 x 16x16x32 MFMA per tile)
+//   O^T[D x 16 cols]     += V^T[D x 16 tok] P^T    (D/16 x 16x16x16 MFMA per tile)
+//   l[16 cols]           += 1 P^T                  (one more: the softmax sums)
+// A page whose tokens every column sees takes no masks, and the softmax reference
+// moves only when a score exceeds it by 8 (base 2), as in k_attn_bf16. At a page
+// a wave waits for its own loads of it and meets the others at a barrier: then
+// the whole page is in LDS, and all have left the stage that the next loads fill.
+//
+// Bound: the page stream where a sequence has few groups, the matrix cores and
+// the exponentials where it has many.
+// Per layer at 33 caches of 512 to 2048 tokens, 32 / 8 heads of 128: 105 us for
+// a 64-token suffix and 52 us for 16 tokens, where one wave per 16 columns, each
+// reading its pages for itself, took 178 and 95; with pages in registers and two
+// tiles per wave, 143 and 70 (the groups' copies of a page took the loads in
+// flight). The 16x16x32 product over two pages' tokens would halve the second
+// line, but its V operand joins halves of two loads; four tiles per wave need
+// more registers than two waves per SIMD have.
+template <int D, int NQ, int LW>
+__global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_prefill(AttnArgs a) {
+  constexpr int NC = D / 32, NJ = D / 16, U = 2 * NC;  // U: 1 KiB units of a page (K, then V)
+  constexpr int NS = 5, LEAD = NS - 1, WAITN = (LEAD - 1) * LW;
+  static_assert(WAITN < 64, "vmcnt has 6 bits");
+  // separate arrays, so that the compiler can tell the stage being loaded from the one being read
+  __shared__ __align__(16) uint4 ks0[U][64];
+  __shared__ __align__(16) uint4 ks1[U][64];
+  __shared__ __align__(16) uint4 ks2[U][64];
+  __shared__ __align__(16) uint4 ks3[U][64];
+  __shared__ __align__(16) uint4 ks4[U][64];
+  auto stage = [&](auto st_c) __attribute__((always_inline)) -> uint4(*)[64] {
+    constexpr int ST = decltype(st_c)::value;
+    return ST == 0 ? ks0 : ST == 1 ? ks1 : ST == 2 ? ks2 : ST == 3 ? ks3 : ks4;
+  };
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = lane & 15, quad = lane >> 4;
+  const int G = a.group, Hkv = a.n_kv_heads;
+  const int waves = blockDim.x >> 6, ng = (a.tq_T + a.tq - 1) / a.tq, sets = (ng + waves - 1) / waves;
+  const int cs = blockIdx.x / Hkv, g = blockIdx.x % Hkv, c = cs / sets;
+  const bool active = (cs - c * sets) * waves + wave < ng;  // (waves past the last group repeat it and store nothing)
+  const int grp = min((cs - c * sets) * waves + wave, ng - 1);
+  const int2 ci = a.chunk_info[c];
+  const int nseg = ci.x, np = ci.y;
+  // physical page ids, lane k holding the chunk's page k (kMaxSplitPages = 64; entries past np are never used)
+  const int my_pid = a.work_pages[(size_t)c * kMaxSplitPages + lane];
+  const int4* sd = a.seg + (size_t)c * kMaxSeg * 2;
+  const size_t lay = (size_t)a.layer * a.max_pages * Hkv + g;
+  constexpr size_t tile_bytes = (size_t)kPage * D * 2;
+  auto load = [&](auto st_c, int i) __attribute__((always_inline)) {
+    uint4(*dst)[64] = stage(st_c);
+    const int phys = __builtin_amdgcn_readlane(my_pid, min(i, np - 1));
+    const size_t off = (lay + (size_t)phys * Hkv) * tile_bytes;
+    // past the chunk's end: descriptors of no range, whose loads cost no memory access
+    const int range = i < np ? (int)tile_bytes : 0;
+#pragma unroll
+    for (int b = 0; b < LW; ++b) {
+      const int u = min(wave + waves * b, U - 1);
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)((const char*)(u < NC ? a.kpool : a.vpool) + off), 0, range, 0x00020000);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)&dst[u][0], 16, 16 * lane, 1024 * (u < NC ? u : u - NC), 0, 0);
+    }
+  };
+
+  int k = 0, s = 0, poff = 0, end = 0, part = 0, parts = 0, full_end = 0, next_i0 = 0;
+  bf16x8 qop[NQ][NC];
+  int col_end[NQ];  // keys of the lane's column in this segment end here
+  f32x4 acc[NQ][NJ], l[NQ];
+  float m_ref[NQ];
+  auto open = [&]() __attribute__((always_inline)) {  // segment k
+    const int4 e0 = sd[2 * k], e1 = sd[2 * k + 1];
+    s = e0.x, poff = e0.z, end = e0.w, part = e1.x, parts = e1.y;
+    next_i0 = k + 1 < nseg ? sd[2 * k + 2].y : 0x7fffffff;
+    // every column sees the keys before full_end (the group's first token has the fewest)
+    full_end = min(end, e1.z - mq_col(a, s, grp, g, 0).end_off);
+#pragma unroll
+    for (int t = 0; t < NQ; ++t) {
+      const MqCol m = mq_col(a, s, grp, g, min(16 * t + col, G - 1));  // (columns past the group: never stored)
+      const uint16_t* q = (const uint16_t*)a.q + ((size_t)m.row * a.n_q_heads + m.head) * D;
+#pragma unroll
+      for (int cc = 0; cc < NC; ++cc) qop[t][cc] = as_bf16x8(*(const uint4*)(q + 32 * cc + 8 * quad));
+      col_end[t] = min(end, e1.z - m.end_off);
+      // (finite: a column without keys so far gives weights 2^(-inf - m_ref) = 0 rather than NaN)
+      m_ref[t] = -1e30f;
+      l[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  };
+  // The finished segment: the final output when the sequence lies in this chunk
+  // alone, else the normalised output in bf16 and (m, l) for the merge. A column
+  // of a partial state is in the accumulators' order, so that a lane writes 64
+  // (D = 128) consecutive bytes: element (D/4) quad + 4 j + r is dim 16 j + 4 quad + r.
+  auto close = [&]() __attribute__((always_inline)) {
+    const size_t w = ((size_t)(s * ng + grp) * Hkv + g) * a.split_stride + part;
+#pragma unroll
+    for (int t = 0; t < NQ; ++t) {
+      const int cq = 16 * t + col;
+      const MqCol m = mq_col(a, s, grp, g, cq);
+      if (!active || cq >= G || !m.valid) continue;
+      const float inv = l[t][0] > 0.f ? 1.0f / l[t][0] : 0.f;  // (a column with no keys here: zeros)
+      uint16_t* dst = (uint16_t*)a.part_acc + (w * G + cq) * D + (D / 4) * quad;
+#pragma unroll
+      for (int j = 0; j < NJ; j += 2) {
+        const float4 o0 = make_float4(acc[t][j][0] * inv, acc[t][j][1] * inv, acc[t][j][2] * inv, acc[t][j][3] * inv);
+        const float4 o1 = make_float4(acc[t][j + 1][0] * inv, acc[t][j + 1][1] * inv, acc[t][j + 1][2] * inv, acc[t][j + 1][3] * inv);
+        if (parts == 1) {
+          write_x4(a, m, 16 * j + 4 * quad, D, o0);
+          write_x4(a, m, 16 * j + 16 + 4 * quad, D, o1);
+        } else {
+          *(uint4*)(dst + 4 * j) = make_uint4(f2bf(o0.x) | (f2bf(o0.y) << 16), f2bf(o0.z) | (f2bf(o0.w) << 16),
+                                              f2bf(o1.x) | (f2bf(o1.y) << 16), f2bf(o1.z) | (f2bf(o1.w) << 16));
+        }
+      }
+      if (parts > 1 && quad == 0) *(float2*)(a.part_ml + (w * G + cq) * 2) = make_float2(m_ref[t], l[t][0]);
+    }
+  };
+
+  auto compute = [&](uint4(*src)[64], int i) __attribute__((always_inline)) {
+    if (i == next_i0) {
+      close();
+      ++k;
+      open();
+      wait_vmcnt<0>();  // q is here (rare: once per further sequence)
+    }
+    f32x4 sc[NQ];
+#pragma unroll
+    for (int t = 0; t < NQ; ++t) sc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int cc = 0; cc < NC; ++cc) {
+      const bf16x8 kv = as_bf16x8(src[cc][lane]);
+#pragma unroll
+      for (int t = 0; t < NQ; ++t) sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kv, qop[t][cc], sc[t], 0, 0, 0);
+    }
+    uint4 vc[NC];
+#pragma unroll
+    for (int cc = 0; cc < NC; ++cc) vc[cc] = src[NC + cc][lane];
+    const int t0 = (i + poff) * kPage;  // the page's first token in the sequence
+    if (t0 + kPage > full_end) {
+      const int tb = t0 + 4 * quad;  // token of element r = 0
+#pragma unroll
+      for (int t = 0; t < NQ; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sc[t][r] = tb + r < col_end[t] ? sc[t][r] : kNegInf;
+      // slots past the segment's end hold stale or never-written bits; their
+      // weights are 0, but 0 * NaN is NaN inside the matrix core
+      const uint32_t m01 = (tb + 0 < end ? 0x0000FFFFu : 0u) | (tb + 1 < end ? 0xFFFF0000u : 0u);
+      const uint32_t m23 = (tb + 2 < end ? 0x0000FFFFu : 0u) | (tb + 3 < end ? 0xFFFF0000u : 0u);
+#pragma unroll
+      for (int cc = 0; cc < NC; ++cc) {
+        vc[cc].x &= m01; vc[cc].y &= m23; vc[cc].z &= m01; vc[cc].w &= m23;
+      }
+    }
+    float zmax[NQ];
+    bool move = false;
+#pragma unroll
+    for (int t = 0; t < NQ; ++t) {
+      zmax[t] = fmaxf(fmaxf(sc[t][0], sc[t][1]), fmaxf(sc[t][2], sc[t][3])) * a.scale_log2;
+      move |= zmax[t] > m_ref[t] + 8.0f;
+    }
+    if (__builtin_amdgcn_ballot_w64(move) != 0) {
+#pragma unroll
+      for (int t = 0; t < NQ; ++t) {
+        float mx = fmaxf(zmax[t], __shfl_xor(zmax[t], 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float m_new = fmaxf(m_ref[t], mx), alpha = exp2f(m_ref[t] - m_new);
+        l[t] *= alpha;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[t][j] *= alpha;
+        m_ref[t] = m_new;
+      }
+    }
+    const s16x4 ones = {0x3F80, 0x3F80, 0x3F80, 0x3F80};
+#pragma unroll
+    for (int t = 0; t < NQ; ++t) {
+      // (v_exp_f32: results below 2^-126 are 0, as good as any such weight beside one of 2^-8 or more)
+      f32x2 p01, p23;
+      p01[0] = __builtin_amdgcn_exp2f(fmaf(sc[t][0], a.scale_log2, -m_ref[t]));
+      p01[1] = __builtin_amdgcn_exp2f(fmaf(sc[t][1], a.scale_log2, -m_ref[t]));
+      p23[0] = __builtin_amdgcn_exp2f(fmaf(sc[t][2], a.scale_log2, -m_ref[t]));
+      p23[1] = __builtin_amdgcn_exp2f(fmaf(sc[t][3], a.scale_log2, -m_ref[t]));
+      const s16x4 pop = __builtin_bit_cast(
+          s16x4, make_uint2(__builtin_bit_cast(uint32_t, __builtin_convertvector(p01, bf16x2)),
+                            __builtin_bit_cast(uint32_t, __builtin_convertvector(p23, bf16x2))));
+      // (the normaliser sums exactly the rounded weights)
+      l[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ones, pop, l[t], 0, 0, 0);
+#pragma unroll
+      for (int cc = 0; cc < NC; ++cc) {
+        const s16x4 va = __builtin_bit_cast(s16x4, make_uint2(vc[cc].x, vc[cc].y));
+        const s16x4 vb = __builtin_bit_cast(s16x4, make_uint2(vc[cc].z, vc[cc].w));
+        acc[t][2 * cc] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(va, pop, acc[t][2 * cc], 0, 0, 0);
+        acc[t][2 * cc + 1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vb, pop, acc[t][2 * cc + 1], 0, 0, 0);
+      }
+    }
+  };
+
+  open();
+  static_for<LEAD>([&](auto jc) __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);  // in this order, after q: the waits count on it
+    load(jc, (int)decltype(jc)::value);
+  });
+  for (int i0 = 0; i0 < np; i0 += NS)
+    static_for<NS>([&](auto jc) __attribute__((always_inline)) {
+      constexpr int ST = decltype(jc)::value;
+      const int i = i0 + ST;
+      wait_vmcnt<WAITN>();
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      load(std::integral_constant<int, (ST + LEAD) % NS>{}, i + LEAD);
+      __builtin_amdgcn_sched_barrier(0);
+      if (i < np) compute(stage(jc), i);
+    });
+  wait_vmcnt<0>();  // the loads past the end (into LDS) have landed
+  close();
+}
+
 // ------------------------------------------------------------ decoder stack
 
 constexpr int kProjWaves = 8;  // waves per projection block
@@ -3206,19 +3383,39 @@ hipError_t launch_append(const AppendArgs& a, bool bf16, hipStream_t st, const T
   return go(k_append<false>, dim3(blocks), dim3(128), 0, st, t0(tm), t1(tm), a);
 }
 
+// blocks of `waves` waves, each loading ceil(units of a page / waves) units (a few
+// more where that is no power of two: the last unit again)
+template <int D, int NQ>
+static hipError_t go_prefill(const AttnArgs& a, dim3 grid, int waves, hipStream_t st, const Timing* tm) {
+  constexpr int U = D / 16;
+  const dim3 block(64 * waves);
+  const int lw = (U + waves - 1) / waves;
+  if (lw == 1) return go(k_attn_prefill<D, NQ, 1>, grid, block, 0, st, t0(tm), t1(tm), a);
+  if (lw == 2) return go(k_attn_prefill<D, NQ, 2>, grid, block, 0, st, t0(tm), t1(tm), a);
+  if (U == 4 || lw <= 4) return go(k_attn_prefill<D, NQ, 4>, grid, block, 0, st, t0(tm), t1(tm), a);
+  return go(k_attn_prefill<D, NQ, U>, grid, block, 0, st, t0(tm), t1(tm), a);
+}
+
 hipError_t launch_attn(const AttnArgs& a, int head_dim, bool bf16, hipStream_t st, const Timing* tm) {
   const int n_blocks = a.n_chunks * a.n_kv_heads * a.launch_layers;
   if (bf16) {
-    const bool s = !a.kv_reread;
+    if (a.kv_reread) {  // prefill: tiles of 16 query columns per wave
+      static_assert(kPrefillTiles == 2, "instances below");
+      if (a.group > 16 * kPrefillTiles) return hipErrorInvalidValue;
+      const int ng = (a.tq_T + a.tq - 1) / a.tq, sets = (ng + kPrefillWaves - 1) / kPrefillWaves;
+      const dim3 grid((unsigned)(a.n_chunks * a.n_kv_heads * sets));
+      const int waves = (ng + sets - 1) / sets;
+      if (head_dim == 128)
+        return a.group <= 16 ? go_prefill<128, 1>(a, grid, waves, st, tm) : go_prefill<128, 2>(a, grid, waves, st, tm);
+      if (head_dim == 64)
+        return a.group <= 16 ? go_prefill<64, 1>(a, grid, waves, st, tm) : go_prefill<64, 2>(a, grid, waves, st, tm);
+      return hipErrorInvalidValue;
+    }
     // decode at head dim 128: a 3-page ring (two pages in flight) measured
     // faster than 4 pages (33.7 against 34.2 us at 33 caches x 32 layers): fewer
     // loads past each chunk's end for the same two waves per SIMD
-    if (head_dim == 128)
-      return s ? go(k_attn_bf16<128, 3, true>, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a)
-               : go(k_attn_bf16<128, 4, false>, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a);
-    if (head_dim == 64)
-      return s ? go(k_attn_bf16<64, 4, true>, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a)
-               : go(k_attn_bf16<64, 4, false>, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a);
+    if (head_dim == 128) return go(k_attn_bf16<128, 3>, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a);
+    if (head_dim == 64) return go(k_attn_bf16<64, 4>, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a);
     return hipErrorInvalidValue;
   }
   return head_dim <= 64 ? go(k_attn_f32<1>, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a, head_dim)
@@ -3228,8 +3425,8 @@ hipError_t launch_attn(const AttnArgs& a, int head_dim, bool bf16, hipStream_t s
 int attn_blocks_per_cu(int head_dim, bool bf16) {
   int n = 0;
   hipError_t e;
-  if (bf16 && head_dim == 128) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_attn_bf16<128, 3, true>, 64, 0);
-  else if (bf16) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_attn_bf16<64, 4, true>, 64, 0);
+  if (bf16 && head_dim == 128) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_attn_bf16<128, 3>, 64, 0);
+  else if (bf16) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_attn_bf16<64, 4>, 64, 0);
   else if (head_dim <= 64) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_attn_f32<1>, 64, 0);
   else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_attn_f32<2>, 64, 0);
   return (e == hipSuccess && n > 0) ? n : 8;
@@ -3239,8 +3436,9 @@ hipError_t launch_attn_combine(const AttnArgs& a, int head_dim, bool bf16, hipSt
   const int blocks = a.n_seqs * a.n_kv_heads * a.launch_layers;
   if (bf16) {
     const int items = blocks * a.group;
-    // the prefill's token groups (kv_reread): a wave per (item, kv-head)
-    const dim3 mq((blocks + 3) / 4);
+    // the prefill's token groups (kv_reread): a wave per 64 units of an (item, kv-head)
+    const int ng = a.kv_reread ? (a.tq_T + a.tq - 1) / a.tq : 1;
+    const dim3 mq((blocks * ng * ((a.group * (head_dim / 8) + 63) / 64) + 3) / 4);
     if (head_dim == 128)
       return a.kv_reread ? go(k_attn_combine_mq<128>, mq, dim3(256), 0, st, t0(tm), t1(tm), a)
                          : go(k_attn_combine_bf16<128>, dim3(items), dim3(64), 0, st, t0(tm), t1(tm), a);
