@@ -2895,7 +2895,12 @@ constexpr int kProjWaves = 8;  // waves per projection block
 // Per layer at 4096 / 1024 / 14336 (QKV, O, gate/up and down together): 33 rows
 // 84 us (93 us with the x slice staged whole before a weights-only ring), 65 rows
 // 107 us (144 us with the library GEMM).
-template <int NT>
+// SWIGLU (gate/up in one K slice): the tiles alternate gate / up, so waves 2 i
+// and 2 i + 1 hold both halves of an output; the launch applies the epilogue
+// itself, without the partial sums and k_proj_reduce's launch. The row scales
+// are summed by every block (32 KiB from L2 at 33 rows, behind the W stream).
+// Per layer at 33 rows x 28672 columns: 35.8 + 5.6 us (two launches) -> 40.0 us.
+template <int NT, bool SWIGLU>
 __global__ __launch_bounds__(64 * kProjWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_proj(GemmArgs a) {
   constexpr int WPB = kProjWaves, NS = 8, LEAD = NS - 1;
   constexpr int XU = 2 * NT, XB = (XU + WPB - 1) / WPB;  // 1 KiB x operands of a step; of which each wave loads
@@ -2992,7 +2997,47 @@ __global__ __launch_bounds__(64 * kProjWaves) __attribute__((amdgpu_waves_per_eu
   for (int i = 0; i < n; i += NS)
     static_for<NS>([&](auto jc) __attribute__((always_inline)) { step(jc, i + (int)decltype(jc)::value); });
   wait_vmcnt<0>();  // the loads past the end (some into LDS) have landed
-  if (tile < a.n_tiles) {
+  if constexpr (SWIGLU) {
+    static_assert(kProjWaves == 8, "a stage per pair of waves");
+    float t[2 * NT];  // rows wave, wave + 8, ...
+#pragma unroll
+    for (int r = 0; r < 2 * NT; ++r) t[r] = 0.f;
+    for (int p = 4 * lane; p < a.ss_parts; p += 256)
+#pragma unroll
+      for (int r = 0; r < 2 * NT; ++r) {
+        const float4 v = *(const float4*)(a.ss_in + (size_t)min(wave + WPB * r, a.M - 1) * a.ld_ss + p);
+        t[r] += (v.x + v.y) + (v.z + v.w);
+      }
+    __syncthreads();  // all waves have left the stages, which now hold the row scales and the up tiles
+    float* rho = (float*)&xs4[0][0];
+#pragma unroll
+    for (int r = 0; r < 2 * NT; ++r) {
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) t[r] += __shfl_xor(t[r], o);
+      if (lane == 0) rho[wave + WPB * r] = 1.0f / sqrtf(t[r] * a.inv_norm_dim + a.eps);
+    }
+    uint4(*up)[64] = wave < 2 ? xs0 : wave < 4 ? xs1 : wave < 6 ? xs2 : xs3;
+    if (wave & 1)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) up[nt][lane] = __builtin_bit_cast(uint4, acc[nt]);
+    __syncthreads();
+    if (!(wave & 1) && tile < a.n_tiles) {
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const int m = 16 * nt + col;
+        const f32x4 u = __builtin_bit_cast(f32x4, up[nt][lane]);
+        const float rm = rho[m];
+        uint32_t o[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float gg = acc[nt][q] * rm, uu = u[q] * rm;
+          o[q] = f2bf(gg / (1.0f + expf(-gg)) * uu);
+        }
+        if (m < a.M)
+          *(uint2*)(a.act + (size_t)m * a.F + 8 * tile + 4 * quad) = make_uint2(o[0] | (o[1] << 16), o[2] | (o[3] << 16));
+      }
+    }
+  } else if (tile < a.n_tiles) {
     float* dst = a.part + (size_t)split * a.M * N + 16 * tile + 4 * quad;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
@@ -3496,6 +3541,20 @@ hipError_t launch_reduce(const GemmArgs& a, GemmEpi epi, hipStream_t st, hipEven
     default: return hipErrorInvalidValue;
   }
 }
+template <bool SWIGLU>
+hipError_t go_proj(const GemmArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  const dim3 g((a.n_tiles + kProjWaves - 1) / kProjWaves * a.ksplit), b(64 * kProjWaves);
+  switch ((a.M + 15) / 16) {
+    case 1: return go(k_proj<1, SWIGLU>, g, b, 0, st, ev0, ev1, a);
+    case 2: return go(k_proj<2, SWIGLU>, g, b, 0, st, ev0, ev1, a);
+    case 3: return go(k_proj<3, SWIGLU>, g, b, 0, st, ev0, ev1, a);
+    case 4: return go(k_proj<4, SWIGLU>, g, b, 0, st, ev0, ev1, a);
+    case 5: return go(k_proj<5, SWIGLU>, g, b, 0, st, ev0, ev1, a);
+    case 6: return go(k_proj<6, SWIGLU>, g, b, 0, st, ev0, ev1, a);
+    case 7: return go(k_proj<7, SWIGLU>, g, b, 0, st, ev0, ev1, a);
+    default: return go(k_proj<8, SWIGLU>, g, b, 0, st, ev0, ev1, a);
+  }
+}
 }  // namespace
 
 hipError_t launch_gemm(const GemmArgs& a, GemmEpi epi, hipStream_t st, const Timing* tm) {
@@ -3504,18 +3563,9 @@ hipError_t launch_gemm(const GemmArgs& a, GemmEpi epi, hipStream_t st, const Tim
   const int KS = a.K / 64;
   if (a.ksplit < 1 || a.ksplit > KS) return hipErrorInvalidValue;
   if ((size_t)((KS + a.ksplit - 1) / a.ksplit) * a.n_tiles * 2048 >= 0x7FFFFFFFull) return hipErrorInvalidValue;
-  const dim3 g((a.n_tiles + kProjWaves - 1) / kProjWaves * a.ksplit), b(64 * kProjWaves);
-  hipError_t e;
-  switch ((a.M + 15) / 16) {
-    case 1: e = go(k_proj<1>, g, b, 0, st, t0(tm), nullptr, a); break;
-    case 2: e = go(k_proj<2>, g, b, 0, st, t0(tm), nullptr, a); break;
-    case 3: e = go(k_proj<3>, g, b, 0, st, t0(tm), nullptr, a); break;
-    case 4: e = go(k_proj<4>, g, b, 0, st, t0(tm), nullptr, a); break;
-    case 5: e = go(k_proj<5>, g, b, 0, st, t0(tm), nullptr, a); break;
-    case 6: e = go(k_proj<6>, g, b, 0, st, t0(tm), nullptr, a); break;
-    case 7: e = go(k_proj<7>, g, b, 0, st, t0(tm), nullptr, a); break;
-    default: e = go(k_proj<8>, g, b, 0, st, t0(tm), nullptr, a); break;
-  }
+  const bool fused = epi == kEpiSwiglu && a.ksplit == 1 && a.ss_in && !a.rho_in && a.ss_parts % 4 == 0 && a.ld_ss % 4 == 0;
+  if (fused) return go_proj<true>(a, st, t0(tm), t1(tm));
+  const hipError_t e = go_proj<false>(a, st, t0(tm), nullptr);
   if (e != hipSuccess) return e;
   return launch_reduce(a, epi, st, t1(tm));
 }
