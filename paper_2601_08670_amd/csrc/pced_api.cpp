@@ -194,7 +194,7 @@ Layout make_layout(const pced_config& c) {
   L.pf_q = take(PR * c.n_q_heads * c.head_dim * 2);
   L.pf_x = take(PR * c.hidden * 2);
   L.pf_part_acc = take(PR * c.n_kv_heads * kPrefillParts * G * c.head_dim * 4);
-  L.pf_part_ml = take(PR * c.n_kv_heads * kPrefillParts * G * 2 * 4);
+  L.pf_part_ml = take(2 * PR * c.n_kv_heads * kPrefillParts * G * 2 * 4);  // (bf16 states: pf_part_acc holds twice as many)
   L.pf_proj_elems = std::max(PR * max_cols, (size_t)kLmRowsPad * L.part_cols);
   L.pf_proj = take(L.pf_proj_elems * 4);
   // staging of caches loaded from host memory: the longest sequence's K and V, at
@@ -1048,7 +1048,9 @@ pced_status run_prefill_chunk(pced_ctx* c, const char* model, const int32_t* tok
   R.x = c->at<void>(c->lay.pf_x);
   R.part_acc = c->at<float>(c->lay.pf_part_acc);
   R.part_ml = c->at<float>(c->lay.pf_part_ml);
-  R.part_slots = part_slots;
+  // (bf16 states take half of their slots, so the last resort above may use twice
+  // as many: what the longest chunks split depends on where the chunks fall)
+  R.part_slots = 2 * part_slots;
   R.rho_rows = c->at<float>(c->lay.pf_rho);
   R.proj_part = c->at<float>(c->lay.pf_proj);
   R.proj_cols = M > kProjMaxRows ? c->lay.pf_proj_cols : c->lay.pf_proj_elems / M;
