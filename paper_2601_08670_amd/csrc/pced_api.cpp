@@ -90,6 +90,7 @@ struct Layout {
   size_t pf_proj_cols;  // slices x columns per row of the prefill projection partials
   size_t pf_proj_elems; // floats of that buffer
   int rows_pad, nblk_fuse, nblk_agg, nchunk, max_work;
+  size_t seg_slots;     // segment descriptors of the attention plan
   size_t part_slots;
   size_t part_cols;  // slices x columns one row of the projection partial buffer holds
 };
@@ -125,7 +126,10 @@ Layout make_layout(const pced_config& c) {
   L.src_v = take(S * 8);
   L.meta_end = o;
   L.chunk_info = take((size_t)L.max_work * 8);
-  L.seg = take((size_t)L.max_work * kMaxSeg * 2 * 16);
+  L.seg_slots = (size_t)L.max_work * kMaxSeg;
+  // a prefill chunk holds 4 pages or more on average, or all there are (see plan_for_lengths)
+  if (c.ffn_dim > 0) L.seg_slots = std::max(L.seg_slots, ((size_t)c.max_pages / 4 + 1) * kMaxSplitPages);
+  L.seg = take(L.seg_slots * 2 * 16);
   L.nparts = take(S * 4);
   L.work_pages = take((size_t)L.max_work * kMaxSplitPages * 4);
   L.prev_tok = take(B * 4);
@@ -324,8 +328,10 @@ void plan_stats(const std::vector<long>& pre, long P, long C, AttnPlan* out) {
 
 // C is the number of chunks whose waves all fit on the chip at once (so every
 // wave starts in the first round and streams the same number of pages), at
-// least P/64 (one page id per lane), raised when a chunk would meet more
-// sequences than a wave can stage q rows for.
+// least P/64 (one page id per lane), raised when a decode chunk would meet more
+// sequences than a wave can stage q rows for. (Prefill chunks load a sequence's q
+// when they come to it: any number of short caches beside a long one leaves the
+// chunks, and so the long one's partial states, as they are.)
 AttnPlan plan_for_lengths(const pced_ctx* c, const std::vector<int>& lens, int layers = 1, int groups = 0,
                           bool longest = false);
 
@@ -369,7 +375,9 @@ AttnPlan plan_for_lengths(const pced_ctx* c, const std::vector<int>& lens, int l
   long C = std::max<long>(std::min(cap, P), ceil_div(P, (long)kMaxSplitPages));
   // bf16 decode: the later segments' q rows of a chunk are staged by its wave in LDS
   const int per_seg_units = c->G * c->cfg.head_dim / 8;
-  const int seg_limit = c->bf16 && groups == 0 ? std::min(kMaxSeg, 1 + 64 * kStageUnits / per_seg_units) : kMaxSeg;
+  const int seg_limit = groups > 0 ? kMaxSplitPages
+                        : c->bf16  ? std::min(kMaxSeg, 1 + 64 * kStageUnits / per_seg_units)
+                                   : kMaxSeg;
   AttnPlan plan;
   for (;;) {
     plan_stats(pre, P, C, &plan);
@@ -730,7 +738,9 @@ pced_status run_model_forward(pced_ctx* c, const char* model, const FwdRows& R, 
   const int qd = cfg.n_q_heads * D, kd = cfg.n_kv_heads * D;
   const int AG = c->G * R.att_tq;  // query columns per kv-head of an attention item
   const AttnPlan& plan = R.att_plan;
-  if (plan.chunks > c->lay.max_work) return fail(PCED_ERR_CAPACITY, "attention plan exceeds workspace");
+  const int seg_stride = R.per_layer_q ? kMaxSeg : kMaxSplitPages;
+  if (plan.chunks > c->lay.max_work || (size_t)plan.chunks * seg_stride > c->lay.seg_slots)
+    return fail(PCED_ERR_CAPACITY, "attention plan exceeds workspace");
   // (the partial buffers hold part_slots states of G columns)
   if ((size_t)R.att_n * R.att_ng * cfg.n_kv_heads * plan.max_parts * AG > R.part_slots * c->G)
     return fail(PCED_ERR_CAPACITY, "attention partial states exceed workspace");
@@ -756,6 +766,7 @@ pced_status run_model_forward(pced_ctx* c, const char* model, const FwdRows& R, 
   ap.t = c->t;
   ap.n_chunks = plan.chunks;
   ap.total_pages = (int)plan.pages;
+  ap.seg_stride = seg_stride;
   {
     ProfScope ps(c, PCED_PROF_APPEND, 0, 0);
     HIP_OK(launch_append(ap, true, st, ps.timing()));
@@ -1134,6 +1145,7 @@ pced_status run_step(pced_ctx* c, const void* q, const void* k_new, const void* 
   ap.t = c->t;
   ap.n_chunks = plan.chunks;
   ap.total_pages = (int)plan.pages;
+  ap.seg_stride = kMaxSeg;
   {
     ProfScope ps(c, PCED_PROF_APPEND, 4.0 * c->S * cfg.n_layers * cfg.n_kv_heads * cfg.head_dim * es, 0);
     HIP_OK(launch_append(ap, c->bf16, st, ps.timing()));

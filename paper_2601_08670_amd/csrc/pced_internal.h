@@ -18,7 +18,7 @@ constexpr int kAggExperts = 256;   // experts whose coefficients it holds in LDS
 constexpr int kLmRowsPad = 48;     // hidden-state rows are padded to a multiple of this
 constexpr int kLmRowsMTW = 9;      // many-row LM head: row tiles per wave (up to 32 * 9 = 288 rows at once)
 constexpr int kMaxSplitPages = 64; // pages per attention chunk (one page id per lane)
-constexpr int kMaxSeg = 8;         // sequences one attention chunk may span
+constexpr int kMaxSeg = 8;         // sequences one decode attention chunk may span (a prefill chunk: one per page)
 constexpr int kStageUnits = 4;     // 16-byte q units per lane staged in LDS for a chunk's later sequences
 // Packed LM-head tiles ordered [64-wide k step][16-row vocab block]: at every k
 // step the waves of a launch read adjacent tiles, so the weight stream sweeps W
@@ -52,11 +52,12 @@ struct AttnArgs {
   // Balanced plan of the step (written by the planning blocks of the append
   // launch): the pages of all sequences, concatenated in sequence order, are cut
   // into C chunks of equal size (+-1 page); one wave per (chunk, kv-head). A
-  // chunk meets up to kMaxSeg sequences ("segments"); each segment yields one
+  // chunk meets up to kMaxSeg sequences ("segments"; in the prefill up to
+  // kMaxSplitPages, of which nothing is staged in advance); each segment yields one
   // partial state of its sequence, or the final output when the sequence lies
   // in a single chunk.
   const int2* chunk_info;   // [C] (segments, pages) of each chunk
-  const int4* seg;          // [C][kMaxSeg][2]: {s, first page in chunk, page offset in s - first page,
+  const int4* seg;          // [C][kMaxSeg, prefill kMaxSplitPages][2]: {s, first page in chunk, page offset in s - first page,
                             //  token end in this chunk}, {partial index in s, partials of s, tokens of s, 0}
   const int32_t* nparts;    // [S] partial states of each sequence (chunks it meets)
   const int32_t* work_pages;// [C][kMaxSplitPages] physical pages of each chunk
@@ -94,6 +95,7 @@ struct AppendArgs {
   int32_t* work_pages;
   int n_seqs, n_layers, n_kv_heads, head_dim, max_pages, maxpps, t;
   int n_chunks, total_pages;  // C and P of the balanced plan (P = pages after the append)
+  int seg_stride;             // segment descriptors per chunk
 };
 
 struct LoadArgs {

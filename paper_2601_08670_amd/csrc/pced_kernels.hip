@@ -235,16 +235,17 @@ __global__ __launch_bounds__(128) void k_append(AppendArgs a) {
     const long P = a.total_pages, C = a.n_chunks;
     auto pages_of = [&](int r) { return (a.len0[r] + a.t + 1 + kPage - 1) / kPage; };
     // first global page of this sequence: sum over earlier sequences; the page
-    // counts of the kMaxSeg sequences just before s also go to LDS for the walk
-    // back below (one round of loads instead of a chain of dependent ones)
+    // counts of the kMaxSplitPages sequences just before s (a chunk meets no more)
+    // also go to LDS for the walk back below (one round of loads instead of a
+    // chain of dependent ones)
     __shared__ int red[2];
-    __shared__ int back[kMaxSeg];
+    __shared__ int back[kMaxSplitPages];
     __shared__ int k_first;
     int part = 0;
     for (int r = threadIdx.x; r < s; r += blockDim.x) {
       const int p = pages_of(r);
       part += p;
-      if (r >= s - kMaxSeg) back[r - (s - kMaxSeg)] = p;
+      if (r >= s - kMaxSplitPages) back[r - (s - kMaxSplitPages)] = p;
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) part += __shfl_xor(part, o);
@@ -260,9 +261,9 @@ __global__ __launch_bounds__(128) void k_append(AppendArgs a) {
       const long b0 = chunk_lo(c0, P, C);
       long end = pre;
       int k = 0;
-      for (int r = s - 1; r >= 0 && end > b0 && k < kMaxSeg; --r) {  // r >= s - kMaxSeg
+      for (int r = s - 1; r >= 0 && end > b0 && k < kMaxSplitPages; --r) {  // r >= s - kMaxSplitPages
         ++k;
-        end -= back[r - (s - kMaxSeg)];
+        end -= back[r - (s - kMaxSplitPages)];
       }
       k_first = k;
     }
@@ -272,9 +273,9 @@ __global__ __launch_bounds__(128) void k_append(AppendArgs a) {
       const long lo = max(pre, lo_c), hi = min(pre + ps, hi_c);
       const int k = c == c0 ? k_first : 0;
       const int i0 = (int)(lo - lo_c), pa = (int)(lo - pre);
-      if (k < kMaxSeg) {
-        a.seg[((size_t)c * kMaxSeg + k) * 2] = make_int4(s, i0, pa - i0, min(len, (int)(hi - pre) * kPage));
-        a.seg[((size_t)c * kMaxSeg + k) * 2 + 1] = make_int4(c - c0, c1 - c0 + 1, len, 0);
+      if (k < a.seg_stride) {
+        a.seg[((size_t)c * a.seg_stride + k) * 2] = make_int4(s, i0, pa - i0, min(len, (int)(hi - pre) * kPage));
+        a.seg[((size_t)c * a.seg_stride + k) * 2 + 1] = make_int4(c - c0, c1 - c0 + 1, len, 0);
       }
       if (hi == hi_c) a.chunk_info[c] = make_int2(k + 1, (int)(hi_c - lo_c));  // last segment of chunk c
     }
@@ -2700,7 +2701,7 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
   const int nseg = ci.x, np = ci.y;
   // physical page ids, lane k holding the chunk's page k (kMaxSplitPages = 64; entries past np are never used)
   const int my_pid = a.work_pages[(size_t)c * kMaxSplitPages + lane];
-  const int4* sd = a.seg + (size_t)c * kMaxSeg * 2;
+  const int4* sd = a.seg + (size_t)c * kMaxSplitPages * 2;
   const size_t lay = (size_t)a.layer * a.max_pages * Hkv + g;
   constexpr size_t tile_bytes = (size_t)kPage * D * 2;
   auto load = [&](auto st_c, int i) __attribute__((always_inline)) {

@@ -25,3 +25,13 @@ def test_group_edges(hq, hkv, d, n_tok, cap):
     wl = W.custom(geom, [3], [1, 150, 47], amateur_len=16, steps=1, seed=n_tok)
     _run(wl, ModelSpec(geom, ffn_dim=512, rope_theta=10000.0, seed=n_tok), steps=1, prefill=n_tok,
          max_attn_chunks=cap)
+
+
+@pytest.mark.parametrize("hq,hkv,d,n_tok,cap", [(4, 1, 128, 9, 1), (4, 1, 128, 40, 1), (4, 4, 64, 3, 2)])
+def test_chunk_over_many_short_sequences(hq, hkv, d, n_tok, cap):
+    # chunks of about 50 pages: one holds some 30 of the short caches and the start of the long one
+    from tests.test_gpu_model import _run
+    geom = W.Geometry(2, hq, hkv, d, hq * d, 500, "bf16")
+    wl = W.custom(geom, [32], [3 + i % 9 for i in range(30)] + [1100, 5], amateur_len=16, steps=1, seed=n_tok)
+    _run(wl, ModelSpec(geom, ffn_dim=512, rope_theta=10000.0, seed=n_tok), steps=1, prefill=n_tok,
+         max_attn_chunks=cap)

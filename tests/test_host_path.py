@@ -1,0 +1,90 @@
+"""What the host code plans, launches and copies, checked without a GPU: the
+library's own csrc/pced_api.cpp over recording stand-ins for the HIP runtime and
+the kernel launchers (tests/host_path.cpp). Device addresses are never read."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+from paper_2601_08670_amd import _lib
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2601_08670_amd", "csrc")
+DEVICE = 1 << 46  # addresses from here on count as device memory
+CAPACITY, HIPERR = 2, 3
+
+
+@pytest.fixture(scope="session")
+def host(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("host_path") / "host_path.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__",
+                    "-I/opt/rocm/include", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
+                    os.path.join(ROOT, "tests", "host_path.cpp"), os.path.join(CSRC, "pced_api.cpp"),
+                    "-Wl,-Bsymbolic", "-Wl,--no-undefined", "-o", out], check=True)
+    lib = ctypes.CDLL(out)
+    lib.rec_name.restype = ctypes.c_char_p
+    lib.rec_value.restype = ctypes.c_long
+    lib.pced_workspace_bytes.restype = ctypes.c_size_t
+    lib.pced_last_error.restype = ctypes.c_char_p
+    return lib
+
+
+class Batch:
+    """A context with one loaded query; calls return the status."""
+
+    def __init__(self, lib, lens, reserve, src=DEVICE, **kw):
+        cfg = dict(n_layers=1, n_q_heads=32, n_kv_heads=8, head_dim=128, vocab=1000, dtype="bf16", max_queries=1,
+                   max_seqs=len(lens), max_pages=sum(-(-(n + reserve) // 16) for n in lens),
+                   max_pages_per_seq=max(-(-(n + reserve) // 16) for n in lens))
+        cfg.update(kw)
+        self.lib, self.lens, self.layers = lib, lens, cfg["n_layers"]
+        self.cfg = _lib.make_config(**cfg)
+        self.ctx = ctypes.c_void_p()
+        ws = lib.pced_workspace_bytes(ctypes.byref(self.cfg))
+        assert lib.pced_create(ctypes.byref(self.cfg), ctypes.c_void_p(DEVICE), ctypes.c_size_t(ws),
+                               ctypes.byref(self.ctx)) == 0, self.error()
+        self.status = self.load(reserve, src)
+
+    def load(self, reserve, src=DEVICE):
+        S, p = len(self.lens), ctypes.c_void_p(DEVICE + (1 << 40))
+        ptrs = (ctypes.c_void_p * S)(*[src] * S)
+        self.lib.rec_clear()
+        return self.lib.pced_load_caches(self.ctx, 1, (ctypes.c_int32 * 1)(S - 1), (ctypes.c_int32 * S)(*self.lens),
+                                         ptrs, ptrs, p, p, None, reserve, (ctypes.c_float * (S - 1))(*[0.5] * (S - 1)),
+                                         ctypes.c_float(2.5), None, None)
+
+    def prefill(self, n_tokens):
+        self.lib.rec_clear()
+        p = ctypes.c_void_p(DEVICE)
+        return self.lib.pced_model_prefill(self.ctx, p, n_tokens, p, None)
+
+    def step(self):
+        self.lib.rec_clear()
+        p = ctypes.c_void_p(DEVICE)
+        return self.lib.pced_step(self.ctx, p, p, p, p, p, None, None)
+
+    def calls(self, name):
+        return [[self.lib.rec_value(i, j) for j in range(8)] for i in range(self.lib.rec_count())
+                if self.lib.rec_name(i).decode() == name]
+
+    def error(self):
+        return self.lib.pced_last_error().decode()
+
+    def __del__(self):
+        if self.ctx:
+            self.lib.pced_destroy(self.ctx)
+
+
+# attention launches: first layer, layers, chunks, prefill, tokens per group, tokens, partial states per sequence, sequences
+LAYER, LAYERS, CHUNKS, PREFILL, TQ, TOKENS, PARTS, SEQS = range(8)
+
+
+@pytest.mark.parametrize("short,n_short,long,suffix", [
+    (16, 75, 8192, 16), (16, 70, 6000, 32), (24, 55, 12288, 20), (1, 100, 30000, 7), (16, 8, 100000, 16),
+])
+def test_prefill_takes_many_short_caches_beside_a_long_one(host, short, n_short, long, suffix):
+    # the partial states that the longest chunks (64 pages) need do not depend on how short the others are
+    b = Batch(host, [16] + [short] * n_short + [long], suffix, ffn_dim=512)
+    assert b.status == 0 and b.prefill(suffix) == 0, b.error()
+    assert b.calls("attn")[0][PARTS] <= -(-(long + suffix) // 16 // 64) + 2
