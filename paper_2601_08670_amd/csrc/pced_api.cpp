@@ -1019,19 +1019,21 @@ pced_status run_prefill_chunk(pced_ctx* c, const char* model, const int32_t* tok
   R.page_table = pm.page_table_out;
   // attention: groups of tq tokens of a sequence, at most kPrefillTiles x 16
   // query columns per kv-head (tq x q-heads per kv-head) and all of about the
-  // same size, so each group reads the sequence's pages once for all its tokens
-  // (the longest chunks, then fewer tokens per group, where the partial states
-  // of the plan would not fit)
-  const size_t part_slots = (size_t)c->lay.pf_rows * cfg.n_kv_heads * kPrefillParts;
+  // same size, so each group reads the sequence's pages once for all its tokens.
+  // Where the partial states of the plan would not fit: the longest chunks, which
+  // split the sequences least; then the largest smaller groups with fewer columns
+  // in all (only the padding of the last groups can go: the longest chunks do not
+  // depend on the groups). The states are bf16 in slots of four bytes an element.
+  const size_t part_slots = 2 * (size_t)c->lay.pf_rows * cfg.n_kv_heads * kPrefillParts;
   R.att_lens.resize(S);  // keys of each sequence's last token
   for (int s = 0; s < S; ++s) R.att_lens[s] = c->len[s] + T - 1;
-  int tq = std::max(1, std::min(T, kPrefillTiles * kMaxGroup / c->G)), ng = 0;
-  for (bool longest = false;; longest = !longest) {
-    if (!longest) tq = ceil_div(T, ceil_div(T, tq));
-    ng = ceil_div(T, tq);
-    R.att_plan = plan_for_lengths(c, R.att_lens, 1, ng, longest);
-    if ((size_t)S * ng * cfg.n_kv_heads * R.att_plan.max_parts * tq <= part_slots || (longest && tq == 1)) break;
-    if (longest) tq = (tq + 1) / 2;
+  int tq = std::max(1, std::min(T, kPrefillTiles * kMaxGroup / c->G)), ng = ceil_div(T, tq);
+  tq = ceil_div(T, ng);
+  auto fits = [&] { return (size_t)S * ng * tq * cfg.n_kv_heads * R.att_plan.max_parts <= part_slots; };
+  R.att_plan = plan_for_lengths(c, R.att_lens, 1, ng);
+  if (!fits()) {
+    R.att_plan = plan_for_lengths(c, R.att_lens, 1, ng, true);
+    while (!fits() && tq > 1) ng = ceil_div(T, --tq);
   }
   PrefillMetaArgs gm = pm;
   gm.len0_out = c->at<int32_t>(c->lay.pf_glen0);
@@ -1059,9 +1061,7 @@ pced_status run_prefill_chunk(pced_ctx* c, const char* model, const int32_t* tok
   R.x = c->at<void>(c->lay.pf_x);
   R.part_acc = c->at<float>(c->lay.pf_part_acc);
   R.part_ml = c->at<float>(c->lay.pf_part_ml);
-  // (bf16 states take half of their slots, so the last resort above may use twice
-  // as many: what the longest chunks split depends on where the chunks fall)
-  R.part_slots = 2 * part_slots;
+  R.part_slots = part_slots;
   R.rho_rows = c->at<float>(c->lay.pf_rho);
   R.proj_part = c->at<float>(c->lay.pf_proj);
   R.proj_cols = M > kProjMaxRows ? c->lay.pf_proj_cols : c->lay.pf_proj_elems / M;

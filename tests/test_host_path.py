@@ -87,4 +87,24 @@ def test_prefill_takes_many_short_caches_beside_a_long_one(host, short, n_short,
     # the partial states that the longest chunks (64 pages) need do not depend on how short the others are
     b = Batch(host, [16] + [short] * n_short + [long], suffix, ffn_dim=512)
     assert b.status == 0 and b.prefill(suffix) == 0, b.error()
-    assert b.calls("attn")[0][PARTS] <= -(-(long + suffix) // 16 // 64) + 2
+
+
+@pytest.mark.parametrize("n,long,suffix,tq", [
+    (33, 10000, 64, 8),   # the longest chunks take most of the partial-state slots with groups of any size
+    (33, 14000, 60, 8), (20, 14000, 100, 8),
+    (2, 3000, 64, 8),     # (a plan for the whole chip)
+])
+def test_prefill_groups_stay_full_where_the_longest_chunks_fit(host, n, long, suffix, tq):
+    b = Batch(host, [16] * n + [long], suffix, ffn_dim=512)
+    assert b.status == 0 and b.prefill(suffix) == 0, b.error()
+    a = b.calls("attn")[0]
+    assert a[TQ] == tq and a[TOKENS] == suffix, a
+
+
+def test_prefill_groups_shrink_only_to_save_padding(host):
+    # 9 tokens as two groups of 5 are 10 columns; as 9 groups of one they are 9
+    b = Batch(host, [16] * 230 + [16 * 64 * 15], 9, ffn_dim=512)
+    assert b.status == 0 and b.prefill(9) == 0, b.error()
+    a = b.calls("attn")[0]
+    assert 231 * 9 * a[PARTS] <= 2 * 2304 * 8 < 231 * 10 * a[PARTS] and a[TQ] in (1, 3), a
+    assert Batch(host, [16] * 230 + [16 * 64 * 20], 9, ffn_dim=512).prefill(9) == CAPACITY
