@@ -92,11 +92,15 @@ typedef struct pced_config {
   int32_t max_pages;         /* pool capacity in pages (per layer)               */
   int32_t max_pages_per_seq; /* page-table row length                            */
   int32_t norm;              /* pced_norm                                        */
-  int32_t max_attn_chunks;   /* cap on the attention launch's work chunks (waves
-                                per kv-head), >= 0; 0 = as many as fit on the
-                                GPU at once. A smaller cap leaves compute units
-                                to other work; each chunk then streams more
-                                pages and may span more sequences            */
+  int32_t max_attn_chunks;   /* cap on the work chunks of an attention launch
+                                (waves per kv-head, over all layers of the
+                                launch or token groups of a prefill), >= 0;
+                                0 = what fills the GPU in whole rounds of
+                                waves. A smaller cap leaves compute units to
+                                other work: a launch then takes fewer layers,
+                                and each chunk streams more pages, up to 64
+                                (a layer has at least one chunk per 64 pages
+                                whatever the cap)                            */
   int32_t aggregation;       /* pced_aggregation. For MoE / PoE (the paper
                                 compares them with Max in Appendix C.4 without
                                 formulas; reading): c_k = (1 + beta_k) s_k -

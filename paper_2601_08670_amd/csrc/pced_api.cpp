@@ -371,7 +371,9 @@ AttnPlan plan_for_lengths(const pced_ctx* c, const std::vector<int>& lens, int l
     cap *= ceil_div(P, cap * kMaxSplitPages);
     cap = longest ? 1 : std::min(cap, std::max<long>(1, P / 4));
   }
-  if (c->cfg.max_attn_chunks > 0) cap = std::min<long>(cap, c->cfg.max_attn_chunks);
+  // (the configured cap counts the waves of a launch: over all of its layers, or token groups)
+  if (c->cfg.max_attn_chunks > 0)
+    cap = std::min(cap, std::max<long>(1, c->cfg.max_attn_chunks / std::max({1, layers, groups})));
   long C = std::max<long>(std::min(cap, P), ceil_div(P, (long)kMaxSplitPages));
   // bf16 decode: the later segments' q rows of a chunk are staged by its wave in LDS
   const int per_seg_units = c->G * c->cfg.head_dim / 8;
@@ -1108,6 +1110,7 @@ pced_status run_step(pced_ctx* c, const void* q, const void* k_new, const void* 
       return fail(PCED_ERR_CAPACITY, "sequence %d has no page for token %d", s, c->len[s]);
   }
   // Layers per launch: all, or what the partial states of the plan leave room for
+  // and the configured cap on a launch's chunks
   const size_t es_part = c->bf16 ? 2 : 4;
   const size_t part_bytes = c->lay.part_slots * c->G * cfg.head_dim * 4;  // (part_ml holds 2 part_slots of them)
   AttnPlan plan;
@@ -1116,9 +1119,10 @@ pced_status run_step(pced_ctx* c, const void* q, const void* k_new, const void* 
   for (;;) {
     plan = plan_attention(c, per_launch);
     slots = (size_t)c->S * cfg.n_kv_heads * plan.max_parts;
-    const size_t room = plan.max_parts > 1
-                            ? std::min(part_bytes / (slots * c->G * cfg.head_dim * es_part), 2 * c->lay.part_slots / slots)
-                            : (size_t)cfg.n_layers;
+    size_t room = plan.max_parts > 1
+                      ? std::min(part_bytes / (slots * c->G * cfg.head_dim * es_part), 2 * c->lay.part_slots / slots)
+                      : (size_t)cfg.n_layers;
+    if (cfg.max_attn_chunks > 0) room = std::min<size_t>(room, cfg.max_attn_chunks / plan.chunks);
     if (per_launch == 1 || (size_t)per_launch <= room) break;
     per_launch = std::max(1, std::min<int>(per_launch - 1, (int)room));
   }

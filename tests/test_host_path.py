@@ -108,3 +108,34 @@ def test_prefill_groups_shrink_only_to_save_padding(host):
     a = b.calls("attn")[0]
     assert 231 * 9 * a[PARTS] <= 2 * 2304 * 8 < 231 * 10 * a[PARTS] and a[TQ] in (1, 3), a
     assert Batch(host, [16] * 230 + [16 * 64 * 20], 9, ffn_dim=512).prefill(9) == CAPACITY
+
+
+@pytest.mark.parametrize("layers,lens,cap", [
+    (32, [64] + [1500] * 32, 4),   # more pages than 64 per chunk: a launch per layer, as many chunks as it needs
+    (32, [64] + [1500] * 32, 256), (32, [64] + [1500] * 32, 100), (5, [16] + [90] * 3, 2), (7, [16] + [90] * 8, 4),
+    (32, [16] + [700] * 4, 9), (1, [16] + [700] * 4, 3), (32, [64] + [1500] * 32, 0), (5, [16] + [90] * 3, 0),
+])
+def test_step_launches_keep_to_the_chunk_cap(host, layers, lens, cap):
+    b = Batch(host, lens, 2, n_layers=layers, max_attn_chunks=cap)
+    assert b.status == 0 and b.step() == 0, b.error()
+    at, nxt = b.calls("attn"), 0
+    for a in at:  # every layer once, in order
+        assert a[LAYER] == nxt and a[LAYERS] >= 1
+        nxt += a[LAYERS]
+        assert not cap or a[LAYERS] == 1 or a[LAYERS] * a[CHUNKS] <= cap, a
+    assert nxt == layers
+    pages = sum(-(-(n + 1) // 16) for n in lens)
+    if cap:
+        assert at[0][CHUNKS] <= max(cap, -(-pages // 64), pages // 2), at[0]
+    else:
+        assert len(at) == 1
+
+
+@pytest.mark.parametrize("suffix,cap", [(9, 4), (64, 8), (64, 100), (1, 3)])
+def test_prefill_launch_keeps_to_the_chunk_cap(host, suffix, cap):
+    lens = [16] + [800] * 8
+    b = Batch(host, lens, suffix, ffn_dim=512, max_attn_chunks=cap)
+    assert b.status == 0 and b.prefill(suffix) == 0, b.error()
+    groups = -(-suffix // b.calls("attn")[0][TQ])
+    pages = sum(-(-(n + suffix) // 16) for n in lens)
+    assert b.calls("attn")[0][CHUNKS] * groups <= max(cap, groups * -(-pages // 64))
