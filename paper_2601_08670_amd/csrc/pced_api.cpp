@@ -1448,7 +1448,10 @@ pced_status pced_load_caches(pced_ctx* c, int32_t n_queries, const int32_t* n_ex
     if (!on_host[s]) continue;
     any_host = true;
     r = load_from_host(c, la, (int)s, cache_len[s], (const char*)src_k[s], (const char*)src_v[s], st);
-    if (r != PCED_OK) return r;
+    if (r != PCED_OK) {  // the host buffers are the caller's again: earlier copies may still be reading them
+      (void)hipStreamSynchronize(st);
+      return r;
+    }
   }
   if (any_host) HIP_OK(hipStreamSynchronize(st));  // the host buffers have been read
 

@@ -139,3 +139,14 @@ def test_prefill_launch_keeps_to_the_chunk_cap(host, suffix, cap):
     groups = -(-suffix // b.calls("attn")[0][TQ])
     pages = sum(-(-(n + suffix) // 16) for n in lens)
     assert b.calls("attn")[0][CHUNKS] * groups <= max(cap, groups * -(-pages // 64))
+
+
+@pytest.mark.parametrize("call,nth", [("copy_in", 3), ("copy_in", 4), ("load", 1), ("load", 2)])
+def test_failing_host_load_waits_for_its_copies(host, call, nth):
+    # (the first copy is the metadata; then K, V and a launch per sequence)
+    b = Batch(host, [40, 50, 60], 0)
+    host.rec_fail(call.encode(), nth)
+    assert b.load(0, src=4096) == HIPERR
+    host.rec_fail(b"", 0)
+    assert host.rec_name(host.rec_count() - 1) == b"synchronize"
+    assert b.load(0, src=4096) == 0 and len(b.calls("synchronize")) == 1 and len(b.calls("copy_in")) == 7
