@@ -68,3 +68,49 @@ def test_attention_f32(hq, hkv, d, lens, chunks):
             bound = 2 * (2 * dz + (T + 32) * eps) * vv.abs().max().item()
             assert (out[s] - ref).abs().max().item() <= bound, (s, T)
         assert torch.equal(got["hidden"].view(S, hq, d), got["attn_out"][:, -1])
+
+
+def _lane_sum_f32(k):
+    """Sums of rows [n][d] in fp32 by halves of a 64-wide tree (elements i and i + 64 first)."""
+    t = np.zeros((len(k), 128), np.float32)
+    t[:, :k.shape[1]] = k
+    w = 64
+    while w:
+        t = t[:, :w] + t[:, w:2 * w]
+        w //= 2
+    return t[:, 0]
+
+
+@pytest.mark.parametrize("d", [20, 64, 80, 128])
+def test_attention_f32_score_rounding(d):
+    """The rounding of a score's d products stays that of a tree: 16 keys whose exact scores are
+    equal (orders of the same elements, sum nearly 0) and one-hot values, so that the outputs are
+    the weights and their logarithms the scores' errors."""
+    from paper_2601_08670_amd.session import PcedSession
+    S, L, T, c = 64, 4, 16, 64.0
+    g = np.random.default_rng(d)
+    k = np.empty((S, L, T, d), np.float32)
+    for s in range(S):
+        for l in range(L):
+            row = g.standard_normal(d).astype(np.float32)
+            row[-1] = -row[:-1].astype(np.float64).sum()
+            for t in range(T):
+                k[s, l, t] = g.permutation(row)
+    v = torch.eye(T, d).view(1, T, 1, d).expand(L, -1, -1, -1)
+    kk = torch.from_numpy(k)
+    sess = PcedSession(n_layers=L, n_q_heads=4, n_kv_heads=1, head_dim=d, vocab=17, dtype="f32", max_queries=1,
+                       max_seqs=S, max_pages=S, max_pages_per_seq=1, device=DEV)
+    sess.load([S - 1], [T - 1] * S, [kk[s, :, :T - 1, None].contiguous().to(DEV) for s in range(S)],
+              [v[:, :T - 1].contiguous().to(DEV)] * S, [0.5] * (S - 1), reserve_tokens=1)
+    q = torch.full((S, L, 4, d), c)  # (a power of two: the products are exact)
+    out = sess.step(q.to(DEV), kk[:, :, T - 1:].contiguous().to(DEV), v[None, :, T - 1].expand(S, -1, -1, -1).contiguous().to(DEV),
+                    sess.pack_lm_head(torch.randn(17, 4 * d).to(DEV)), want=("attn_out",))["attn_out"]
+    z = np.log(out[:, :, 0, :T].cpu().double().numpy()) * d ** 0.5 / c
+
+    def rms(x):  # about each sequence's mean: the softmax does not see a common offset
+        x = x.reshape(-1, T)
+        return float(np.sqrt(np.square(x - x.mean(1, keepdims=True)).mean()))
+
+    tree = rms(_lane_sum_f32(k.reshape(-1, d)).astype(np.float64))
+    # 4096 errors of each (1.6% of sampling in their ratio), a few ulp of weights near 1/16 and their logarithms
+    assert rms(z) <= 1.1 * tree + 4 * 2.0 ** -24 * d ** 0.5 / c, (rms(z), tree)
