@@ -2732,7 +2732,8 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
 
   int k = 0, s = 0, poff = 0, end = 0, part = 0, parts = 0, full_end = 0, next_i0 = 0;
   bf16x8 qop[NQ][NC];
-  int col_end[NQ];  // keys of the lane's column in this segment end here
+  int col_end[NQ];   // keys of the lane's column in this segment end here
+  int tile_end[NQ];  // and of any of the tile's columns
   f32x4 acc[NQ][NJ], l[NQ];
   float m_ref[NQ];
   auto open = [&]() __attribute__((always_inline)) {  // segment k
@@ -2748,6 +2749,7 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
 #pragma unroll
       for (int cc = 0; cc < NC; ++cc) qop[t][cc] = as_bf16x8(*(const uint4*)(q + 32 * cc + 8 * quad));
       col_end[t] = min(end, e1.z - m.end_off);
+      tile_end[t] = min(end, e1.z - mq_col(a, s, grp, g, min(16 * t + 15, G - 1)).end_off);
       // (finite: a column without keys so far gives weights 2^(-inf - m_ref) = 0 rather than NaN)
       m_ref[t] = -1e30f;
       l[t] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -2804,20 +2806,25 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
 #pragma unroll
     for (int cc = 0; cc < NC; ++cc) vc[cc] = src[NC + cc][lane];
     const int t0 = (i + poff) * kPage;  // the page's first token in the sequence
-    if (t0 + kPage > full_end) {
-      const int tb = t0 + 4 * quad;  // token of element r = 0
-#pragma unroll
-      for (int t = 0; t < NQ; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sc[t][r] = tb + r < col_end[t] ? sc[t][r] : kNegInf;
-      // slots past the segment's end hold stale or never-written bits; their
-      // weights are 0, but 0 * NaN is NaN inside the matrix core
-      const uint32_t m01 = (tb + 0 < end ? 0x0000FFFFu : 0u) | (tb + 1 < end ? 0xFFFF0000u : 0u);
-      const uint32_t m23 = (tb + 2 < end ? 0x0000FFFFu : 0u) | (tb + 3 < end ? 0xFFFF0000u : 0u);
+    const bool masked = t0 + kPage > full_end;
+    const int tb = t0 + 4 * quad;  // token of element r = 0
+    // V rows that no column of a tile sees count as zero: later tokens, whose values
+    // may be infinite or NaN, and slots past the sequence, which hold stale or
+    // never-written bits. Their weights are 0, but 0 * NaN is NaN inside the matrix core.
+    auto mask_v = [&](int e) __attribute__((always_inline)) {
+      const uint32_t m01 = (tb + 0 < e ? 0x0000FFFFu : 0u) | (tb + 1 < e ? 0xFFFF0000u : 0u);
+      const uint32_t m23 = (tb + 2 < e ? 0x0000FFFFu : 0u) | (tb + 3 < e ? 0xFFFF0000u : 0u);
 #pragma unroll
       for (int cc = 0; cc < NC; ++cc) {
         vc[cc].x &= m01; vc[cc].y &= m23; vc[cc].z &= m01; vc[cc].w &= m23;
       }
+    };
+    if (masked) {
+#pragma unroll
+      for (int t = 0; t < NQ; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sc[t][r] = tb + r < col_end[t] ? sc[t][r] : kNegInf;
+      mask_v(tile_end[NQ - 1]);
     }
     float zmax[NQ];
     bool move = false;
@@ -2840,7 +2847,8 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
     }
     const s16x4 ones = {0x3F80, 0x3F80, 0x3F80, 0x3F80};
 #pragma unroll
-    for (int t = 0; t < NQ; ++t) {
+    for (int t = NQ - 1; t >= 0; --t) {
+      if (t < NQ - 1 && masked) mask_v(tile_end[t]);  // (an earlier tile's tokens: none of them later)
       // (v_exp_f32: results below 2^-126 are 0, as good as any such weight beside one of 2^-8 or more)
       f32x2 p01, p23;
       p01[0] = __builtin_amdgcn_exp2f(fmaf(sc[t][0], a.scale_log2, -m_ref[t]));
