@@ -89,7 +89,7 @@ struct Layout {
   int pf_rows;          // rows of one prefill chunk (sequences x suffix tokens)
   size_t pf_proj_cols;  // slices x columns per row of the prefill projection partials
   size_t pf_proj_elems; // floats of that buffer
-  int rows_pad, nblk_fuse, nblk_agg, nchunk, max_work;
+  int rows_pad, nblk_fuse, nchunk, max_work;
   size_t seg_slots;     // segment descriptors of the attention plan
   size_t part_slots;
   size_t part_cols;  // slices x columns one row of the projection partial buffer holds
@@ -101,7 +101,6 @@ Layout make_layout(const pced_config& c) {
   const int G = c.n_q_heads / c.n_kv_heads;
   L.rows_pad = ceil_div(c.max_seqs, kLmRowsPad) * kLmRowsPad;
   L.nblk_fuse = ceil_div(c.vocab, 512);  // at most: the stand-alone fuse's slices are 512 or 1024 tokens
-  L.nblk_agg = ceil_div(c.vocab, kAggSlice);
   L.nchunk = ceil_div(c.vocab, kBetaChunk);
   // every attention chunk holds at least one page: chunks <= pages in use (a
   // prefill chunk's rows count their shared pages once per row)
@@ -475,9 +474,10 @@ FuseArgs fuse_args(pced_ctx* c, const float* logits, int32_t* tokens_out, int to
 pced_status run_fuse(pced_ctx* c, const float* logits, bool refresh_beta, int32_t* tokens_out,
                      int tok_stride, const pced_step_out* extra, hipStream_t st) {
   const pced_config& cfg = c->cfg;
-  FuseArgs f = fuse_args(c, logits, tokens_out, tok_stride, extra,
-                         cfg.aggregation != PCED_AGG_MAX ? c->lay.nblk_agg
-                                                         : ceil_div(cfg.vocab, fuse_slice(cfg.vocab, c->B, c->num_cus)));
+  const int max_n = *std::max_element(c->n_experts.begin(), c->n_experts.end());
+  const int slice = cfg.aggregation != PCED_AGG_MAX ? agg_slice(cfg.vocab, c->B, max_n, c->num_cus)
+                                                    : fuse_slice(cfg.vocab, c->B, c->num_cus);
+  FuseArgs f = fuse_args(c, logits, tokens_out, tok_stride, extra, ceil_div(cfg.vocab, slice));
   if (c->dynamic_beta && refresh_beta) {
     BetaArgs b{};
     b.logits = logits;
@@ -518,7 +518,7 @@ pced_status run_fuse(pced_ctx* c, const float* logits, bool refresh_beta, int32_
     g.part = f.part;
     g.V = cfg.vocab;
     g.nchunk = c->lay.nchunk;
-    g.nblk = c->lay.nblk_agg;
+    g.nblk = f.nblk;
     g.product = cfg.aggregation == PCED_AGG_POE;
     {
       ProfScope ps(c, PCED_PROF_FUSE, 2.0 * (c->NE + c->S) * cfg.vocab * 4, 0);

@@ -13,7 +13,7 @@ constexpr int kFuseBlock = 256;    // threads of the fuse work-groups
 constexpr int kFuseInlineQueries = 32;  // queries whose row offsets the fuse gets in its kernel arguments
 constexpr int kBetaChunk = 4096;   // vocab entries per beta work-group
 constexpr int kBetaFoldMax = 1024; // experts of a query whose beta the fuse sums itself (LDS)
-constexpr int kAggSlice = 256;     // vocab entries per MoE / PoE work-group
+constexpr int kAggSlice = 256;     // vocab entries per MoE / PoE work-group, or wave
 constexpr int kAggExperts = 256;   // experts whose coefficients it holds in LDS at a time
 constexpr int kLmRowsPad = 48;     // hidden-state rows are padded to a multiple of this
 constexpr int kLmRowsMTW = 9;      // many-row LM head: row tiles per wave (up to 32 * 9 = 288 rows at once)
@@ -193,7 +193,7 @@ struct AggArgs {
   const float* jsd_part;    // optional [sum N][nchunk]: beta is summed from these and stored to beta_out
   float* beta_out;
   float* lse_part;          // [sum N][nchunk][2]
-  float* part;              // [B][nblk][5] slice candidates for k_fuse_final (kAggSlice tokens each)
+  float* part;              // [B][nblk][5] slice candidates for k_fuse_final (agg_slice() tokens each)
   int V, nchunk, nblk, product;  // product: 0 = mixture (MoE), 1 = product (PoE)
 };
 
@@ -324,6 +324,9 @@ hipError_t launch_fuse(const FuseArgs& a, int n_queries, hipStream_t st, const T
                        const Timing* tm_merge = nullptr);
 // vocabulary tokens per work-group of the stand-alone fuse (1024, or 512 for few queries)
 int fuse_slice(int V, int n_queries, int num_cus);
+// vocabulary tokens per work-group of the MoE / PoE aggregation (kAggSlice, or 4 kAggSlice for many
+// queries of few experts); max_n: most experts of any query
+int agg_slice(int V, int n_queries, int max_n, int num_cus);
 hipError_t launch_beta_mean(const BetaArgs& a, int n_queries, hipStream_t st);
 hipError_t launch_agg(const AggArgs& a, int n_exp, int n_queries, hipStream_t st, const Timing* tm = nullptr);
 // the final per-query merge alone (after an LM head with the fused epilogue)

@@ -2497,7 +2497,7 @@ __device__ __forceinline__ float agg_row_lse(const AggArgs& a, int e) {
   return m + logf(sum);
 }
 
-// Per (query, slice of kAggSlice = 256 tokens): per token v the experts' weighted
+// Per (query, slice of agg_slice() tokens): per token v the experts' weighted
 // log-probabilities j_k = log pi_k + c_k(v) - lse_k, then
 //   MoE: log sum_k exp(j_k)  (running max and rescaled sum)
 //   PoE: sum_k pi_k (c_k(v) - lse_k)
@@ -2505,23 +2505,24 @@ __device__ __forceinline__ float agg_row_lse(const AggArgs& a, int e) {
 // tokens go to the same partial buffer k_fuse_final merges. As in k_fuse, the
 // four waves take a quarter of the experts each and a lane 4 tokens (one 16-byte
 // load per row, NB rows in flight); the sum is rescaled once per batch of rows,
-// and the waves' states meet in LDS. The experts' lse come from the chunk
+// and the waves' states meet in LDS. WIDE: the waves split the tokens instead, 256
+// each, and every wave takes all experts. The experts' lse come from the chunk
 // partials in every block (8 KiB at 32 experts), kAggExperts of them at a time
 // in LDS. 32 experts x 128256: 12.5 us (one token per thread, row after row:
 // 17.2 us, and 7.8 us for a launch that finished lse).
-template <bool VEC>
+template <bool VEC, bool WIDE>
 __global__ __launch_bounds__(256) void k_agg(AggArgs a) {
 #pragma clang fp contract(off)
-  constexpr int NB = 8;
+  constexpr int NB = 8, LS = WIDE ? 1 : kAggSlice;
   __shared__ float s_beta[kAggExperts], s_lse[kAggExperts], s_logw[kAggExperts];
-  __shared__ float sm[4][kAggSlice], ssum[4][kAggSlice], sj[4][kAggSlice];
-  __shared__ int sk[4][kAggSlice];
+  __shared__ float sm[4][LS], ssum[4][LS], sj[4][LS];
+  __shared__ int sk[4][LS];
   const int b = blockIdx.y, lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int s0 = a.query_seq0[b];
   const int N = a.query_seq0[b + 1] - s0 - 1;
   const int e0 = a.query_exp0[b];
-  const int vb = blockIdx.x * kAggSlice;
+  const int vb = WIDE ? (blockIdx.x * 4 + wave) * kAggSlice : blockIdx.x * kAggSlice;
   const float* L0 = a.logits + (size_t)s0 * a.V;
   const float4 sa4 = load_tok4<VEC>(L0, vb + 4 * lane, a.V);
   const float sa[4] = {sa4.x, sa4.y, sa4.z, sa4.w};
@@ -2542,7 +2543,7 @@ __global__ __launch_bounds__(256) void k_agg(AggArgs a) {
       }
     }
     __syncthreads();
-    const int per = (n + 3) / 4, lo = wave * per, hi = min(n, lo + per) - 1;  // (in the group)
+    const int per = (n + 3) / 4, lo = WIDE ? 0 : wave * per, hi = (WIDE ? n : min(n, lo + per)) - 1;  // (in the group)
     for (int kb = lo; kb <= hi; kb += NB) {
       float4 x[NB];
 #pragma unroll
@@ -2583,32 +2584,40 @@ __global__ __launch_bounds__(256) void k_agg(AggArgs a) {
       }
     }
   }
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    sm[wave][4 * lane + c] = m[c];
-    ssum[wave][4 * lane + c] = sum[c];
-    sj[wave][4 * lane + c] = jb[c];
-    sk[wave][4 * lane + c] = bk[c];
-  }
-  __syncthreads();
-  const int t = threadIdx.x, v = vb + t;
-  float mt = kNegInf, tot = 0.f, j = sj[0][t];
-  int k = sk[0][t];
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    mt = fmaxf(mt, sm[w][t]);
-    // (an expert of a later wave may have a lower number once a query has several groups of experts)
-    const float jw = sj[w][t];
-    const int kw = sk[w][t];
-    if (jw > j || (jw == j && kw < k)) { j = jw; k = kw; }
-  }
-#pragma unroll
-  for (int w = 0; w < 4; ++w) tot += a.product ? ssum[w][t] : ssum[w][t] * exp_rel(sm[w][t], mt);
   Top2 c{kNegInf, 0x7FFFFFFF, 0, kNegInf, 0x7FFFFFFF};
-  if (v < a.V) {
-    c.v1 = a.product ? tot : mt + logf(tot);
-    c.i1 = v;
-    c.k1 = k;
+  if constexpr (WIDE) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int v = vb + 4 * lane + u;
+      if (v < a.V) c = merge(c, Top2{a.product ? sum[u] : m[u] + logf(sum[u]), v, bk[u], kNegInf, 0x7FFFFFFF});
+    }
+  } else {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      sm[wave][4 * lane + c] = m[c];
+      ssum[wave][4 * lane + c] = sum[c];
+      sj[wave][4 * lane + c] = jb[c];
+      sk[wave][4 * lane + c] = bk[c];
+    }
+    __syncthreads();
+    const int t = threadIdx.x, v = vb + t;
+    float mt = kNegInf, tot = 0.f, j = sj[0][t];
+    int k = sk[0][t];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      mt = fmaxf(mt, sm[w][t]);
+      // (an expert of a later wave may have a lower number once a query has several groups of experts)
+      const float jw = sj[w][t];
+      const int kw = sk[w][t];
+      if (jw > j || (jw == j && kw < k)) { j = jw; k = kw; }
+    }
+#pragma unroll
+    for (int w = 0; w < 4; ++w) tot += a.product ? ssum[w][t] : ssum[w][t] * exp_rel(sm[w][t], mt);
+    if (v < a.V) {
+      c.v1 = a.product ? tot : mt + logf(tot);
+      c.i1 = v;
+      c.k1 = k;
+    }
   }
   c = block_top2<4>(c);
   if (threadIdx.x == 0) {
@@ -3775,6 +3784,18 @@ int fuse_slice(int V, int n_queries, int num_cus) {
   return (long)((V + 1023) / 1024) * n_queries >= num_cus ? 1024 : 512;
 }
 
+int agg_slice(int V, int n_queries, int max_n, int num_cus) {
+  // Four times the tokens per work-group (a wave's own 256 tokens and all experts,
+  // instead of a quarter of the experts) once that leaves a work-group per compute
+  // unit and 8 experts: the log-sum-exp finish and the waves' meeting weigh more the
+  // fewer experts a wave has, and less than the memory round trips of a long column of
+  // experts on an idle GPU. Mixture, frozen beta, V = 128256, split experts / split
+  // tokens: 1 expert x 64 queries 178 / 66 us, 8 x 16 75 / 46, 16 x 4 35 / 32, 16 x 2
+  // 22.6 / 25.2, 32 x 1 22.2 / 32.7; V = 32000: 8 x 8 18.4 / 17.5, 8 x 4 15.9 / 16.7.
+  const long wide = (long)((V + 4 * kAggSlice - 1) / (4 * kAggSlice)) * n_queries;
+  return wide * 8 >= (long)num_cus * max_n ? 4 * kAggSlice : kAggSlice;
+}
+
 template <int SW, bool BETA>
 hipError_t launch_fuse_sw(const FuseArgs& a, dim3 g, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   const bool vec = a.V % 4 == 0 && a.V >= 4;
@@ -3810,8 +3831,13 @@ hipError_t launch_agg(const AggArgs& a, int n_exp, int n_queries, hipStream_t st
   hipError_t e = go(k_agg_lse, dim3(a.nchunk, n_exp), dim3(256), 0, st, t0(tm), nullptr, a);
   if (e != hipSuccess) return e;
   const dim3 g(a.nblk, n_queries);
-  return a.V % 4 == 0 ? go(k_agg<true>, g, dim3(256), 0, st, nullptr, t1(tm), a)
-                      : go(k_agg<false>, g, dim3(256), 0, st, nullptr, t1(tm), a);
+  const bool vec = a.V % 4 == 0;
+  // a.nblk: slices of agg_slice() tokens
+  if ((a.V + a.nblk - 1) / a.nblk > kAggSlice)
+    return vec ? go(k_agg<true, true>, g, dim3(256), 0, st, nullptr, t1(tm), a)
+               : go(k_agg<false, true>, g, dim3(256), 0, st, nullptr, t1(tm), a);
+  return vec ? go(k_agg<true, false>, g, dim3(256), 0, st, nullptr, t1(tm), a)
+             : go(k_agg<false, false>, g, dim3(256), 0, st, nullptr, t1(tm), a);
 }
 
 hipError_t launch_fuse_final(const FuseArgs& a, int n_queries, hipStream_t st, const Timing* tm) {

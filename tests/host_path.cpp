@@ -91,6 +91,7 @@ hipError_t launch_lmhead(const LmArgs&, bool, hipStream_t, const Timing*) { retu
 hipError_t launch_beta(const BetaArgs&, int, int, bool, hipStream_t, const Timing*) { return note("beta"); }
 hipError_t launch_fuse(const FuseArgs&, int, hipStream_t, const Timing*, const Timing*) { return note("fuse"); }
 int fuse_slice(int, int, int) { return 512; }
+int agg_slice(int, int, int, int) { return kAggSlice; }
 hipError_t launch_beta_mean(const BetaArgs&, int, hipStream_t) { return note("beta_mean"); }
 hipError_t launch_agg(const AggArgs&, int, int, hipStream_t, const Timing*) { return note("agg"); }
 hipError_t launch_fuse_final(const FuseArgs&, int, hipStream_t, const Timing*) { return note("fuse_final"); }

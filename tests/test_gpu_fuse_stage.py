@@ -42,6 +42,8 @@ def _reference(s, n_exp, rel, beta, rule):
     ([1], 5), ([3, 1], 255), ([33], 4097), ([8, 31], 1026), ([32, 5, 64], 8192),
     ([257], 260), ([600, 2], 515),     # more experts than one group
     ([1100], 36),                      # more than the fuse sums beta for itself
+    # many queries of few experts: the aggregation's waves split the tokens
+    ([1] * 40, 5), ([1, 2] * 30, 257), ([3] * 140, 1023), ([2] * 50 + [1], 1026), ([1] * 40 + [4], 4099),
 ])
 @pytest.mark.parametrize("rule", ["max", "moe", "poe"])
 @pytest.mark.parametrize("fixed", [False, True])
@@ -76,6 +78,11 @@ def test_fuse_stage(experts, vocab, rule, fixed):
             assert float(score[tok]) > float(two[0]) - 2 * tol
             assert 1 <= win <= n and float(every[win - 1, tok]) > float(every[:, tok].max()) - 2 * tol
             e += n
+
+
+@pytest.mark.parametrize("rule", ["moe", "poe"])
+def test_fuse_stage_more_experts_than_one_group_beside_many_queries(rule):
+    test_fuse_stage([1] * 4200 + [257], 1030, rule, True)  # (4201 x 2 work-groups: split tokens, 257 experts)
 
 
 @pytest.mark.parametrize("rule", ["moe", "poe"])
