@@ -491,9 +491,18 @@ pced_status run_fuse(pced_ctx* c, const float* logits, bool refresh_beta, int32_
     b.nchunk = c->lay.nchunk;
     b.query_exp0 = c->at<int32_t>(c->lay.query_exp0);
     ProfScope ps(c, PCED_PROF_BETA, (double)(c->S + 2.0 * c->NE) * cfg.vocab * 4, 0);
-    // the launch that uses beta sums its partials itself, unless their mean over a query is wanted
-    // or a query has more experts than the fuse holds
-    const bool sums = cfg.beta_scalar || (cfg.aggregation == PCED_AGG_MAX && f.max_n > kBetaFoldMax);
+    // the launch that uses beta sums its partials itself, unless their mean over a query is wanted,
+    // a query has more experts than the fuse holds, or the fuse's work-groups, each of which sums,
+    // are many (more than 8 per compute unit, or 2 where the rows' loads are not whole 16 bytes and
+    // wait longer behind the sums; or 1600 partials read per compute unit). First step, sums in a
+    // launch / in the fuse, queries x experts over tokens: 16 x 1 over 32000 (512 work-groups) 20.6 /
+    // 19.3 us, 64 x 1 over 32000 (2048) 31.4 / 30.5, 64 x 1 over 128256 (8064) 84.6 / 88.5; 8 x 8 over
+    // 50257 (400) 33.7 / 33.3, 16 x 1 over 50257 (800) 28.2 / 30.0, 64 x 1 over 50257 (3200) 51.4 /
+    // 66.8; 8 x 8 over 128256 (258000 partials) 37.6 / 36.7, 16 x 16 over 128256 (1.03 M) 83.9 / 85.5.
+    const double groups = (double)f.nblk * c->B;
+    const bool many = groups > (double)c->num_cus * (cfg.vocab % 4 == 0 ? 8 : 2) ||
+                      groups * f.max_n * b.nchunk > 1600.0 * c->num_cus;
+    const bool sums = cfg.beta_scalar || (cfg.aggregation == PCED_AGG_MAX && (f.max_n > kBetaFoldMax || many));
     HIP_OK(launch_beta(b, c->S, c->NE, sums, st, ps.timing()));
     if (cfg.beta_scalar) HIP_OK(launch_beta_mean(b, c->B, st));
     if (!sums) {

@@ -43,6 +43,7 @@ def _reference(s, n_exp, rel, beta, rule):
     ([257], 260), ([600, 2], 515),     # more experts than one group
     ([1100], 36),                      # more than the fuse sums beta for itself
     # many queries of few experts: the aggregation's waves split the tokens
+    ([1] * 300, 1537),                 # more work-groups than sum beta for themselves
     ([1] * 40, 2), ([1] * 40, 5), ([1, 2] * 30, 257), ([3] * 140, 1023), ([2] * 50 + [1], 1026), ([1] * 40 + [4], 4099),
 ])
 @pytest.mark.parametrize("rule", ["max", "moe", "poe"])
