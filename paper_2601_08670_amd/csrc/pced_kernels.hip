@@ -3663,6 +3663,22 @@ static int wide_tiles_for(int rows, bool groups) {
   return groups ? std::max(mth, 5) : mth <= 4 ? 4 : mth <= 6 ? 6 : 9;
 }
 
+// Row groups leave the GPU idle where the vocabulary gives few 256-row chunks: the
+// 48-row kernel spreads the rows over more work-groups, and while these fit the 256
+// compute units at once it takes as long for 1200 rows as for 289. At hidden 4096,
+// V = 4000 (16 chunks), 48-row kernel / row groups: 384 rows 68.7 / 74.8 us, 577 rows
+// 70.0 / 84.5, 800 rows (272 work-groups) 128.7 / 103.6. Two exceptions: groups of 160
+// rows keep up where the hidden size is long (289 rows over 8000 tokens: 68.5 / 65.0 us
+// at 4096, but 25.5 / 27.8 at 1024), and at short hidden sizes, where a launch and the
+// packing of x weigh most, larger groups do not in two rounds either (480 rows over
+// 8000 tokens at 256: 21.9 / 24.3 us; 384 rows over 16000, groups of 192: 22.8 / 21.4).
+// The rule looks at the rows alone, so that a step whose logits are wanted and one
+// with the fused token choice run the same kernel and choose the same tokens.
+static bool few_chunks(int M, int V, int K, int mth) {
+  const long rounds = ((long)((V + 255) / 256) * ((M + kLmRowsPad - 1) / kLmRowsPad) + 255) / 256;
+  return (rounds == 1 && !(mth == 5 && K >= 4096)) || (rounds == 2 && K <= 512 && mth >= 7);
+}
+
 LmWidePlan lmhead_wide_plan(int M, int V, int K) {
   LmWidePlan p;
   if (M <= kLmRowsPad || K % 256 != 0) return p;
@@ -3670,7 +3686,7 @@ LmWidePlan lmhead_wide_plan(int M, int V, int K) {
   p.groups = (M + kLmWideMaxRows - 1) / kLmWideMaxRows;
   p.rows = ((M + 15) / 16 + p.groups - 1) / p.groups * 16;
   p.mth = wide_tiles_for(p.rows, p.groups > 1);
-  return p;
+  return p.groups > 1 && few_chunks(M, V, K, p.mth) ? LmWidePlan{} : p;
 }
 
 LmWidePlan lmhead_wide_plan_queries(const int32_t* seq_off, int n_queries, int V, int K, int max_packed_rows) {

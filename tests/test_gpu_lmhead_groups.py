@@ -15,6 +15,10 @@ DEV = "cuda:0"
     (321, 4096, 512, True), (385, 17, 256, False), (449, 2300, 256, True), (576, 513, 1024, False),
     (577, 300, 256, False),      # three groups
     (1200, 2049, 256, False),
+    # vocabularies of enough chunks for row groups (the ones above fit the 48-row kernel in one round)
+    (289, 9700, 256, False), (289, 40, 4096, True), (321, 9500, 512, True), (385, 9001, 1024, False),
+    (449, 9000, 1024, True), (576, 7003, 768, False), (577, 6000, 1024, False), (1200, 3000, 1024, False),
+    (480, 8000, 256, False), (480, 16400, 256, False),   # short hidden size: two rounds of the 48-row kernel, and more
 ])
 def test_lmhead_row_groups(rows, vocab, hidden, noalloc):
     from paper_2601_08670_amd import _lib
@@ -43,7 +47,8 @@ def test_lmhead_row_groups(rows, vocab, hidden, noalloc):
     ([287, 1], 1003),               # one query fills a group
     ([70, 141, 3, 100, 30], 515),   # ragged groups
     ([1] * 150 + [13], 300),        # many queries per group
-    ([288, 2], 300),                # a query larger than a group: not fused
+    ([288, 2], 300), ([288, 2], 9500),  # a query larger than a group: not fused
+    ([90] * 4, 8300), ([287, 1], 9500), ([70, 141, 3, 100, 30], 8303), ([1] * 150 + [13], 9500),  # (row groups, as above)
 ])
 def test_fused_choice_over_row_groups(experts, vocab):
     from paper_2601_08670_amd.session import PcedSession
