@@ -102,11 +102,9 @@ Layout make_layout(const pced_config& c) {
   L.rows_pad = ceil_div(c.max_seqs, kLmRowsPad) * kLmRowsPad;
   L.nblk_fuse = ceil_div(c.vocab, 512);  // at most: the stand-alone fuse's slices are 512 or 1024 tokens
   L.nchunk = ceil_div(c.vocab, kBetaChunk);
-  // every attention chunk holds at least one page: chunks <= pages in use (a
-  // prefill chunk's rows count their shared pages once per row)
+  // every attention chunk holds at least one page of its own (the sequences' pages
+  // are distinct, and the prefill plans by sequences too): chunks <= pages in use
   L.max_work = c.max_pages;
-  if (c.ffn_dim > 0)
-    L.max_work = std::max<long>(L.max_work, (long)std::max(c.max_seqs, kPrefillRows) * c.max_pages_per_seq);
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t r = o; o = align_up(o + bytes); return r; };
   // metadata block, uploaded by one copy at load
@@ -185,10 +183,10 @@ Layout make_layout(const pced_config& c) {
   L.pf_len0 = take(PR * 4);
   L.pf_pt = take(PR * c.max_pages_per_seq * 4);
   L.pf_tok = take(PR * 4);
-  // the attention's token groups (at most one per row)
-  L.pf_glen0 = take(PR * 4);
-  L.pf_gpt = take(PR * c.max_pages_per_seq * 4);
-  L.pf_nparts = take(PR * 4);
+  // the attention's sequences
+  L.pf_glen0 = take(dec * S * 4);
+  L.pf_gpt = take(dec * S * c.max_pages_per_seq * 4);
+  L.pf_nparts = take(dec * S * 4);
   L.pf_rho = take(PR * 4);
   L.pf_h = take(PR * c.hidden * 4);
   L.pf_a = take(PR * c.hidden * 2);

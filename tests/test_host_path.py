@@ -150,3 +150,18 @@ def test_failing_host_load_waits_for_its_copies(host, call, nth):
     host.rec_fail(b"", 0)
     assert host.rec_name(host.rec_count() - 1) == b"synchronize"
     assert b.load(0, src=4096) == 0 and len(b.calls("synchronize")) == 1 and len(b.calls("copy_in")) == 7
+
+
+def _workspace(host, **kw):
+    c = dict(n_layers=32, n_q_heads=32, n_kv_heads=8, head_dim=128, vocab=1000, dtype="bf16", max_queries=1,
+             max_seqs=33, max_pages=33 * 130, max_pages_per_seq=130)
+    c.update(kw)
+    return host.pced_workspace_bytes(ctypes.byref(_lib.make_config(**c)))
+
+
+def test_attention_plan_is_sized_by_pages(host):
+    # a page more per sequence costs the rows' and the sequences' page tables (4 bytes a row) and room for
+    # partial states, but no plan entries (520 bytes each) per suffix row
+    grow = _workspace(host, ffn_dim=512, max_pages_per_seq=131) - _workspace(host, ffn_dim=512)
+    plain = _workspace(host, max_pages_per_seq=131) - _workspace(host)
+    assert grow - plain <= 4 * (2304 + 33) + 131 * 16 * 64 * 8 + 8 * 256
