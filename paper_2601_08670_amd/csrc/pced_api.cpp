@@ -81,7 +81,7 @@ constexpr size_t kPartBytes = (size_t)128 << 20;  // attention partial states of
 struct Layout {
   size_t len0, page_table, seq_query, query_seq0, query_exp0, exp_seq, exp_query, prior, logw, beta_fixed,
       load_items, src_k, src_v, meta_end;
-  size_t chunk_info, seg, nparts, work_pages, prev_tok, beta, part_acc, part_ml, x, x_layers, logits,
+  size_t chunk_info, seg, nparts, work_pages, prev_tok, beta, part_acc, part_ml, x, logits,
       rho, x_packed, fuse_part, lse_part, jsd_part, syn_q, syn_k, syn_v, dec_h, dec_a, dec_act, dec_ss, dec_rho, dec_part,
       rope, pf_len0, pf_pt, pf_tok, pf_glen0, pf_gpt, pf_nparts, pf_rho, pf_h, pf_a, pf_act, pf_ss, pf_q, pf_x, pf_part_acc, pf_part_ml, pf_proj,
       load_stage, stage_bytes, total;
@@ -139,8 +139,6 @@ Layout make_layout(const pced_config& c) {
   L.part_acc = take(L.part_slots * G * c.head_dim * 4);
   L.part_ml = take(2 * L.part_slots * G * 2 * 4);
   L.x = take((size_t)L.rows_pad * c.hidden * es);
-  // the outputs of the layers before the last, for launches that take several layers
-  L.x_layers = take(c.n_layers > 1 ? S * c.n_layers * c.hidden * es : 0);
   L.logits = take(S * c.vocab * 4);
   L.rho = take((size_t)L.rows_pad * 4);
   // the many-row LM head's operand-ordered copy of x (bf16, more than 48 rows)
@@ -1197,8 +1195,7 @@ pced_status run_step(pced_ctx* c, const void* q, const void* k_new, const void* 
   at.n_chunks = plan.chunks;
   at.acc_layer_bytes = slots * c->G * cfg.head_dim * es_part;
   at.ml_layer = slots * c->G * 2;
-  at.x_layers = c->at<void>(c->lay.x_layers);
-  at.x_layer_bytes = (size_t)c->S * cfg.hidden * esize_of(cfg);
+  at.x_last_only = 1;
   for (int l = 0; l < cfg.n_layers; l += per_launch) {
     at.layer = l;
     at.launch_layers = std::min(per_launch, cfg.n_layers - l);

@@ -63,15 +63,12 @@ struct AttnArgs {
   const int32_t* work_pages;// [C][kMaxSplitPages] physical pages of each chunk
   float* part_acc;          // [S*Hkv][split_stride][G][D] partial outputs (bf16 path: normalised, as bf16)
   float* part_ml;           // [S*Hkv][split_stride][G][2] (running max in log2 units, sum)
-  void* x_out;              // [S][Hq*D] layer output, storage type
+  void* x_out;              // [S][Hq*D] layer output, storage type (null: not wanted)
   float* attn_out;          // optional [S][L][Hq][D]
   float* hidden_out;        // optional [S][Hq*D] (last layer only)
   int launch_layers, n_chunks;             // layers of this launch; chunks C of the plan
   size_t acc_layer_bytes, ml_layer;        // partial states: bytes of part_acc and floats of part_ml per layer
-  // with x_layers, x_out receives the last layer's output and x_layers
-  // [L][S][Hq*D] the others' (is_last_layer is then set by the kernel)
-  void* x_layers;
-  size_t x_layer_bytes;
+  int x_last_only;          // x_out receives the last layer's output alone (the kernel sets is_last_layer)
   int n_seqs, n_layers, layer, n_q_heads, n_kv_heads, group;
   int max_pages, maxpps, t, split_stride, is_last_layer;
   int kv_reread;            // prefill (k_attn_prefill): pages are read by several token groups

@@ -378,9 +378,9 @@ __device__ __forceinline__ void select_layer(AttnArgs& a, int l) {
   a.layer += l;
   a.part_acc = (float*)((char*)a.part_acc + l * a.acc_layer_bytes);
   a.part_ml += l * a.ml_layer;
-  if (a.x_layers) {
+  if (a.x_last_only) {
     a.is_last_layer = a.layer == a.n_layers - 1;
-    if (!a.is_last_layer) a.x_out = (char*)a.x_layers + a.layer * a.x_layer_bytes;
+    if (!a.is_last_layer) a.x_out = nullptr;
   }
 }
 
@@ -399,11 +399,11 @@ __device__ __forceinline__ void write_o4(const AttnArgs& a, int s, int head, int
     uint2 pk;
     pk.x = b0 | (b1 << 16);
     pk.y = b2 | (b3 << 16);
-    *(uint2*)((uint16_t*)a.x_out + xo) = pk;
+    if (a.x_out) *(uint2*)((uint16_t*)a.x_out + xo) = pk;
     if (a.is_last_layer && a.hidden_out)
       *(float4*)(a.hidden_out + xo) = make_float4(bf2f(b0), bf2f(b1), bf2f(b2), bf2f(b3));
   } else {
-    *(float4*)((float*)a.x_out + xo) = o;
+    if (a.x_out) *(float4*)((float*)a.x_out + xo) = o;
     if (a.is_last_layer && a.hidden_out) *(float4*)(a.hidden_out + xo) = o;
   }
 }
@@ -506,8 +506,9 @@ __device__ __forceinline__ void merge_store(const AttnArgs& a, int s, int head, 
   }
   const int d = 8 * lane;
   const size_t row = (size_t)s * a.n_q_heads + head;
-  *(uint4*)((uint16_t*)a.x_out + row * D + d) =
-      make_uint4(b[0] | (b[1] << 16), b[2] | (b[3] << 16), b[4] | (b[5] << 16), b[6] | (b[7] << 16));
+  if (a.x_out)
+    *(uint4*)((uint16_t*)a.x_out + row * D + d) =
+        make_uint4(b[0] | (b[1] << 16), b[2] | (b[3] << 16), b[4] | (b[5] << 16), b[6] | (b[7] << 16));
   if (a.attn_out) {
     float* p = a.attn_out + (((size_t)s * a.n_layers + layer) * a.n_q_heads + head) * D + d;
     *(float4*)p = make_float4(o[0], o[1], o[2], o[3]);

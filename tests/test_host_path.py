@@ -165,3 +165,11 @@ def test_attention_plan_is_sized_by_pages(host):
     grow = _workspace(host, ffn_dim=512, max_pages_per_seq=131) - _workspace(host, ffn_dim=512)
     plain = _workspace(host, max_pages_per_seq=131) - _workspace(host)
     assert grow - plain <= 4 * (2304 + 33) + 131 * 16 * 64 * 8 + 8 * 256
+
+
+def test_workspace_holds_one_layer_output(host):
+    # a layer more: pced_generate's q, k and v rows (12288 bytes a sequence), room for partial states and for
+    # staging a cache from host memory, but no copy of the layer's output (8192 bytes a sequence)
+    short = dict(max_pages=33, max_pages_per_seq=1)
+    grow = _workspace(host, n_layers=33, **short) - _workspace(host, n_layers=32, **short)
+    assert grow <= 33 * 12288 + 33 * 8 * (2048 + 64) + 2 * 16 * 8 * 128 * 2 + 33 * 4096
