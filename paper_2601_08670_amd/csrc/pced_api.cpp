@@ -84,7 +84,7 @@ struct Layout {
   size_t chunk_info, seg, nparts, work_pages, prev_tok, beta, part_acc, part_ml, x, logits,
       rho, x_packed, fuse_part, lse_part, jsd_part, syn_q, syn_k, syn_v, dec_h, dec_a, dec_act, dec_ss, dec_rho, dec_part,
       rope, pf_len0, pf_pt, pf_tok, pf_glen0, pf_gpt, pf_nparts, pf_rho, pf_h, pf_a, pf_act, pf_ss, pf_q, pf_x, pf_part_acc, pf_part_ml, pf_proj,
-      load_stage, stage_bytes, total;
+      stage_bytes, total;
   int packed_rows;      // rows x_packed holds
   int pf_rows;          // rows of one prefill chunk (sequences x suffix tokens)
   size_t pf_proj_cols;  // slices x columns per row of the prefill projection partials
@@ -136,7 +136,13 @@ Layout make_layout(const pced_config& c) {
   // (room for one layer at least; for all of them up to kPartBytes)
   L.part_slots = (size_t)c.max_seqs * c.n_kv_heads * c.max_pages_per_seq;
   L.part_slots = std::max(L.part_slots, std::min(L.part_slots * c.n_layers, kPartBytes / ((size_t)G * c.head_dim * 4)));
-  L.part_acc = take(L.part_slots * G * c.head_dim * 4);
+  // The region also stages caches loaded from host memory (a load follows and is
+  // followed by the steps on their stream, and no partial state outlives its launches): the
+  // longest sequence's K and V, at most kLoadStage (longer ones go in pieces), at
+  // least one page of one layer.
+  const size_t page_bytes = (size_t)kPage * c.n_kv_heads * c.head_dim * es;
+  L.stage_bytes = align_up(2 * std::max(page_bytes, std::min(kLoadStage / 2, page_bytes * c.max_pages_per_seq * c.n_layers)));
+  L.part_acc = take(std::max(L.part_slots * G * c.head_dim * 4, L.stage_bytes));
   L.part_ml = take(2 * L.part_slots * G * 2 * 4);
   L.x = take((size_t)L.rows_pad * c.hidden * es);
   L.logits = take(S * c.vocab * 4);
@@ -196,11 +202,6 @@ Layout make_layout(const pced_config& c) {
   L.pf_part_ml = take(2 * PR * c.n_kv_heads * kPrefillParts * G * 2 * 4);  // (bf16 states: pf_part_acc holds twice as many)
   L.pf_proj_elems = std::max(PR * max_cols, (size_t)kLmRowsPad * L.part_cols);
   L.pf_proj = take(L.pf_proj_elems * 4);
-  // staging of caches loaded from host memory: the longest sequence's K and V, at
-  // most kLoadStage (longer ones go in pieces), at least one page of one layer
-  const size_t page_bytes = (size_t)kPage * c.n_kv_heads * c.head_dim * es;
-  L.stage_bytes = align_up(2 * std::max(page_bytes, std::min(kLoadStage / 2, page_bytes * c.max_pages_per_seq * c.n_layers)));
-  L.load_stage = take(L.stage_bytes);
   L.total = o;
   return L;
 }
@@ -396,7 +397,7 @@ bool is_device_memory(const void* p) {
 }
 
 // Host path of pced_load_caches: a sequence's cache, held in host memory as
-// [L][len][Hkv][D], is copied as it is into the workspace's staging region and
+// [L][len][Hkv][D], is copied as it is into the workspace (the partial states' region) and
 // moved from there into the pool's tiles by the load kernel. A piece is as many
 // whole layers as the region holds (K in its first half, V in its second), or,
 // where one layer does not fit, as many of its pages. Copies and kernels follow
@@ -405,7 +406,7 @@ pced_status load_from_host(pced_ctx* c, LoadArgs a, int s, int len, const char* 
                            hipStream_t st) {
   const size_t row = (size_t)c->cfg.n_kv_heads * c->cfg.head_dim * esize_of(c->cfg);
   const size_t half = c->lay.stage_bytes / 2;
-  char* stage = c->at<char>(c->lay.load_stage);
+  char* stage = c->at<char>(c->lay.part_acc);
   a.items = nullptr;
   a.one_s = s;
   a.one_k = stage;

@@ -173,3 +173,14 @@ def test_workspace_holds_one_layer_output(host):
     short = dict(max_pages=33, max_pages_per_seq=1)
     grow = _workspace(host, n_layers=33, **short) - _workspace(host, n_layers=32, **short)
     assert grow <= 33 * 12288 + 33 * 8 * (2048 + 64) + 2 * 16 * 8 * 128 * 2 + 33 * 4096
+
+
+def test_host_caches_are_staged_in_the_partial_states_region(host):
+    # K and V of 130 pages x 32 layers: 130 MiB, moved in pieces of 2 x 32 MiB; the partial states take 34 MiB
+    shape = dict(n_q_heads=8, max_seqs=2, max_pages=260)
+    assert 64 << 20 < _workspace(host, **shape) < 80 << 20
+    b = Batch(host, [2000, 16, 40], 4, n_layers=32, src=4096)
+    assert b.status == 0, b.error()
+    copies, ws = b.calls("copy_in")[1:], host.pced_workspace_bytes(ctypes.byref(b.cfg))
+    assert sum(c[0] for c in copies) == 2 * 2056 * 32 * 8 * 128 * 2 and max(c[0] for c in copies) <= 32 << 20
+    assert all(DEVICE <= c[1] and c[1] + c[0] <= DEVICE + ws for c in copies)
