@@ -132,10 +132,14 @@ Layout make_layout(const pced_config& c) {
   L.prev_tok = take(B * 4);
   L.beta = take(S * 4);
   // split partials: [layer][S*Hkv][stride][G][D] (bf16 or fp32) with stride <=
-  // pages per sequence; a launch takes as many layers as fit at the step's stride
-  // (room for one layer at least; for all of them up to kPartBytes)
-  L.part_slots = (size_t)c.max_seqs * c.n_kv_heads * c.max_pages_per_seq;
-  L.part_slots = std::max(L.part_slots, std::min(L.part_slots * c.n_layers, kPartBytes / ((size_t)G * c.head_dim * 4)));
+  // pages per sequence; a launch takes as many layers as fit at the step's stride.
+  // Room for any plan of one layer, and up to kPartBytes for a usual plan of all:
+  // chunks of 32 pages, or shorter ones that make one round of waves over the layers
+  // (a plan that needs more goes in several launches).
+  const size_t sh = (size_t)c.max_seqs * c.n_kv_heads, mp = c.max_pages_per_seq, nl = c.n_layers;
+  const size_t parts = std::min(nl * mp, std::max(nl * (mp / 32 + 2), 2048 / c.n_kv_heads + 2 * nl));
+  const size_t all_layers = sh * (c.dtype == PCED_BF16 ? (parts + 1) / 2 : parts);  // (slots of 4 bytes an element)
+  L.part_slots = std::max(sh * mp, std::min(all_layers, kPartBytes / ((size_t)G * c.head_dim * 4)));
   // The region also stages caches loaded from host memory (a load follows and is
   // followed by the steps on their stream, and no partial state outlives its launches): the
   // longest sequence's K and V, at most kLoadStage (longer ones go in pieces), at

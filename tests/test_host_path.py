@@ -184,3 +184,19 @@ def test_host_caches_are_staged_in_the_partial_states_region(host):
     copies, ws = b.calls("copy_in")[1:], host.pced_workspace_bytes(ctypes.byref(b.cfg))
     assert sum(c[0] for c in copies) == 2 * 2056 * 32 * 8 * 128 * 2 and max(c[0] for c in copies) <= 32 << 20
     assert all(DEVICE <= c[1] and c[1] + c[0] <= DEVICE + ws for c in copies)
+
+
+@pytest.mark.parametrize("layers,lens,kw", [
+    (32, [64] + [1024] * 8, {}), (32, [64] + [500 + 50 * i for i in range(32)], {}), (32, [16] + [30] * 64, {}),
+    (16, [16, 20000] + [40] * 6, {}), (2, [64] + [2000] * 32, {}), (32, [64] * 5, dict(dtype="f32")),
+    (32, [16] + [300] * 16, dict(n_q_heads=16, n_kv_heads=16, head_dim=64)),
+])
+def test_partial_states_of_all_layers_fit(host, layers, lens, kw):
+    b = Batch(host, lens, 4, n_layers=layers, **kw)
+    assert b.status == 0 and b.step() == 0, b.error()
+    assert [a[LAYERS] for a in b.calls("attn")] == [layers]
+
+
+def test_partial_states_take_no_more_than_a_usual_plan(host):
+    # 9 sequences x 20 pages x 32 layers: 32 MiB of staging, where the worst plan of all layers is 94 MiB
+    assert _workspace(host, max_seqs=9, max_pages=180, max_pages_per_seq=20) < 64 << 20
