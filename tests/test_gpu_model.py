@@ -194,7 +194,7 @@ def test_model_steps_two_row_tiles():
 @pytest.mark.parametrize("experts", [[15], [16], [15, 15], [23, 23]], ids=lambda e: f"{sum(e) + len(e)}-rows")
 def test_model_steps_row_tile_edges(experts):
     # 16, 17, 32 and 48 rows: the edges of one, two and three 16-row tiles in the
-    # projections' N dimension (48 is the most the split-K kernel takes)
+    # projections' N dimension (more rows: test_gpu_proj_rows.py)
     geom = W.Geometry(2, 4, 2, 64, 256, 800, "bf16")
     rng = np.random.default_rng(29 + sum(experts))
     wl = W.custom(geom, experts, rng.integers(3, 200, size=sum(experts)).tolist(), amateur_len=8, steps=1,
@@ -211,8 +211,8 @@ def test_model_prefill_then_steps_shuffled_pages():
 
 
 def test_model_many_rows_two_row_groups():
-    # 57 sequences: more than 48 rows, so the decode steps' projections go to
-    # the library GEMM too; the prefill runs as one chunk of 570 rows
+    # 57 sequences: four 16-row tiles in the decode steps' projections; the prefill
+    # runs as one chunk of 570 rows, whose projections go to the library GEMM
     geom = W.Geometry(1, 4, 1, 64, 256, 700, "bf16")
     wl = W.custom(geom, [30, 25], list(range(3, 58)), amateur_len=7, steps=2, seed=23)
     spec = ModelSpec(geom, ffn_dim=256, rope_theta=10000.0, seed=23)
