@@ -89,7 +89,7 @@ struct Layout {
   int pf_rows;          // rows of one prefill chunk (sequences x suffix tokens)
   size_t pf_proj_cols;  // slices x columns per row of the prefill projection partials
   size_t pf_proj_elems; // floats of that buffer
-  int rows_pad, nblk_fuse, nchunk, max_work;
+  int rows_pad, nchunk, max_work;
   size_t seg_slots;     // segment descriptors of the attention plan
   size_t part_slots;
   size_t part_cols;  // slices x columns one row of the projection partial buffer holds
@@ -100,7 +100,6 @@ Layout make_layout(const pced_config& c) {
   const size_t S = c.max_seqs, B = c.max_queries, es = esize_of(c);
   const int G = c.n_q_heads / c.n_kv_heads;
   L.rows_pad = ceil_div(c.max_seqs, kLmRowsPad) * kLmRowsPad;
-  L.nblk_fuse = ceil_div(c.vocab, 512);  // at most: the stand-alone fuse's slices are 512 or 1024 tokens
   L.nchunk = ceil_div(c.vocab, kBetaChunk);
   // every attention chunk holds at least one page of its own (the sequences' pages
   // are distinct, and the prefill plans by sequences too): chunks <= pages in use
@@ -156,7 +155,7 @@ Layout make_layout(const pced_config& c) {
   // (row groups of at most 288 rows; one group to spare for groups of whole queries)
   L.packed_rows = !wide ? 0 : (ceil_div(c.max_seqs, kLmWideMaxRows) + (c.max_seqs > kLmWideMaxRows ? 1 : 0)) * kLmWideMaxRows;
   L.x_packed = take((size_t)L.packed_rows * c.hidden * 2);
-  // per-slice candidates: k_fuse uses 256-column slices, the fused LM-head epilogue 128-column ones
+  // per-slice candidates: the fused LM-head epilogue's 128-token slices are the shortest
   L.fuse_part = take(B * (size_t)ceil_div(c.vocab, 128) * 5 * 4);
   L.lse_part = take(S * L.nchunk * 2 * 4);
   L.jsd_part = take(S * L.nchunk * 4);
@@ -864,7 +863,6 @@ pced_status run_model_forward(pced_ctx* c, const char* model, const FwdRows& R, 
   g.t = c->t;
   g.log2_theta = std::log2((double)cfg.rope_theta);
   g.rope = c->at<float2>(c->lay.rope);
-  g.num_cus = c->num_cus;
   g.part = R.proj_part;
   g.rho_rows = R.rho_rows;
   // (beyond the projection kernel's rows: one slice, the library GEMM's products)
@@ -1645,7 +1643,8 @@ pced_status pced_lmhead(pced_ctx* c, const void* x, int32_t n_rows, const void* 
   // the many-row kernel reads only these rows of x, through its packed copy
   if (c->bf16 && lmhead_wide_plan(n_rows, c->cfg.vocab, c->cfg.hidden).groups > 0)
     return run_lmhead(c, x, n_rows, lm_head, logits, st);
-  // the others read whole 48-row tiles: stage the rows in the padded buffer
+  // the others read x in aligned 16-byte units, k_lmhead_rows_bf16 whole 16-row tiles too: stage
+  // the rows in the padded buffer
   void* xw = c->at<void>(c->lay.x);
   HIP_OK(launch_copy_rows(x, xw, (size_t)n_rows * c->cfg.hidden * esize_of(c->cfg), st));
   return run_lmhead(c, xw, n_rows, lm_head, logits, st);

@@ -262,7 +262,6 @@ struct GemmArgs {
   // [maxpps * page][head_dim / 2]: (cos, sin) of RoPE angle pos * theta^(-2i/D)
   // for each position and pair i (launch_rope_table)
   const float2* rope;
-  int num_cus;              // compute units of the device (choice of the many-row path)
 };
 struct EmbedArgs {
   const uint16_t* embed;    // [V][hidden]
@@ -275,15 +274,14 @@ struct EmbedArgs {
   int hidden, vocab, tok_stride, ld_ss;
 };
 // Rows of one prefill chunk: row r = s*T + i is sequence s's suffix token i0 + i,
-// a virtual sequence over s's pages ending at position len_s + i. With tq > 1
-// the rows are token groups instead: row r = s*ceil(T/tq) + j covers tokens
-// tq j .. min(tq j + tq, T) - 1 and ends at its last one.
+// a virtual sequence over s's pages ending at position len_s + i. For the
+// attention's plan (tq = T) there is one row per sequence, ending at its last token.
 struct PrefillMetaArgs {
   const int32_t* len0;      // [S]
   const int32_t* page_table;// [S][maxpps]
   const int32_t* seq_query; // [S]
-  int32_t* len0_out;        // [S*T] len0[s] + i
-  int32_t* page_table_out;  // [S*T][maxpps] copy of s's row
+  int32_t* len0_out;        // [rows] len0[s] + i
+  int32_t* page_table_out;  // [rows][maxpps] copy of s's row
   int32_t* tok_map;         // [S*T] index of the row's token in tokens [B][n_tokens] (optional)
   int n_seqs, T, i0, n_tokens, maxpps;
   int tq;                   // >= 1: one output row per group of tq tokens (len0 of its last token)

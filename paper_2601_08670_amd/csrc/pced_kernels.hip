@@ -420,11 +420,12 @@ __device__ __forceinline__ void write_x4(const AttnArgs& a, const MqCol& m, int 
 // output o_j in bf16 (the fp32 path keeps acc_j in fp32). Sequences that fit
 // one split were written directly by the attention kernel.
 //
-// bf16: one wave per item (layer, sequence, kv-head, q-head). Splits go in groups of 16, merged online. Within a group, lane l loads 8
-// dims (16 bytes) of split 4 i + l / (D/8) in load i (D = 128: 4 splits per
-// load), and lane l % 16 holds (m, l) of split l % 16; a lane sums its splits in
-// order, then the lane groups are added by a butterfly (every group ends with
-// the same bits). Slots past the split count are read but never used.
+// bf16: one wave per item (layer, sequence, kv-head, q-head). Splits go in groups
+// of 16, merged online. Within a group, lane l loads 8 dims (16 bytes) of split
+// 4 i + l / (D/8) in load i (D = 128: 4 splits per load), and lane l % 16 holds
+// (m, l) of split l % 16; a lane sums its splits in order, then the lane groups
+// are added by a butterfly (every group ends with the same bits). Slots past the
+// split count are read but never used.
 template <int D>
 struct MergeShape {
   static constexpr int LPS = D / 8;     // lanes per split
@@ -482,11 +483,10 @@ __device__ __forceinline__ void merge_group(const MergeRegs<D>& R, int j0, int n
   }
 }
 
-// Sum over the lane groups and store: x_out (bf16), attn_out at `layer` and,
-// for the last layer, hidden_out (fp32 of the stored x).
+// Sum over the lane groups and store: x_out (bf16), attn_out and, for the last
+// layer, hidden_out (fp32 of the stored x).
 template <int D>
-__device__ __forceinline__ void merge_store(const AttnArgs& a, int s, int head, int layer, bool last_layer,
-                                            int lane, float den, float (&num)[8]) {
+__device__ __forceinline__ void merge_store(const AttnArgs& a, int s, int head, int lane, float den, float (&num)[8]) {
 #pragma clang fp contract(off)
   using M = MergeShape<D>;
 #pragma unroll
@@ -510,34 +510,17 @@ __device__ __forceinline__ void merge_store(const AttnArgs& a, int s, int head, 
     *(uint4*)((uint16_t*)a.x_out + row * D + d) =
         make_uint4(b[0] | (b[1] << 16), b[2] | (b[3] << 16), b[4] | (b[5] << 16), b[6] | (b[7] << 16));
   if (a.attn_out) {
-    float* p = a.attn_out + (((size_t)s * a.n_layers + layer) * a.n_q_heads + head) * D + d;
+    float* p = a.attn_out + (((size_t)s * a.n_layers + a.layer) * a.n_q_heads + head) * D + d;
     *(float4*)p = make_float4(o[0], o[1], o[2], o[3]);
     *(float4*)(p + 4) = make_float4(o[4], o[5], o[6], o[7]);
   }
-  if (last_layer && a.hidden_out) {
+  if (a.is_last_layer && a.hidden_out) {
     float* p = a.hidden_out + row * D + d;
     *(float4*)p = make_float4(bf2f(b[0]), bf2f(b[1]), bf2f(b[2]), bf2f(b[3]));
     *(float4*)(p + 4) = make_float4(bf2f(b[4]), bf2f(b[5]), bf2f(b[6]), bf2f(b[7]));
   }
 }
 
-// The whole merge of item `it` whose first group is already in R.
-template <int D>
-__device__ __forceinline__ void merge_item(const AttnArgs& a, MergeRegs<D>& R, const uint16_t* acc,
-                                           const float* ml, int s, int g, int h, int n, int layer,
-                                           bool last_layer, int lane) {
-  if (n <= 1) return;  // written directly by the attention kernel
-  const size_t w0 = (size_t)(s * a.n_kv_heads + g) * a.split_stride;
-  float m_run = kNegInf, den = 0.f;
-  float num[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int j0 = 0; j0 < n; j0 += 16) {
-    if (j0 > 0) merge_load<D>(R, acc, ml, w0, a.split_stride, a.group, h, j0, lane);
-    merge_group<D>(R, j0, n, lane, m_run, den, num);
-  }
-  merge_store<D>(a, s, g * a.group + h, layer, last_layer, lane, den, num);
-}
-
-// The merge as a launch of its own: one wave per item.
 template <int D>
 __global__ __launch_bounds__(64) void k_attn_combine_bf16(AttnArgs a) {
   const int lane = threadIdx.x;
@@ -547,9 +530,17 @@ __global__ __launch_bounds__(64) void k_attn_combine_bf16(AttnArgs a) {
   const int s = it / (Hkv * G), g = (it / G) % Hkv, h = it % G;
   const int n = a.nparts[s];
   const uint16_t* acc = (const uint16_t*)a.part_acc;
+  const size_t w0 = (size_t)(s * Hkv + g) * a.split_stride;
   MergeRegs<D> R;
-  merge_load<D>(R, acc, a.part_ml, (size_t)(s * Hkv + g) * a.split_stride, a.split_stride, G, h, 0, lane);
-  merge_item<D>(a, R, acc, a.part_ml, s, g, h, n, a.layer, a.is_last_layer != 0, lane);
+  merge_load<D>(R, acc, a.part_ml, w0, a.split_stride, G, h, 0, lane);  // (beside the load of n)
+  if (n <= 1) return;  // written directly by the attention kernel
+  float m_run = kNegInf, den = 0.f;
+  float num[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  for (int j0 = 0; j0 < n; j0 += 16) {
+    if (j0 > 0) merge_load<D>(R, acc, a.part_ml, w0, a.split_stride, G, h, j0, lane);
+    merge_group<D>(R, j0, n, lane, m_run, den, num);
+  }
+  merge_store<D>(a, s, g * G + h, lane, den, num);
 }
 
 // The merge for the prefill's token groups (items), which are many and mostly
