@@ -920,16 +920,20 @@ __device__ __forceinline__ float wave_sum(float v) {
 // accumulator (j, e) holds dims 64j + 4c + e for c = 4 quad + rr. Every product of
 // the scores starts from zero and their sums are added as a tree: its rounding
 // error is that of a sum over 64 lanes (rms 5.4e-7 of a unit-variance q.k at D =
-// 64, 8.2e-7 at 128; one accumulator through all of them: 1.2e-6 and 2.3e-6), and
-// no product waits for another (a step over 3 caches of 8192 tokens: 92.7 -> 70.2 us). Online softmax
-// in base 2, the reference moved at every page. Bound: at small shapes one
-// memory round trip per page, so the next page's loads are issued before a
-// page's products, and page ids come from the plan. NJ: 64-dim blocks of D <= 128.
-// 5 caches of 128 tokens, 2 kv-heads x 64 dims: 4.6 us (one token at a time with
-// a wave-wide sum per head and token: 18.7 us).
-template <int NJ>
-__global__ __launch_bounds__(64) void k_attn_f32(AttnArgs a, int D) {
-  constexpr int NU = 4 * NJ;  // 16-dim units of a row, at most
+// 64, 8.2e-7 at 128; one accumulator through all of them: 1.2e-6 and 2.3e-6).
+// Online softmax in base 2, the reference moved at every page. Bound: at small
+// shapes one memory round trip per page, at large ones the products and the adds
+// around them. NU: 16-dim units of a row (D <= 128), so that no product is spent on
+// units past D. Up to NU = 6 the registers are held to two waves per SIMD, which
+// also keeps the products out of the accumulation registers (reading 16 or more
+// of those per page cost more than the adds: 40 caches of 1500 tokens x 2 layers, 5
+// kv-heads x 80 dims 98 -> 77 us); up to NU = 4 there is room to hold the next page's
+// loads ahead of this page's products. 5 caches of 128 tokens, 2 kv-heads x 64 dims:
+// 4.9 us (one accumulator 4.5, one token at a time with a wave-wide sum per head and
+// token 18.7); 3 caches of 8192 tokens 53 us with the merge (one accumulator 76).
+template <int NU>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NU <= 6 ? 2 : 1, 8))) void k_attn_f32(AttnArgs a, int D) {
+  constexpr int NJ = (NU + 3) / 4;
   const int lane = threadIdx.x, col = lane & 15, quad = lane >> 4;
   const int G = a.group, Hkv = a.n_kv_heads;
   const int lc = blockIdx.x / Hkv, g = blockIdx.x % Hkv, l0 = lc / a.n_chunks, c = lc - l0 * a.n_chunks;
@@ -986,7 +990,12 @@ __global__ __launch_bounds__(64) void k_attn_f32(AttnArgs a, int D) {
       for (int e = 0; e < 4; ++e) acc[j][e] = zero;
     float m = kNegInf, l = 0.f;
     for (int i = i0; i < i1; ++i) {
-      load_page(i + 1, nxt);
+      if constexpr (NU <= 4) {  // the next page's loads go out before this one's products
+        if (i + 1 < np) load_page(i + 1, nxt);
+        __builtin_amdgcn_sched_barrier(0);
+      } else {
+        load_page(i + 1, nxt);
+      }
       f32x4 t[NU];
 #pragma unroll
       for (int u = 0; u < NU; ++u) {
@@ -996,9 +1005,9 @@ __global__ __launch_bounds__(64) void k_attn_f32(AttnArgs a, int D) {
         t[u] = (p[0] + p[1]) + (p[2] + p[3]);
       }
 #pragma unroll
-      for (int w = NU / 2; w >= 1; w /= 2)
+      for (int n = NU; n > 1; n = (n + 1) / 2)
 #pragma unroll
-        for (int u = 0; u < w; ++u) t[u] += t[u + w];
+        for (int u = (n + 1) / 2; u < n; ++u) t[u - (n + 1) / 2] += t[u];
       const f32x4 sc = t[0];
       const int tb = (i + poff) * kPage + 4 * quad;
       float z[4], mx = kNegInf;
@@ -3499,8 +3508,16 @@ hipError_t launch_attn(const AttnArgs& a, int head_dim, bool bf16, hipStream_t s
     if (head_dim == 64) return go(k_attn_bf16<64, 4>, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a);
     return hipErrorInvalidValue;
   }
-  return head_dim <= 64 ? go(k_attn_f32<1>, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a, head_dim)
-                        : go(k_attn_f32<2>, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a, head_dim);
+  switch ((head_dim + 15) / 16) {  // (head_dim <= 128)
+    case 1: return go(k_attn_f32<1>, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a, head_dim);
+    case 2: return go(k_attn_f32<2>, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a, head_dim);
+    case 3: return go(k_attn_f32<3>, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a, head_dim);
+    case 4: return go(k_attn_f32<4>, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a, head_dim);
+    case 5: return go(k_attn_f32<5>, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a, head_dim);
+    case 6: return go(k_attn_f32<6>, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a, head_dim);
+    case 7: return go(k_attn_f32<7>, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a, head_dim);
+    default: return go(k_attn_f32<8>, dim3(n_blocks), dim3(64), 0, st, t0(tm), t1(tm), a, head_dim);
+  }
 }
 
 int attn_blocks_per_cu(int head_dim, bool bf16) {
@@ -3508,8 +3525,12 @@ int attn_blocks_per_cu(int head_dim, bool bf16) {
   hipError_t e;
   if (bf16 && head_dim == 128) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_attn_bf16<128, 3>, 64, 0);
   else if (bf16) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_attn_bf16<64, 4>, 64, 0);
-  else if (head_dim <= 64) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_attn_f32<1>, 64, 0);
-  else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_attn_f32<2>, 64, 0);
+  else {
+    void (*const f32[8])(AttnArgs, int) = {k_attn_f32<1>, k_attn_f32<2>, k_attn_f32<3>, k_attn_f32<4>,
+                                           k_attn_f32<5>, k_attn_f32<6>, k_attn_f32<7>, k_attn_f32<8>};
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f32[(head_dim + 15) / 16 - 1], 64, 0);
+    n = std::min(n, 8);  // (3 caches of 8192 tokens, 2 kv-heads x 64 dims: 57 us, 75 with 12 waves per CU and their partial states)
+  }
   return (e == hipSuccess && n > 0) ? n : 8;
 }
 
