@@ -3620,7 +3620,12 @@ hipError_t launch_gemm(const GemmArgs& a, GemmEpi epi, hipStream_t st, const Tim
   const int KS = a.K / 64;
   if (a.ksplit < 1 || a.ksplit > KS) return hipErrorInvalidValue;
   if ((size_t)((KS + a.ksplit - 1) / a.ksplit) * a.n_tiles * 2048 >= 0x7FFFFFFFull) return hipErrorInvalidValue;
-  const bool fused = epi == kEpiSwiglu && a.ksplit == 1 && a.ss_in && !a.rho_in && a.ss_parts % 4 == 0 && a.ld_ss % 4 == 0;
+  // SwiGLU in the launch while its blocks fit the 256 compute units at once: in a second
+  // round every block's own sum of the row scales is exposed again. Per layer, two launches
+  // / one: F = 14336 (224 blocks) 48 rows 42.5 / 40.8 us, 64 rows 45.0 / 43.4, 128 rows 62.8 /
+  // 61.9; F = 18944 (296 blocks) 48 rows 66.8 / 67.7, 64 rows 70.8 / 72.4, 128 rows 96.6 / 103.9.
+  const bool fused = epi == kEpiSwiglu && a.ksplit == 1 && a.n_tiles <= 256 * kProjWaves && a.ss_in && !a.rho_in &&
+                     a.ss_parts % 4 == 0 && a.ld_ss % 4 == 0;
   if (fused) return go_proj<true>(a, st, t0(tm), t1(tm));
   const hipError_t e = go_proj<false>(a, st, t0(tm), nullptr);
   if (e != hipSuccess) return e;

@@ -1,5 +1,7 @@
-"""Gate/up with its epilogue in the projection launch (one K slice: hidden 256)
-at the row-tile edges up to 48 rows; the activations are compared stage-wise."""
+"""Gate/up in one K slice (hidden 256), with its epilogue in the projection launch at
+the row-tile edges up to 48 rows (more: test_gpu_proj_rows.py), and as two launches
+where the columns give more blocks than compute units; the activations are compared
+stage-wise."""
 import numpy as np
 import pytest
 
@@ -10,7 +12,7 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("rows,ffn", [(2, 64), (16, 1408), (17, 64), (33, 1408), (48, 192)])
+@pytest.mark.parametrize("rows,ffn", [(2, 64), (16, 1408), (17, 64), (33, 1408), (48, 192), (5, 16384), (17, 16448)])
 def test_swiglu_rows(rows, ffn):
     from tests.test_gpu_model import _run
     geom = W.Geometry(2, 4, 2, 64, 256, 300, "bf16")
