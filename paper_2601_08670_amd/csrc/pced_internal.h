@@ -221,7 +221,11 @@ struct SynthArgs {
 // for the M step rows, W packed in 16-row tiles (k_pack_w_bf16 layout), with an
 // epilogue per projection.
 enum GemmEpi { kEpiQkv = 0, kEpiResid = 1, kEpiSwiglu = 2 };
-constexpr int kProjMaxRows = 128;  // rows of the projection kernels (more: the library GEMM)
+// Rows of the projection kernels; more go to the library GEMM. Per layer (QKV, O, gate/up, down),
+// kernel / library: Llama-3-8B shapes 49 rows 105 / 142 us, 97 rows 136 / 166, 128 rows 153 / 204; hidden
+// 3584, MLP 18944: 49 rows 129 / 200, 128 rows 186 / 239; hidden 512, MLP 1408: 128 rows 58 / 107. Eight
+// row tiles are what the rings' 128 KiB of LDS hold; 129 rows take the library 193 us (Llama-3-8B).
+constexpr int kProjMaxRows = 128;
 constexpr int kProjMaxSplit = 16;  // K slices of a projection (partial buffer sized for this many)
 constexpr int kPrefillRows = 2304;  // (sequence, suffix token) rows of one prefill chunk, at least
 constexpr int kPrefillTiles = 2;   // 16-column query tiles of a prefill token group, at most

@@ -3808,8 +3808,11 @@ hipError_t launch_lmhead(const LmArgs& a0, bool bf16, hipStream_t st, const Timi
     return fused ? go(k_lmhead_bf16<VT, NT, true, true>, dim3(blocks), dim3(256), 0, st, t0(tm), t1(tm), b)
                  : go(k_lmhead_bf16<VT, NT, false, true>, dim3(blocks), dim3(256), 0, st, t0(tm), t1(tm), b);
   }
-  // two vocab tiles per block once one-tile blocks would come to several per compute unit
-  const bool two = a.V >= 16384;
+  // two vocab tiles per block once one-tile blocks would come to two per compute unit (512
+  // blocks at V = 8192). Hidden 1024, one tile / two: V = 4000, 32 rows 13.9 / 13.9 us, 48 rows
+  // 14.8 / 19.8; V = 8000, 32 rows 17.3 / 14.5, 48 rows 20.6 / 20.6; V = 16000, 1 row 19.4 / 14.7,
+  // 48 rows 43.3 / 28.6; hidden 4096, V = 4000, 1 row 26.0 / 28.5, V = 16000, 48 rows 160 / 105.
+  const bool two = a.V >= 8192;
   const dim3 g((a.V + (two ? 31 : 15)) / (two ? 32 : 16));
 #define PCED_F32(NT)                                                                          \
   return two ? go(k_lmhead_f32<NT, 2>, g, dim3(256), 0, st, t0(tm), t1(tm), a)                \

@@ -11,7 +11,8 @@ DEV = "cuda:0"
     (1, 2, 1, 4),         # less than one unit of the hidden dimension, one partial vocab tile
     (16, 17, 1, 36), (17, 16, 3, 12), (5, 1000, 4, 64),
     (33, 1003, 5, 80), (48, 15, 2, 100), (49, 33, 4, 128),   # 49 rows: a second row group
-    (100, 16384, 2, 20), (19, 16421, 1, 128),               # two vocab tiles per block
+    (49, 8191, 2, 20), (100, 8192, 2, 20),                  # the most with one vocab tile per block; two
+    (100, 16384, 2, 20), (19, 16421, 1, 128),
 ])
 @pytest.mark.parametrize("norm", ["rms", "none"])
 def test_lmhead_f32(rows, vocab, hq, d, norm):
