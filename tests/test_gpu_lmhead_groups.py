@@ -69,3 +69,14 @@ def test_fused_choice_over_row_groups(experts, vocab):
         got.append(sess.step(q, kn, vn, sess.pack_lm_head(w), want=want))
     for name in ("tokens", "winner", "top1", "top2"):
         assert torch.equal(got[0][name], got[1][name]), name
+
+
+@pytest.mark.parametrize("vocab", [300, 9700])  # the 48-row kernel; row groups
+def test_decoder_stack_beyond_288_rows(vocab):
+    """Rows whose scales come from the final norm's sums."""
+    from pced_inputs import workloads as W
+    from pced_inputs.model import ModelSpec
+    from tests.test_gpu_model import _run
+    geom = W.Geometry(1, 4, 1, 64, 256, vocab, "bf16")
+    wl = W.custom(geom, [150, 148], [1 + i % 7 for i in range(298)], amateur_len=3, steps=2, seed=vocab)
+    _run(wl, ModelSpec(geom, ffn_dim=128, rope_theta=10000.0, seed=vocab), steps=2)
